@@ -5,6 +5,8 @@
 // Prefill schedule (row map from moe_plan): XCD-affine column slices, see dispatch_slices_kernel.
 // Decode schedule: ONE launch, no grid-wide synchronisation: every workgroup derives the rows of its
 //   token from the routing ids themselves (see the decode section below).
+#include <algorithm>
+
 #include "device_utils.h"
 #include "launch.h"
 #include "moe_rbf.h"
@@ -21,10 +23,20 @@ namespace moe_rbf {
 #endif
 
 constexpr int kSlices = 8;   // column slices per row = XCDs per device
+constexpr int kLine = 8;     // 16-byte vectors of a 128-byte cache line
 
-// Prefill dispatch.  Work unit = (J consecutive branches of one token, column slice c of 8); a workgroup
-// holds U units.  Workgroup b handles slice c = b % 8.  Workgroups are handed to the 8 XCDs round-robin, so XCD c only
-// ever touches column slice c: the k re-reads of X[t]'s slice by the branches of a token hit in that
+// Both prefill kernels split a destination row into 8 column slices, one per XCD, cut at cache lines of the
+// DESTINATION: a line that two XCDs write halves of leaves two L2s as partial writes, and that costs far more than
+// the bytes.  (With cuts every ceil(H16 / 8) vectors, whatever line they fell into, us per dispatch of 528 MB, before /
+// now: H = 2560 98 / 84, 4608 95 / 84, 7680 88 / 81; rows that are no multiple of a line: H = 1032 214 / 116, 2056 181 /
+// 97, 4104 119 / 99, 7176 124 / 87; H = 640, 378 MB: 175 / 64.)  A row that starts `a` vectors into its first line
+// touches n = ceil((a + H16) / 8) lines; slice c holds the lines [c*n/8, (c+1)*n/8).  Where n is no multiple of 8
+// the slices differ by a line, so slice c of token t goes to XCD (c - t) mod 8: every XCD gets its share of the longer
+// ones, and a (token, slice) still belongs to one XCD, whose L2 serves its k reads.
+
+// Prefill dispatch in token order, for rows that start at a cache line.  Work unit = (J consecutive branches of one token,
+// one column slice); a workgroup holds U units.  Workgroups are handed to the 8 XCDs round-robin, so workgroup b runs on
+// XCD b % 8 and the k re-reads of X[t]'s slice by the branches of a token hit in that
 // XCD's L2 (X is fetched from HBM once), every wave issues few 16-byte stores per lane, and the 8 XCDs
 // together lay down whole destination rows.  Stores are streaming (nontemporal) so that they do not
 // evict the X slices from L2; loads are ordinary so that they stay.
@@ -32,23 +44,24 @@ constexpr int kSlices = 8;   // column slices per row = XCDs per device
 template <int BLOCK, int J, int U>
 __global__ __launch_bounds__(BLOCK) void dispatch_slices_kernel(const u32x4 *__restrict__ X,
                                                                 const int32_t *__restrict__ row_map,
-                                                                u32x4 *__restrict__ window, int k, int H16, int slice,
+                                                                u32x4 *__restrict__ window, int k, int H16, int rotate,
                                                                 int N) {
   // U units per workgroup, each with BLOCK / U lanes: narrow slices (small H) still fill the workgroup
   constexpr int kLanes = BLOCK / U;
   const int unit = U == 1 ? 0 : (int)threadIdx.x / kLanes;
   const int lane = U == 1 ? (int)threadIdx.x : (int)threadIdx.x % kLanes;
   const int g = (blockIdx.x / kSlices) * U + unit;
-  const int c = blockIdx.x % kSlices;
   const int n = g * J;                       // J consecutive branches of one token (J divides k)
   if (U > 1 && n >= N) return;
   int row[J];
 #pragma unroll
   for (int u = 0; u < J; ++u) row[u] = kLanes % kWave == 0 ? uniform(row_map[n + u]) : row_map[n + u];
   const int t = n / k;
-  const int end = min((c + 1) * slice, H16);
+  const int c = (blockIdx.x + (t & rotate)) % kSlices;         // rotate: 7, or 0 where the slices are equal
+  const int lines = (H16 + kLine - 1) / kLine;
+  const int begin = ((c * lines) >> 3) * kLine, end = min(((c * lines + lines) >> 3) * kLine, H16);
   const u32x4 *src = X + (size_t)t * (size_t)H16;
-  for (int col = c * slice + lane; col < end; col += kLanes) {
+  for (int col = begin + lane; col < end; col += kLanes) {
     const u32x4 v = src[col];
 #pragma unroll
     for (int u = 0; u < J; ++u)
@@ -56,29 +69,65 @@ __global__ __launch_bounds__(BLOCK) void dispatch_slices_kernel(const u32x4 *__r
   }
 }
 
-// Prefill dispatch along the plan's order list: unit p copies column slice c of X[token] to window[row] for
-// the p-th (token, row) pair.  The pairs are sorted by row inside stretches of tokens whose X slices fit the
-// L2 of an XCD, so consecutive workgroups of an XCD write consecutive rows of one expert block and re-read
-// tokens from L2.  U units per workgroup, each with 128 / U lanes, as in dispatch_slices_kernel.
-template <int U>
-__global__ __launch_bounds__(128) void dispatch_list_kernel(const u32x4 *__restrict__ X,
-                                                            const int32_t *__restrict__ order,
-                                                            u32x4 *__restrict__ window, int H16, int slice, int N) {
+// Vector offset of a row: one 32 x 32 -> 64 bit product (a sign-extended index would take three multiplications a lane).
+__device__ __forceinline__ size_t row_offset(int row, int H16) {
+  return (size_t)((unsigned long long)(unsigned)row * (unsigned)H16);
+}
+
+// Prefill dispatch, one unit per (branch, column slice).  LIST: along the plan's order list, unit p copies a slice of
+// X[token] to window[row] for the p-th (token, row) pair.  The pairs are sorted by row inside stretches of tokens whose X
+// slices fit the L2 of an XCD, so consecutive workgroups of an XCD write consecutive rows of one expert block and re-read
+// tokens from L2.  Without LIST: in token order, for narrow rows and for rows that do not start at a cache line (ALIGNED =
+// false; their cuts differ from branch to branch).  ROTATE: the slices are not all equal (see above; always so without ALIGNED).
+// A unit takes `lanes` = the longest slice's vectors, and a workgroup is U units side by side without a gap, about
+// 4 waves: units padded to 64 or 128 lanes leave up to half of a wave idle while workgroups can only be started at
+// about 4.7 per ns (H = 4608: 84 us against 95 with 72 of 128 lanes busy).  Unequal short slices leave lanes idle all
+// the same; there Q = 2 consecutive branches per unit pay (H = 640 77 -> 64 us, 768 86 -> 72), while equal or longer
+// slices lose with them (H = 1536 82 -> 88, 3072 81 -> 88, 8192 74 -> 86: more writes in flight arrive in less order).
+template <int Q, bool LIST, bool ROTATE, bool ALIGNED>
+__global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__restrict__ X,
+                                                             const int32_t *__restrict__ entries,
+                                                             u32x4 *__restrict__ window, int k, int H16, int misalign,
+                                                             int N, int lanes, unsigned magic, int U) {
   typedef int i32x2 __attribute__((ext_vector_type(2)));
-  constexpr int kLanes = 128 / U;
-  const int unit = U == 1 ? 0 : (int)threadIdx.x / kLanes;
-  const int lane = U == 1 ? (int)threadIdx.x : (int)threadIdx.x % kLanes;
-  const int pidx = (blockIdx.x / kSlices) * U + unit;
-  const int c = blockIdx.x % kSlices;
-  if (pidx >= N) return;
-  i32x2 pair = ((const i32x2 *)order)[pidx];
-  if (kLanes % kWave == 0) pair = i32x2{uniform(pair[0]), uniform(pair[1])};
-  const int t = pair[0], row = pair[1];
-  if (t < 0 || row < 0) return;
-  const int end = min((c + 1) * slice, H16);
-  const u32x4 *src = X + (size_t)t * (size_t)H16;
-  u32x4 *dst = window + (size_t)row * (size_t)H16;
-  for (int col = c * slice + lane; col < end; col += kLanes) store_stream(dst + col, src[col]);
+  const int unit = (int)__umulhi(threadIdx.x, magic);          // threadIdx.x / lanes
+  const int lane = (int)threadIdx.x - (int)__umul24(unit, lanes);
+  const int p0 = (int)(blockIdx.x / kSlices) * U * Q + unit * Q;
+  int t[Q], row[Q], col[Q], end[Q];
+  u32x4 v[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int p = p0 + q;
+    t[q] = row[q] = -1;
+    if (p < N) {
+      if (LIST) {
+        const i32x2 pair = ((const i32x2 *)entries)[p];
+        t[q] = pair[0], row[q] = pair[1];
+      } else {
+        t[q] = p / k, row[q] = entries[p];
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int a = ALIGNED ? 0 : (misalign + (int)((unsigned)row[q] * (unsigned)H16)) & (kLine - 1);
+    const int c = (blockIdx.x + (ROTATE ? t[q] : 0)) % kSlices;
+    const int n = (a + H16 + kLine - 1) / kLine;
+    const int cn = (int)__umul24(c, n);
+    col[q] = (cn >> 3) * kLine - a + lane;                     // below 0: the line's part in front of the row
+    end[q] = min(((cn + n) >> 3) * kLine - a, H16);
+    if (!ALIGNED && col[q] < 0) col[q] += lanes;               // (past the slice, unless it is longer than a workgroup)
+    if ((t[q] | row[q]) < 0) end[q] = 0;                       // nothing to do
+    if (col[q] < end[q]) v[q] = X[row_offset(t[q], H16) + (unsigned)col[q]];
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (col[q] >= end[q]) continue;
+    store_stream(window + (row_offset(row[q], H16) + (unsigned)col[q]), v[q]);
+    if (Q == 1)                                                // slices longer than a workgroup
+      for (int x = col[q] + lanes; x < end[q]; x += lanes)
+        store_stream(window + (row_offset(row[q], H16) + (unsigned)x), X[row_offset(t[q], H16) + (unsigned)x]);
+  }
 }
 
 // ---- decode -------------------------------------------------------------------------------------
@@ -380,34 +429,54 @@ __global__ __launch_bounds__(BLOCK) void dispatch_quant_rows_kernel(const u32x4 
 }
 
 template <int J, int U>
-static hipError_t launch_dispatch_ju(const Dims &d, const void *x, const PlanView &p, void *window, int slice,
+static hipError_t launch_dispatch_ju(const Dims &d, const void *x, const PlanView &p, void *window, int rotate,
                                      hipStream_t s) {
   const unsigned units = (unsigned)(d.N / J);
   const dim3 grid((units + U - 1) / U * (unsigned)kSlices);
   return launch(dispatch_slices_kernel<128, J, U>, grid, dim3(128), 0, s, (const u32x4 *)x,
-                (const int32_t *)p.row_map, (u32x4 *)window, d.k, d.H16, slice, d.N);
+                (const int32_t *)p.row_map, (u32x4 *)window, d.k, d.H16, rotate, d.N);
 }
 
-static hipError_t launch_dispatch_list(const Dims &d, const void *x, const PlanView &p, void *window, hipStream_t s) {
-  // units per workgroup: as many as fit 128 lanes (a unit has as many lanes as its slice has vectors, rounded up
-  // to a power of two, at least 16)
-  const int slice = (d.H16 + kSlices - 1) / kSlices;
-  const int U = slice > 64 ? 1 : slice > 32 ? 2 : slice > 16 ? 4 : 8;
-  const dim3 grid(((unsigned)d.N + U - 1) / U * (unsigned)kSlices);
+static hipError_t launch_dispatch_units(const Dims &d, const void *x, const PlanView &p, void *window, bool list,
+                                        hipStream_t s) {
+  constexpr int kMost = 640;                                   // threads of a workgroup
+  const int misalign = (int)(((uintptr_t)window >> 4) & (kLine - 1));
+  const bool aligned = misalign == 0 && d.H16 % kLine == 0;
+  const int lines = (d.H16 + (aligned ? 0 : kLine - 1) + kLine - 1) / kLine;      // lines a row touches at most
+  const bool rotate = !aligned || lines % kSlices != 0;
+  const int lanes = std::min((lines + kSlices - 1) / kSlices * kLine, 512);
+  // units per workgroup: about 256 threads, a whole number of waves where that is near
+  int U = std::max(1, 256 / lanes);
+  for (int u = U; u >= 1 && U * lanes % kWave != 0; --u)
+    if (u * lanes % kWave == 0) U = u;
+  for (int u = U; u * lanes <= kMost && U * lanes % kWave != 0; ++u)
+    if (u * lanes % kWave == 0) U = u;
+  const unsigned magic = (unsigned)(((1ull << 32) + lanes - 1) / lanes);
+  const int Q = rotate && lanes <= 40 ? 2 : 1;
+  const unsigned per = (unsigned)(U * Q);
+  const dim3 grid(((unsigned)d.N + per - 1) / per * (unsigned)kSlices);
   auto go = [&](auto kernel) {
-    return launch(kernel, grid, dim3(128), 0, s, (const u32x4 *)x, (const int32_t *)p.order, (u32x4 *)window, d.H16,
-                  slice, d.N);
+    return launch(kernel, grid, dim3((unsigned)(U * lanes)), 0, s, (const u32x4 *)x,
+                  (const int32_t *)(list ? p.order : p.row_map), (u32x4 *)window, d.k, d.H16, misalign, d.N, lanes, magic,
+                  U);
   };
-  switch (U) {
-    case 1: return go(dispatch_list_kernel<1>);
-    case 2: return go(dispatch_list_kernel<2>);
-    case 4: return go(dispatch_list_kernel<4>);
-    default: return go(dispatch_list_kernel<8>);
+  if (!list) {
+    if (!aligned) return Q == 2 ? go(dispatch_units_kernel<2, false, true, false>) : go(dispatch_units_kernel<1, false, true, false>);
+    if (!rotate) return go(dispatch_units_kernel<1, false, false, true>);
+    return Q == 2 ? go(dispatch_units_kernel<2, false, true, true>) : go(dispatch_units_kernel<1, false, true, true>);
   }
+  if (!aligned) return Q == 2 ? go(dispatch_units_kernel<2, true, true, false>) : go(dispatch_units_kernel<1, true, true, false>);
+  if (!rotate) return go(dispatch_units_kernel<1, true, false, true>);
+  return Q == 2 ? go(dispatch_units_kernel<2, true, true, true>) : go(dispatch_units_kernel<1, true, true, true>);
 }
 
 hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void *window, hipStream_t s) {
-  if (d.order_tiles > 0 && p.order) return launch_dispatch_list(d, x, p, window, s);
+  if (d.order_tiles > 0 && p.order) return launch_dispatch_units(d, x, p, window, true, s);
+  // Rows that do not start at a cache line, and narrow rows while X is no larger than the Infinity Cache (us per
+  // dispatch, units / token-order slices: H = 512, T = 32768 47 / 53; H = 640, T = 10000 20.6 / 21.1).
+  const bool x_cold = (int64_t)d.T * d.H16 * 16 > ((int64_t)256 << 20);
+  if (d.H16 % kLine != 0 || ((uintptr_t)window >> 4) % kLine != 0 || (d.H16 < 96 && !x_cold))
+    return launch_dispatch_units(d, x, p, window, false, s);
   // A workgroup should move a few KB, so that the grid stays within what the dispatcher sustains (about 3000
   // workgroups per microsecond), with its lanes busy.
   //   Normally one unit per workgroup; a unit takes J branches of its token until it moves 4 KB (1.75 KB
@@ -419,7 +488,9 @@ hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void
   // Measured in a plan -> dispatch -> combine sequence, k = 8, us per dispatch, this rule / one unit only:
   //   H = 512, T = 131072: 212 / 544;  H = 1024, T = 131072: 466 / 828;  H = 2048, T = 65536: 436 / 459;
   //   H = 2048, k = 6, T = 8192: 37 / 58 (launches alone).
-  const int slice = (d.H16 + kSlices - 1) / kSlices;
+  const int lines = d.H16 / kLine;
+  const int slice = (lines + kSlices - 1) / kSlices * kLine;
+  const int rotate = lines % kSlices != 0 ? kSlices - 1 : 0;
   const int slice_bytes = slice * 16;
   int lanes = 8;                                   // lanes of a unit
   while (lanes < 128 && lanes < slice) lanes *= 2;
@@ -431,7 +502,7 @@ hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void
   // so fewer, larger units do better there: 2 branches per unit, 8 where a slice is a single wave.
   // Measured, k = 8, us per dispatch with this rule / without: H = 7168: T = 20480 501 / 752, 24576 632 / 915,
   // 32768 943 / 1292; H = 4096, T = 65536: 957 / 1064 (J = 4) / 1961 (J = 1).
-  if ((int64_t)d.T * d.H16 * 16 > ((int64_t)256 << 20)) {
+  if (x_cold) {
     const int most = slice <= 64 ? 8 : 2;
     while (J < most && d.k % (2 * J) == 0) J *= 2;
   }
@@ -441,7 +512,7 @@ hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void
     J = 1;
     while (J < 8 && U * J * slice_bytes < want && d.k % (2 * J) == 0) J *= 2;
   }
-#define GO(J_, U_) if (J == J_ && U == U_) return launch_dispatch_ju<J_, U_>(d, x, p, window, slice, s)
+#define GO(J_, U_) if (J == J_ && U == U_) return launch_dispatch_ju<J_, U_>(d, x, p, window, rotate, s)
   GO(1, 1); GO(2, 1); GO(4, 1); GO(8, 1);
   GO(1, 2); GO(2, 2); GO(4, 2); GO(8, 2);
   GO(1, 4); GO(2, 4); GO(4, 4); GO(8, 4);

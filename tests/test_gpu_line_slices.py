@@ -1,0 +1,52 @@
+"""Prefill dispatch where its column slices, cut at cache lines of the destination, can go wrong: rows of one vector, of
+fewer lines than slices, one vector short of and past a line and a slice, slices that differ by a line, slices longer than
+a workgroup, windows that do not start at a line; along the order list and in token order."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def moe():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_06055_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.mark.parametrize("H16", [1, 7, 8, 9, 63, 64, 65, 72, 96, 97, 128, 136, 257, 320, 321, 513, 576, 960, 1000, 4096, 4104, 5001])
+@pytest.mark.parametrize("shift", [0, 1, 7])                   # 16-byte vectors from a line to the window's first row
+def test_dispatch_writes_every_vector_once(moe, H16, shift):
+    from paper_2605_06055_amd.layer import to_device, to_host
+    rng = np.random.default_rng(H16 * 8 + shift)
+    H, k, E, R = H16 * 8, (8, 6, 5)[shift % 3], 48, 4
+    T = max(40, min(3000, (6 << 20) // (H * 2)))               # X just past the size from which the list is used
+    N = T * k
+    K = wl.random_routing(rng, T, k, E, p_masked=0.04, p_invalid=0.01)
+    X = rng.integers(0, 1 << 16, size=(T, H), dtype=np.uint16)                     # any bits: dispatch copies
+    ref = oracle.plan(K, E, R)
+    want = oracle.dispatch(X, ref.row_map, ref.window_rows, fill=np.uint16(0x7B7B))
+    xd, kd = to_device(X), to_device(K)
+    for with_order in (True, False):
+        print(f"[slices] H16={H16} T={T} k={k} shift={shift} list={with_order}", flush=True)
+        shape = moe.MoeShape(T=T, H=H, k=k, E=E, R=R, dtype=moe.MOE_DTYPE_BF16, schedule=moe.MOE_SCHEDULE_PREFILL)
+        plan = moe.MoePlan(shape, with_order=with_order)
+        buf = torch.full(((N + 2) * H + 128,), 0x7B7B, dtype=torch.int16, device="cuda")
+        assert buf.data_ptr() % 128 == 0
+        window = buf[shift * 8:shift * 8 + N * H].view(N, H)
+        moe.moe_plan(shape, kd, plan)
+        moe.moe_dispatch(shape, xd, kd, plan, window)
+        torch.cuda.synchronize()
+        got = to_host(buf).view(np.uint16)
+        rows = got[shift * 8:shift * 8 + N * H].reshape(N, H)
+        assert np.array_equal(rows[:ref.window_rows], want)
+        # nothing else is written: in front of the window, in its unused rows, behind it
+        assert np.all(got[:shift * 8] == 0x7B7B) and np.all(rows[ref.window_rows:] == 0x7B7B)
+        assert np.all(got[shift * 8 + N * H:] == 0x7B7B)
