@@ -24,6 +24,7 @@ namespace moe_rbf {
 
 constexpr int kSlices = 8;   // column slices per row = XCDs per device
 constexpr int kLine = 8;     // 16-byte vectors of a 128-byte cache line
+constexpr int kWarmTokens = 8;
 
 // Both prefill kernels split a destination row into 8 column slices, one per XCD, cut at cache lines of the
 // DESTINATION: a line that two XCDs write halves of leaves two L2s as partial writes, and that costs far more than
@@ -84,15 +85,49 @@ __device__ __forceinline__ size_t row_offset(int row, int H16) {
 // about 4.7 per ns (H = 4608: 84 us against 95 with 72 of 128 lanes busy).  Unequal short slices leave lanes idle all
 // the same; there Q = 2 consecutive branches per unit pay (H = 640 77 -> 64 us, 768 86 -> 72), while equal or longer
 // slices lose with them (H = 1536 82 -> 88, 3072 81 -> 88, 8192 74 -> 86: more writes in flight arrive in less order).
-template <int Q, bool LIST, bool ROTATE, bool ALIGNED>
+// WARM (with LIST, for an X that no longer fits the Infinity Cache beside the window): the grid's y dimension walks the
+// stretches, and the first warm_blocks workgroups of each read the stretch's X, every XCD the slices that its units are
+// about to copy.  The list asks for a token's row at k scattered moments while the chip is saturated with writes; what is
+// not cached then comes in 1 KB pieces, and the write stream waits behind them.  Read in bulk, 24 MB at a time and just
+// before it is used, X costs little more than its bytes.  Nothing waits for the reads: they are a hint.
+// us per layer, token order / list / list with bulk reads, X not cached when the layer starts: H = 7168: T = 8192 485 / 420 /
+// 383, 13000 760 / 699 / 602, Zipf 16384 933 / 812 / 725; H = 8192, T = 12000 768 / 656 / 609; H = 4096: T = 24000 633 / 683 /
+// 605, 11000 294 (list) / 268; H = 3072, k = 10, T = 32768 1087 / 908 / 799; H = 4096, k = 3, T = 16000 263 / 212 / 188; X
+// fully cached: H = 7168: T = 8192 356 / 357 / 371, 16384 709 / 718 / 741; H = 4096, T = 20000 505 / 466 / 479.
+template <int Q, bool LIST, bool ROTATE, bool ALIGNED, bool WARM>
 __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__restrict__ X,
                                                              const int32_t *__restrict__ entries,
                                                              u32x4 *__restrict__ window, int k, int H16, int misalign,
-                                                             int N, int lanes, unsigned magic, int U) {
+                                                             int N, int lanes, unsigned magic, int U, int T,
+                                                             int warm_blocks, int stretch) {
   typedef int i32x2 __attribute__((ext_vector_type(2)));
   const int unit = (int)__umulhi(threadIdx.x, magic);          // threadIdx.x / lanes
   const int lane = (int)threadIdx.x - (int)__umul24(unit, lanes);
-  const int p0 = (int)(blockIdx.x / kSlices) * U * Q + unit * Q;
+  int block = (int)blockIdx.x, stretch_start = 0;
+  if (WARM) {
+    stretch_start = (int)blockIdx.y * stretch;
+    if (block < warm_blocks) {                                 // warm_blocks is a multiple of 8: XCD = block % 8
+      const int first = stretch_start / k + ((block / kSlices) * U + unit) * kWarmTokens;
+      const int last = min(min(first + kWarmTokens, (stretch_start + stretch + k - 1) / k), T);
+      const int n = (H16 + kLine - 1) / kLine;
+      u32x4 w[kWarmTokens];
+#pragma unroll
+      for (int i = 0; i < kWarmTokens; ++i) {
+        const int c = (block + (ROTATE ? first + i : 0)) % kSlices;
+        const int cn = (int)__umul24(c, n);
+        const int x = (cn >> 3) * kLine + lane, stop = min(((cn + n) >> 3) * kLine, H16);
+        w[i] = first + i < last && x < stop ? X[row_offset(first + i, H16) + (unsigned)x] : u32x4{0u, 0u, 0u, 0u};
+      }
+      unsigned used = 0;
+#pragma unroll
+      for (int i = 0; i < kWarmTokens; ++i) used |= w[i][0];
+      asm volatile("" ::"v"(used));      // the loads are kept although nothing uses their values
+      return;
+    }
+    block -= warm_blocks;
+    N = min(N, stretch_start + stretch);
+  }
+  const int p0 = stretch_start + (block / kSlices) * U * Q + unit * Q;
   int t[Q], row[Q], col[Q], end[Q];
   u32x4 v[Q];
 #pragma unroll
@@ -453,21 +488,34 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
     if (u * lanes % kWave == 0) U = u;
   const unsigned magic = (unsigned)(((1ull << 32) + lanes - 1) / lanes);
   const int Q = rotate && lanes <= 40 ? 2 : 1;
-  const unsigned per = (unsigned)(U * Q);
-  const dim3 grid(((unsigned)d.N + per - 1) / per * (unsigned)kSlices);
+  const int per = U * Q;
+  dim3 grid((unsigned)((d.N + per - 1) / per * kSlices));
+  const bool warm = list && order_streams_x(d);
+  int stretch = 0, warm_blocks = 0;
+  if (warm) {
+    stretch = d.order_tiles * plan_tile_size(d.N);
+    const int tokens = stretch / d.k + 2;                      // a stretch may begin and end inside a token
+    warm_blocks = (tokens + U * kWarmTokens - 1) / (U * kWarmTokens) * kSlices;
+    grid = dim3((unsigned)(warm_blocks + (stretch + per - 1) / per * kSlices), (unsigned)((d.N + stretch - 1) / stretch));
+  }
   auto go = [&](auto kernel) {
     return launch(kernel, grid, dim3((unsigned)(U * lanes)), 0, s, (const u32x4 *)x,
                   (const int32_t *)(list ? p.order : p.row_map), (u32x4 *)window, d.k, d.H16, misalign, d.N, lanes, magic,
-                  U);
+                  U, d.T, warm_blocks, stretch);
   };
-  if (!list) {
-    if (!aligned) return Q == 2 ? go(dispatch_units_kernel<2, false, true, false>) : go(dispatch_units_kernel<1, false, true, false>);
-    if (!rotate) return go(dispatch_units_kernel<1, false, false, true>);
-    return Q == 2 ? go(dispatch_units_kernel<2, false, true, true>) : go(dispatch_units_kernel<1, false, true, true>);
+#define GO(LIST_, WARM_)                                                                                     \
+  if (list == LIST_ && warm == WARM_) {                                                                      \
+    if (!aligned) return Q == 2 ? go(dispatch_units_kernel<2, LIST_, true, false, WARM_>)                    \
+                                : go(dispatch_units_kernel<1, LIST_, true, false, WARM_>);                   \
+    if (!rotate) return go(dispatch_units_kernel<1, LIST_, false, true, WARM_>);                             \
+    return Q == 2 ? go(dispatch_units_kernel<2, LIST_, true, true, WARM_>)                                   \
+                  : go(dispatch_units_kernel<1, LIST_, true, true, WARM_>);                                  \
   }
-  if (!aligned) return Q == 2 ? go(dispatch_units_kernel<2, true, true, false>) : go(dispatch_units_kernel<1, true, true, false>);
-  if (!rotate) return go(dispatch_units_kernel<1, true, false, true>);
-  return Q == 2 ? go(dispatch_units_kernel<2, true, true, true>) : go(dispatch_units_kernel<1, true, true, true>);
+  GO(false, false)
+  GO(true, false)
+  GO(true, true)
+#undef GO
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void *window, hipStream_t s) {

@@ -50,6 +50,9 @@ bool plan_uses_workspace(int64_t N);
 // token order and the list is neither written nor read.  Depends on the shape only, so that moe_plan, the
 // decode-schedule dispatch (which leaves a plan) and the prefill-schedule dispatch agree.
 int plan_order_tiles(const Dims &d);
+// Does the dispatch along the order list read each stretch of X in bulk before it copies it?  (X too large to be
+// still cached beside the window.)
+bool order_streams_x(const Dims &d);
 
 hipError_t launch_plan_empty(const Dims &d, const PlanView &p, hipStream_t s);
 hipError_t launch_plan(const Dims &d, const int32_t *K, const PlanView &p, int32_t *tile_hist, const WarmRange &warm,

@@ -308,7 +308,8 @@ bool plan_uses_workspace(int64_t N) { return N > (int64_t)MOE_PLAN_FUSED_MAX_TIL
 // X still being in the Infinity Cache when the dispatch starts (the list makes every token row be fetched at
 // k scattered moments of its stretch), so the list is used
 //   for rows of 12 KB or more while X holds at most 96 MiB and the window at most 770 MiB,
-//   for narrower rows (8 to 12 KB, and 2 to 4 KB) with windows of up to 1100 MiB.
+//   for narrower rows with windows of up to 1100 MiB,
+// and for larger X with bulk reads (order_streams_x).
 // Rows of 2 to 4 KB, us per layer with the list / in token order: H = 2048: T = 8192 105.4 / 108.0, 16384 197.0 / 204.3,
 // 32768 388.6 / 407.6; H = 1024: T = 16384 110.0 / 113.4, 65536 405.7 / 426.0.  With slices cut at cache lines and units
 // packed side by side the same holds for every width from 1.5 KB on (sum of the kernels' us): H = 2560, T = 11468
@@ -316,19 +317,26 @@ bool plan_uses_workspace(int64_t N) { return N > (int64_t)MOE_PLAN_FUSED_MAX_TIL
 // Narrower rows pay more for the list in the plan than dispatch gains (H = 640, T = 10000 59.2 / 57.2), and so do
 // batches whose X is in the L2s anyway: H = 2048, T = 1400 26.9 / 26.5; H = 2560, T = 1024 23.5 / 23.1; but H = 3072,
 // T = 1400 (8.6 MB) 34.5 / 35.7.
-int plan_order_tiles(const Dims &d) {
+// From 80 MiB of X on the list is used at every window size with X read in bulk (order_streams_x), except for degrees that
+// re-read X too little: us per layer, X not cached, list with bulk reads / the rule above: k = 2: H = 7168, T = 14000 225.5 /
+// 214.6; H = 4096, T = 28000 246 / 266; k = 1: H = 4096, T = 20000 128 / 122; around the line: H = 7168: T = 5000 (72 MB)
+// 217 / 209, 6200 (89 MB) 280 / 294; H = 2560, T = 14000 (72 MB) 219 / 216; H = 4096, T = 11000 (90 MB) 267 / 295.
+bool order_streams_x(const Dims &d) {
   const int64_t row_bytes = (int64_t)d.H16 * 16;
-  if (d.H16 < 96 || (int64_t)d.T * row_bytes <= ((int64_t)5 << 20)) return 0;
-#ifndef MOE_ORDER_LIMIT_SCALE
-#define MOE_ORDER_LIMIT_SCALE 1          // tuning knob: scales all limits
-#endif
-  const int64_t mib = (int64_t)MOE_ORDER_LIMIT_SCALE << 20;
-  const int64_t window = (int64_t)d.N * row_bytes, x = (int64_t)d.T * row_bytes;
-  if (row_bytes < 12288 ? window > 1100 * mib : (window > 770 * mib || x > 96 * mib)) return 0;
+  return (int64_t)d.T * row_bytes > ((int64_t)80 << 20) && (d.k >= 3 || (d.k == 2 && row_bytes < 12288));
+}
+
+int plan_order_tiles(const Dims &d) {
+  const int64_t row_bytes = (int64_t)d.H16 * 16, x = (int64_t)d.T * row_bytes, window = (int64_t)d.N * row_bytes;
+  constexpr int64_t mib = 1 << 20;
+  if (d.H16 < 96 || x <= 5 * mib) return 0;
+  const bool bulk = order_streams_x(d);
+  if (!bulk && (row_bytes < 12288 ? window > 1100 * mib : (window > 770 * mib || x > 96 * mib))) return 0;
   const int tile = plan_tile_size(d.N), tiles = plan_tile_count(d.N);
   if (!plan_uses_workspace(d.N)) return tiles;                      // single-launch plan: the batch is one stretch
-  // stretches of about 28 MB of X, all of (nearly) the same length
-  const int64_t most = ((int64_t)28 << 20) / row_bytes * d.k / tile;
+  // stretches of about 28 MB of X (24 MB where it is read in bulk: with 20 or 28 MB the layers above differ by 2 % either
+  // way), all of (nearly) the same length
+  const int64_t most = (bulk ? 24 : 28) * mib / row_bytes * d.k / tile;
   if (most < 1) return 1;
   const int64_t n = (tiles + most - 1) / most;
   return (int)((tiles + n - 1) / n);

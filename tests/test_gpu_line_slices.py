@@ -50,3 +50,30 @@ def test_dispatch_writes_every_vector_once(moe, H16, shift):
         # nothing else is written: in front of the window, in its unused rows, behind it
         assert np.all(got[:shift * 8] == 0x7B7B) and np.all(rows[ref.window_rows:] == 0x7B7B)
         assert np.all(got[shift * 8 + N * H:] == 0x7B7B)
+
+
+@pytest.mark.parametrize("T,H,k,stride", [(2700, 16392, 3, 0),       # one stretch (single-launch plan), ragged rows
+                                          (9001, 4872, 3, 0),        # stretches that begin and end inside a token
+                                          (9000, 4864, 5, 7000),     # unequal slices, dropped branches, ragged last stretch
+                                          (29000, 1536, 2, 0)])      # two branches per unit
+def test_dispatch_with_bulk_reads_of_x(moe, T, H, k, stride):
+    """X of more than 80 MiB: the list's stretches are read in bulk ahead of their copies."""
+    from paper_2605_06055_amd.layer import MoeLayer, to_device, to_host
+    rng = np.random.default_rng(T)
+    E, R = 48, 6
+    assert T * H * 2 > 80 << 20
+    K = wl.random_routing(rng, T, k, E, p_masked=0.03, p_invalid=0.01)
+    ref = oracle.plan(K, E, R, stride)
+    print(f"[bulk] T={T} H={H} k={k} stride={stride}", flush=True)
+    layer = MoeLayer(T, H, k, E, R, region_stride_rows=stride, schedule=moe.MOE_SCHEDULE_PREFILL)
+    x = torch.randint(-(1 << 15), 1 << 15, (T, H), dtype=torch.int16, device="cuda")
+    bits = layer.window.view(torch.int16)
+    bits.fill_(0x7B7B)
+    layer.dispatch(x.view(torch.bfloat16), to_device(K))
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(layer.plan.row_map)[:T * k].reshape(T, k), ref.row_map)
+    rows = torch.from_numpy(ref.row_map.reshape(-1).astype(np.int64)).cuda()
+    at = torch.full((bits.shape[0],), -1, dtype=torch.int64, device="cuda")
+    at[rows[rows >= 0]] = (torch.arange(T * k, device="cuda") // k)[rows >= 0]
+    assert torch.equal(bits[at >= 0], x[at[at >= 0]])
+    assert bool((bits[at < 0] == 0x7B7B).all())
