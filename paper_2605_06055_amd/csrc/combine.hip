@@ -9,6 +9,8 @@
 // row is read exactly once and Y is written exactly once, in token order: no un-permute buffer.
 // Row ids and weights are uniform per workgroup and live in scalar registers.
 #include <atomic>
+#include <type_traits>
+#include <utility>
 
 #include "device_utils.h"
 #include "launch.h"
@@ -119,16 +121,60 @@ __global__ __launch_bounds__(BLOCK) void combine_rows_kernel(const u32x4 *__rest
   store_stream(Y + (size_t)t * (size_t)H16 + col, acc.result());
 }
 
-// Large launches: a persistent grid, one workgroup of 8 waves per compute unit, whose threads keep the results
-// of R units in registers and store them only after the last row load of the round.  All waves run the same
+// Large launches: a persistent grid, one workgroup of 8 waves per compute unit, whose threads hold the results of up to
+// 56 units and store them only after the last row load of the launch.  All waves run the same
 // amount of work, so chip-wide the reads come first and the 11 % of writes follow in a burst instead of being
-// mixed into the read stream (measured inside plan -> dispatch -> combine layers, H = 7168, k = 8, R = 28:
+// mixed into the read stream (measured inside plan -> dispatch -> combine layers, H = 7168, k = 8, 28 units held:
 // T = 4096 179.3-180.0 against 184.4-185.3 us per layer, T = 8192 351.6 / 360.4, Zipf T = 16384 676.6 / 681.3).
-// T = 4096 is exactly one round of 28 units per thread on 256 CUs.  Same arithmetic as combine_rows_kernel
+// Every change from reading to writing costs about 6 us (the CUs do not finish together, and the write burst has to start),
+// so a thread holds as many results as the CU has room for: 36 in registers (144 of the 256 VGPRs that 8 waves may take)
+// and 20 in the 160 KB of LDS, which are otherwise idle.  us per layer, X not cached, 28 units and two rounds per launch /
+// up to 56 units and one: H = 7168: T = 5000 209.4 / 204.5, 6200 281 / 273, Zipf 16384 722 / 707; H = 4096: T = 11000
+// 268 / 260.5, group-limited 32768 845 / 830; T = 4096, H = 7168 (28 units either way) 176.3 / 176.2.
+// Same arithmetic as combine_rows_kernel
 // (ascending j, one fma per placed branch, one rounding).  Units (token, column) are numbered token-major over
-// columns padded to a multiple of 64, so that a wave stays inside one token.
+// columns padded to a multiple of 64, so that a wave stays inside one token: without the padding (H = 4104: 115
+// against 95 us per combine, H = 640 79 / 68) the row numbers are no longer scalar and every unit waits for them.
 constexpr int kDeferBlock = 512;
-constexpr int kDeferUnits = 28;
+constexpr int kDeferRegs = 36;     // results per thread held in registers ...
+constexpr int kDeferLds = 20;      // ... and in LDS (all 160 KB)
+
+// Straight-line repetition while f returns true (the loop is longer than what the compiler unrolls fully when asked).
+// It is left at once where a wave has no unit left: to test and skip each of the remaining copies means as many jumps
+// into code that is not cached, about 0.2 us each.
+template <int... I, typename F>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F &&f) {
+  (void)(f(std::integral_constant<int, I>{}) && ...);
+}
+
+template <int DT, int KFIX>
+__device__ __forceinline__ u32x4 combine_unit(const u32x4 *__restrict__ Yexp, const float *__restrict__ wt,
+                                              const int32_t *__restrict__ rm, int t, int col, int k, int H16) {
+  constexpr int G = KFIX > 0 ? (KFIX < kGather ? KFIX : kGather) : kGather;
+  const int ts = uniform(t);
+  const int32_t *rows = rm + (size_t)ts * k;
+  const float *w = wt + (size_t)ts * k;
+  Acc<DT> acc;
+  acc.zero();
+  for (int j0 = 0; j0 < k; j0 += G) {
+    int row[G];
+    float wj[G];
+    u32x4 y[G];
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const bool in = (KFIX > 0 && KFIX % G == 0) || j0 + u < k;
+      row[u] = in ? uniform(rows[j0 + u]) : -1;
+      wj[u] = in ? __uint_as_float(uniform(__float_as_uint(w[j0 + u]))) : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < G; ++u)
+      y[u] = row[u] >= 0 ? load_stream(Yexp + (size_t)row[u] * (size_t)H16 + col) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int u = 0; u < G; ++u)
+      if (row[u] >= 0) acc.fma(wj[u], y[u]);
+  }
+  return acc.result();
+}
 
 template <int DT, int KFIX>
 __global__ __launch_bounds__(kDeferBlock) void combine_deferred_kernel(const u32x4 *__restrict__ Yexp,
@@ -136,60 +182,49 @@ __global__ __launch_bounds__(kDeferBlock) void combine_deferred_kernel(const u32
                                                                        const int32_t *__restrict__ row_map,
                                                                        u32x4 *__restrict__ Y, int k_arg, int H16,
                                                                        int cols_pad, int units, int dq, int dr,
-                                                                       int first) {
-  // this launch covers units [first, units)
-  constexpr int R = kDeferUnits;
+                                                                       int first, int in_lds) {
+  // this launch covers units [first, units), at most in_lds + kDeferRegs a thread
+  extern __shared__ u32x4 held[];
   const int k = KFIX > 0 ? KFIX : k_arg;
-  constexpr int G = KFIX > 0 ? (KFIX < kGather ? KFIX : kGather) : kGather;
   const int nthreads = (int)gridDim.x * kDeferBlock;
   const int g = (int)blockIdx.x * kDeferBlock + (int)threadIdx.x;
   const int32_t *rm = (const int32_t *)__builtin_assume_aligned(row_map, 16);
   const float *wt = (const float *)__builtin_assume_aligned(W, 16);
-  for (long long base = first; base < units; base += (long long)nthreads * R) {
-    const long long u0 = base + g;
-    const int t0 = (int)(u0 / cols_pad), col0 = (int)(u0 - (long long)t0 * cols_pad);
-    u32x4 res[R];
-    int t = t0, col = col0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (u0 + (long long)r * nthreads < units && col < H16) {     // the first test is uniform per wave
-        const int ts = uniform(t);
-        const int32_t *rows = rm + (size_t)ts * k;
-        const float *w = wt + (size_t)ts * k;
-        Acc<DT> acc;
-        acc.zero();
-        for (int j0 = 0; j0 < k; j0 += G) {
-          int row[G];
-          float wj[G];
-          u32x4 y[G];
-#pragma unroll
-          for (int u = 0; u < G; ++u) {
-            const bool in = (KFIX > 0 && KFIX % G == 0) || j0 + u < k;
-            row[u] = in ? uniform(rows[j0 + u]) : -1;
-            wj[u] = in ? __uint_as_float(uniform(__float_as_uint(w[j0 + u]))) : 0.0f;
-          }
-#pragma unroll
-          for (int u = 0; u < G; ++u)
-            y[u] = row[u] >= 0 ? load_stream(Yexp + (size_t)row[u] * (size_t)H16 + col) : u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-          for (int u = 0; u < G; ++u)
-            if (row[u] >= 0) acc.fma(wj[u], y[u]);
-        }
-        res[r] = acc.result();
-      }
-      col += dr;
-      t += dq;
-      if (col >= cols_pad) col -= cols_pad, ++t;
-    }
-    t = t0, col = col0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (u0 + (long long)r * nthreads < units && col < H16) store_stream(Y + (size_t)t * (size_t)H16 + col, res[r]);
-      col += dr;
-      t += dq;
-      if (col >= cols_pad) col -= cols_pad, ++t;
-    }
+  const long long u0 = (long long)first + g;
+  const long long wave0 = (long long)first + (int)blockIdx.x * kDeferBlock + uniform((int)threadIdx.x & ~(kWave - 1));
+  const int t0 = (int)(u0 / cols_pad), col0 = (int)(u0 - (long long)t0 * cols_pad);
+  u32x4 res[kDeferRegs];
+  long long u = wave0;                 // the wave's first unit: scalar
+  int t = t0, col = col0;
+  auto step = [&] {
+    u += nthreads;
+    col += dr;
+    t += dq;
+    if (col >= cols_pad) col -= cols_pad, ++t;
+  };
+#pragma unroll 1
+  for (int r = 0; r < in_lds && u < units; ++r) {
+    if (col < H16) held[r * kDeferBlock + threadIdx.x] = combine_unit<DT, KFIX>(Yexp, wt, rm, t, col, k, H16);
+    step();
   }
+  unrolled(std::make_integer_sequence<int, kDeferRegs>{}, [&](auto r) {
+    if (u >= units) return false;
+    if (col < H16) res[r] = combine_unit<DT, KFIX>(Yexp, wt, rm, t, col, k, H16);
+    step();
+    return true;
+  });
+  u = wave0, t = t0, col = col0;
+#pragma unroll 1
+  for (int r = 0; r < in_lds && u < units; ++r) {
+    if (col < H16) store_stream(Y + (size_t)t * (size_t)H16 + col, held[r * kDeferBlock + threadIdx.x]);
+    step();
+  }
+  unrolled(std::make_integer_sequence<int, kDeferRegs>{}, [&](auto r) {
+    if (u >= units) return false;
+    if (col < H16) store_stream(Y + (size_t)t * (size_t)H16 + col, res[r]);
+    step();
+    return true;
+  });
 }
 
 // Compute units of the current device (asked once per device; no allocation).  Calls may come from several host
@@ -211,18 +246,24 @@ static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out,
                                           void *y, int cols_pad, int units, hipStream_t s) {
   const int grid = device_cus();
   const int nthreads = grid * kDeferBlock;
-  // Two rounds per launch: the workgroups drift apart over the rounds and reads and writes mix again; a kernel
-  // boundary lines them up.  Measured inside layers, us per combine, one launch / one round per launch / two:
-  // wide (4.6 rounds) 412 / 386 / 391, Zipf T = 16384 (4 rounds) 329 / 325 / 323, balanced T = 16384 332.5 / 331 / 329,
-  // H = 4096: T = 8192 (1.1 rounds) 94.9 / 96.9 / 94.8, T = 16384 (2.3 rounds) 190.0 / 190.6 / 190.4.
-  constexpr int kRoundsPerLaunch = 2;
+  // As few launches as can hold all results, of equal length.
+  const long long per_thread = ((long long)units + nthreads - 1) / nthreads;
+  const long long launches = (per_thread + kDeferRegs + kDeferLds - 1) / (kDeferRegs + kDeferLds);
+  const int each = (int)((per_thread + launches - 1) / launches);
+  const int in_lds = each > kDeferRegs ? each - kDeferRegs : 0;
+  const size_t lds = (size_t)in_lds * kDeferBlock * sizeof(u32x4);
   auto go = [&](auto kernel) {
-    const long long per = (long long)nthreads * kDeferUnits * kRoundsPerLaunch;
+    if (lds > 64 * 1024) {
+      static const hipError_t raised = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                           kDeferLds * kDeferBlock * (int)sizeof(u32x4));
+      if (raised != hipSuccess) return raised;
+    }
+    const long long per = (long long)nthreads * each;
     for (long long first = 0; first < units; first += per) {
       const long long end = first + per < units ? first + per : units;
-      const hipError_t e = launch(kernel, dim3(grid), dim3(kDeferBlock), 0, s, (const u32x4 *)expert_out, W,
+      const hipError_t e = launch(kernel, dim3(grid), dim3(kDeferBlock), lds, s, (const u32x4 *)expert_out, W,
                                   (const int32_t *)p.row_map, (u32x4 *)y, d.k, d.H16, cols_pad, (int)end,
-                                  nthreads / cols_pad, nthreads % cols_pad, (int)first);
+                                  nthreads / cols_pad, nthreads % cols_pad, (int)first, in_lds);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
