@@ -94,14 +94,18 @@ __device__ __forceinline__ size_t row_offset(int row, int H16) {
 // 383, 13000 760 / 699 / 602, Zipf 16384 933 / 812 / 725; H = 8192, T = 12000 768 / 656 / 609; H = 4096: T = 24000 633 / 683 /
 // 605, 11000 294 (list) / 268; H = 3072, k = 10, T = 32768 1087 / 908 / 799; H = 4096, k = 3, T = 16000 263 / 212 / 188; X
 // fully cached: H = 7168: T = 8192 356 / 357 / 371, 16384 709 / 718 / 741; H = 4096, T = 20000 505 / 466 / 479.
-template <int Q, bool LIST, bool ROTATE, bool ALIGNED, bool WARM>
+// ALONE: one unit per workgroup of 128 threads, its entry in scalar registers.  Slices of 97 to 112 vectors nearly fill two
+// waves that way, and batches of up to 36 MiB of X then gain from waves that start copying earlier: us per dispatch, packed /
+// alone: H = 7168: T = 1400 25.4 / 23.4, 2000 38.3 / 35.2, but 2800 52.4 / 55.0; H = 6656, T = 1400 25.4 / 22.7; shorter and
+// longer slices do not (H = 6144, T = 1400 21.3 / 22.4; H = 8192 27.4 / 27.8; H = 4608 17.4 / 22.1).
+template <int Q, bool LIST, bool ROTATE, bool ALIGNED, bool WARM, bool ALONE = false>
 __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__restrict__ X,
                                                              const int32_t *__restrict__ entries,
                                                              u32x4 *__restrict__ window, int k, int H16, int misalign,
                                                              int N, int lanes, unsigned magic, int U, int T,
                                                              int warm_blocks, int stretch) {
   typedef int i32x2 __attribute__((ext_vector_type(2)));
-  const int unit = (int)__umulhi(threadIdx.x, magic);          // threadIdx.x / lanes
+  const int unit = ALONE ? 0 : (int)__umulhi(threadIdx.x, magic);          // threadIdx.x / lanes
   const int lane = (int)threadIdx.x - (int)__umul24(unit, lanes);
   int block = (int)blockIdx.x, stretch_start = 0;
   if (WARM) {
@@ -142,6 +146,7 @@ __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__rest
         t[q] = p / k, row[q] = entries[p];
       }
     }
+    if (ALONE) t[q] = uniform(t[q]), row[q] = uniform(row[q]);
   }
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
@@ -479,7 +484,7 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
   const bool aligned = misalign == 0 && d.H16 % kLine == 0;
   const int lines = (d.H16 + (aligned ? 0 : kLine - 1) + kLine - 1) / kLine;      // lines a row touches at most
   const bool rotate = !aligned || lines % kSlices != 0;
-  const int lanes = std::min((lines + kSlices - 1) / kSlices * kLine, 512);
+  int lanes = std::min((lines + kSlices - 1) / kSlices * kLine, 512);
   // units per workgroup: about 256 threads, a whole number of waves where that is near
   int U = std::max(1, 256 / lanes);
   for (int u = U; u >= 1 && U * lanes % kWave != 0; --u)
@@ -488,6 +493,8 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
     if (u * lanes % kWave == 0) U = u;
   const unsigned magic = (unsigned)(((1ull << 32) + lanes - 1) / lanes);
   const int Q = rotate && lanes <= 40 ? 2 : 1;
+  const bool alone = list && aligned && lanes > 96 && lanes <= 112 && (int64_t)d.T * d.H16 * 16 <= ((int64_t)36 << 20);
+  if (alone) U = 1, lanes = 128;
   const int per = U * Q;
   dim3 grid((unsigned)((d.N + per - 1) / per * kSlices));
   const bool warm = list && order_streams_x(d);
@@ -503,6 +510,8 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
                   (const int32_t *)(list ? p.order : p.row_map), (u32x4 *)window, d.k, d.H16, misalign, d.N, lanes, magic,
                   U, d.T, warm_blocks, stretch);
   };
+  if (alone) return rotate ? go(dispatch_units_kernel<1, true, true, true, false, true>)
+                           : go(dispatch_units_kernel<1, true, false, true, false, true>);
 #define GO(LIST_, WARM_)                                                                                     \
   if (list == LIST_ && warm == WARM_) {                                                                      \
     if (!aligned) return Q == 2 ? go(dispatch_units_kernel<2, LIST_, true, false, WARM_>)                    \

@@ -21,7 +21,7 @@ def moe():
     return m
 
 
-@pytest.mark.parametrize("H16", [1, 7, 8, 9, 63, 64, 65, 72, 96, 97, 128, 136, 257, 320, 321, 513, 576, 960, 1000, 4096, 4104, 5001])
+@pytest.mark.parametrize("H16", [1, 7, 8, 9, 63, 64, 65, 72, 96, 97, 128, 136, 257, 320, 321, 513, 576, 832, 896, 960, 1000, 4096, 4104, 5001])
 @pytest.mark.parametrize("shift", [0, 1, 7])                   # 16-byte vectors from a line to the window's first row
 def test_dispatch_writes_every_vector_once(moe, H16, shift):
     from paper_2605_06055_amd.layer import to_device, to_host
