@@ -241,6 +241,15 @@ static int device_cus() {
   return n;
 }
 
+// Raises this kernel's limit on dynamic LDS (64 KB by default), once per process.
+template <int DT, int KFIX>
+static hipError_t raise_lds_limit() {
+  static const hipError_t raised =
+      hipFuncSetAttribute((const void *)combine_deferred_kernel<DT, KFIX>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                          kDeferLds * kDeferBlock * (int)sizeof(u32x4));
+  return raised;
+}
+
 template <int DT>
 static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out, const float *W, const PlanView &p,
                                           void *y, int cols_pad, int units, hipStream_t s) {
@@ -252,10 +261,9 @@ static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out,
   const int each = (int)((per_thread + launches - 1) / launches);
   const int in_lds = each > kDeferRegs ? each - kDeferRegs : 0;
   const size_t lds = (size_t)in_lds * kDeferBlock * sizeof(u32x4);
-  auto go = [&](auto kernel) {
+  auto go = [&](auto kernel, hipError_t (*raise)()) {
     if (lds > 64 * 1024) {
-      static const hipError_t raised = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                           kDeferLds * kDeferBlock * (int)sizeof(u32x4));
+      const hipError_t raised = raise();
       if (raised != hipSuccess) return raised;
     }
     const long long per = (long long)nthreads * each;
@@ -269,8 +277,8 @@ static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out,
     return hipSuccess;
   };
   switch (d.k) {
-    case 8: return go(combine_deferred_kernel<DT, 8>);
-    case 6: return go(combine_deferred_kernel<DT, 6>);
+    case 8: return go(combine_deferred_kernel<DT, 8>, raise_lds_limit<DT, 8>);
+    case 6: return go(combine_deferred_kernel<DT, 6>, raise_lds_limit<DT, 6>);
     default: return hipErrorInvalidValue;      // other routing degrees keep combine_rows_kernel (see launch_combine)
   }
 }
