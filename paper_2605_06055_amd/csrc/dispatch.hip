@@ -95,9 +95,10 @@ __device__ __forceinline__ size_t row_offset(int row, int H16) {
 // 605, 11000 294 (list) / 268; H = 3072, k = 10, T = 32768 1087 / 908 / 799; H = 4096, k = 3, T = 16000 263 / 212 / 188; X
 // fully cached: H = 7168: T = 8192 356 / 357 / 371, 16384 709 / 718 / 741; H = 4096, T = 20000 505 / 466 / 479.
 // ALONE: one unit per workgroup of 128 threads, its entry in scalar registers.  Slices of 97 to 112 vectors nearly fill two
-// waves that way, and batches of up to 36 MiB of X then gain from waves that start copying earlier: us per dispatch, packed /
-// alone: H = 7168: T = 1400 25.4 / 23.4, 2000 38.3 / 35.2, but 2800 52.4 / 55.0; H = 6656, T = 1400 25.4 / 22.7; shorter and
-// longer slices do not (H = 6144, T = 1400 21.3 / 22.4; H = 8192 27.4 / 27.8; H = 4608 17.4 / 22.1).
+// waves that way, and without bulk reads they then do better: us per dispatch, packed / alone: H = 7168: T = 1400 25.4 /
+// 23.4, 2000 38.3 / 35.2, 2800 52.4 / 55.0, 4096 79.4 / 80.9, where the layer with X not cached takes 210 / 197; H = 6656,
+// T = 1400 25.4 / 22.7, 3000 54.3 / 51.5; shorter and longer slices do not (H = 6144, T = 1400 21.3 / 22.4; H = 8192 27.4 /
+// 27.8; H = 4608 17.4 / 22.1).
 template <int Q, bool LIST, bool ROTATE, bool ALIGNED, bool WARM, bool ALONE = false>
 __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__restrict__ X,
                                                              const int32_t *__restrict__ entries,
@@ -493,11 +494,11 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
     if (u * lanes % kWave == 0) U = u;
   const unsigned magic = (unsigned)(((1ull << 32) + lanes - 1) / lanes);
   const int Q = rotate && lanes <= 40 ? 2 : 1;
-  const bool alone = list && aligned && lanes > 96 && lanes <= 112 && (int64_t)d.T * d.H16 * 16 <= ((int64_t)36 << 20);
+  const bool warm = list && order_streams_x(d);
+  const bool alone = list && aligned && !warm && lanes > 96 && lanes <= 112;
   if (alone) U = 1, lanes = 128;
   const int per = U * Q;
   dim3 grid((unsigned)((d.N + per - 1) / per * kSlices));
-  const bool warm = list && order_streams_x(d);
   int stretch = 0, warm_blocks = 0;
   if (warm) {
     stretch = d.order_tiles * plan_tile_size(d.N);
