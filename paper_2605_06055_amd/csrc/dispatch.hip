@@ -529,11 +529,14 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
 }
 
 hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void *window, hipStream_t s) {
-  if (d.order_tiles > 0 && p.order) return launch_dispatch_units(d, x, p, window, true, s);
+  // dispatch_units_kernel cuts its slices with 24-bit products (a 32-bit one per lane costs 0.5 % of a layer: T = 3001, H =
+  // 4104 74.3 / 74.0 us).  Rows of 2^24 lines (2 GiB) or more are left to the token-order slices, which cut in scalar registers.
+  const bool cuts_in_24_bits = (d.H16 + 2 * kLine - 2) / kLine < 1 << 24;
+  if (d.order_tiles > 0 && p.order && cuts_in_24_bits) return launch_dispatch_units(d, x, p, window, true, s);
   // Rows that do not start at a cache line, and narrow rows while X is no larger than the Infinity Cache (us per
   // dispatch, units / token-order slices: H = 512, T = 32768 47 / 53; H = 640, T = 10000 20.6 / 21.1).
   const bool x_cold = (int64_t)d.T * d.H16 * 16 > ((int64_t)256 << 20);
-  if (d.H16 % kLine != 0 || ((uintptr_t)window >> 4) % kLine != 0 || (d.H16 < 96 && !x_cold))
+  if (cuts_in_24_bits && (d.H16 % kLine != 0 || ((uintptr_t)window >> 4) % kLine != 0 || (d.H16 < 96 && !x_cold)))
     return launch_dispatch_units(d, x, p, window, false, s);
   // A workgroup should move a few KB, so that the grid stays within what the dispatcher sustains (about 3000
   // workgroups per microsecond), with its lanes busy.
@@ -546,7 +549,7 @@ hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void
   // Measured in a plan -> dispatch -> combine sequence, k = 8, us per dispatch, this rule / one unit only:
   //   H = 512, T = 131072: 212 / 544;  H = 1024, T = 131072: 466 / 828;  H = 2048, T = 65536: 436 / 459;
   //   H = 2048, k = 6, T = 8192: 37 / 58 (launches alone).
-  const int lines = d.H16 / kLine;
+  const int lines = (d.H16 + kLine - 1) / kLine;
   const int slice = (lines + kSlices - 1) / kSlices * kLine;
   const int rotate = lines % kSlices != 0 ? kSlices - 1 : 0;
   const int slice_bytes = slice * 16;

@@ -77,3 +77,23 @@ def test_dispatch_with_bulk_reads_of_x(moe, T, H, k, stride):
     at[rows[rows >= 0]] = (torch.arange(T * k, device="cuda") // k)[rows >= 0]
     assert torch.equal(bits[at >= 0], x[at[at >= 0]])
     assert bool((bits[at < 0] == 0x7B7B).all())
+
+
+@pytest.mark.parametrize("H16", [1 << 27, (1 << 27) + 1])      # 2^24 lines, and one vector more (rows that start inside a line)
+@pytest.mark.parametrize("with_order", [True, False])
+def test_rows_of_2_gib(moe, H16, with_order):
+    """Slice cuts of rows of 2^24 lines and more: the product of slice and lines needs more than 24 bits."""
+    from paper_2605_06055_amd.layer import to_device, to_host
+    H, k = H16 * 8, 3
+    print(f"[2 GiB rows] H16={H16} list={with_order}", flush=True)
+    shape = moe.MoeShape(T=1, H=H, k=k, E=k, R=1, dtype=moe.MOE_DTYPE_BF16, schedule=moe.MOE_SCHEDULE_PREFILL)
+    plan = moe.MoePlan(shape, with_order=with_order)
+    kd = to_device(np.array([[2, 0, 1]], dtype=np.int32))
+    x = torch.arange(H // 2, dtype=torch.int32, device="cuda")                      # every vector is different
+    window = torch.full((k, H // 2), -7, dtype=torch.int32, device="cuda")
+    moe.moe_plan(shape, kd, plan)
+    moe.moe_dispatch(shape, x, kd, plan, window)
+    torch.cuda.synchronize()
+    assert to_host(plan.row_map)[:k].tolist() == [2, 0, 1]
+    for row in range(k):
+        assert torch.equal(window[row], x), row
