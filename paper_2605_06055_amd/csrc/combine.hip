@@ -307,15 +307,6 @@ static int device_cus() {
   return n;
 }
 
-// Raises this kernel's limit on dynamic LDS (64 KB by default), once per process.
-template <int DT, int KFIX>
-static hipError_t raise_lds_limit() {
-  static const hipError_t raised =
-      hipFuncSetAttribute((const void *)combine_deferred_kernel<DT, KFIX>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          kDeferLds * kDeferBlock * (int)sizeof(u32x4));
-  return raised;
-}
-
 template <int DT>
 static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out, const float *W, const PlanView &p,
                                           void *y, int cols_pad, int units, hipStream_t s) {
@@ -336,10 +327,10 @@ static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out,
   const int each = (int)((per_thread + launches - 1) / launches);
   const int in_lds = each > kDeferRegs ? each - kDeferRegs : 0;
   const size_t lds = (size_t)in_lds * kDeferBlock * sizeof(u32x4);
-  auto go = [&](auto kernel, hipError_t (*raise)()) {
+  auto go = [&](auto kernel, RaisedOn &raised) {
     if (lds > 64 * 1024) {
-      const hipError_t raised = raise();
-      if (raised != hipSuccess) return raised;
+      const hipError_t e = raise_lds_limit((const void *)kernel, kDeferLds * kDeferBlock * (int)sizeof(u32x4), raised);
+      if (e != hipSuccess) return e;
     }
     const long long per = (long long)nthreads * each;
     for (long long first = 0; first < units; first += per) {
@@ -351,9 +342,10 @@ static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out,
     }
     return hipSuccess;
   };
+  static RaisedOn raised8, raised6;
   switch (d.k) {
-    case 8: return go(combine_deferred_kernel<DT, 8>, raise_lds_limit<DT, 8>);
-    case 6: return go(combine_deferred_kernel<DT, 6>, raise_lds_limit<DT, 6>);
+    case 8: return go(combine_deferred_kernel<DT, 8>, raised8);
+    case 6: return go(combine_deferred_kernel<DT, 6>, raised6);
     default: return hipErrorInvalidValue;      // other routing degrees keep combine_rows_kernel (see launch_combine)
   }
 }

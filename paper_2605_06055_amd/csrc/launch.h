@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <tuple>
 #include <utility>
 
@@ -80,6 +81,24 @@ template <typename... P, typename... A>
 inline hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t s, A &&...a) {
   static_assert(sizeof...(P) == sizeof...(A), "kernel argument count");
   return launch_impl(kernel, grid, block, lds, s, std::index_sequence_for<P...>{}, std::forward<A>(a)...);
+}
+
+// Raises a kernel's limit on dynamic LDS (64 KB by default) on the current device.  The limit belongs to the (kernel, device)
+// pair: `raised` is the kernel's own and remembers the devices where it has been done.  A failure is reported and tried
+// again by the next call.
+struct RaisedOn {
+  static constexpr int kDevices = 64;
+  std::atomic<bool> device[kDevices];
+};
+inline hipError_t raise_lds_limit(const void *kernel, int bytes, RaisedOn &raised) {
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const bool known = dev >= 0 && dev < RaisedOn::kDevices;
+  if (known && raised.device[dev].load(std::memory_order_relaxed)) return hipSuccess;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess && known) raised.device[dev].store(true, std::memory_order_relaxed);
+  return e;
 }
 
 }  // namespace moe_rbf

@@ -346,15 +346,11 @@ template <bool FUSED>
 static hipError_t launch_plan_rank(const Dims &d, const int32_t *K, const PlanView &p, const int32_t *tile_hist,
                                    int tiles, int tile, const WarmRange &warm, hipStream_t s) {
   const size_t lds = (size_t)(5 * d.E + 2 + kPlanWaves * d.E + 2 + 3 * d.E + 2) * sizeof(int);
-  if (lds > 64 * 1024) {   // beyond the default dynamic LDS limit (E > ~800): raise it once per process
-    static const hipError_t raised = [] {
-      hipError_t e = hipFuncSetAttribute((const void *)plan_rank_kernel<FUSED, false>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-      return e != hipSuccess ? e
-                             : hipFuncSetAttribute((const void *)plan_rank_kernel<FUSED, true>,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-    }();
-    if (raised != hipSuccess) return raised;
+  if (lds > 64 * 1024) {   // beyond the default dynamic LDS limit (E > ~800)
+    static RaisedOn raised_warm, raised_plain;
+    const hipError_t e = warm.ptr ? raise_lds_limit((const void *)plan_rank_kernel<FUSED, true>, 128 * 1024, raised_warm)
+                                  : raise_lds_limit((const void *)plan_rank_kernel<FUSED, false>, 128 * 1024, raised_plain);
+    if (e != hipSuccess) return e;
   }
   if (!warm.ptr)
     return launch(plan_rank_kernel<FUSED, false>, dim3(tiles + 1), dim3(kPlanBlock), lds, s, K, tile_hist, tiles, tile,
