@@ -108,7 +108,7 @@ __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__rest
   typedef int i32x2 __attribute__((ext_vector_type(2)));
   const int unit = ALONE ? 0 : (int)__umulhi(threadIdx.x, magic);          // threadIdx.x / lanes
   const int lane = (int)threadIdx.x - (int)__umul24(unit, lanes);
-  int block = (int)blockIdx.x, stretch_start = 0;
+  int block = (int)blockIdx.x, stretch_start = stretch;        // without WARM: the first branch of the launch
   if (WARM) {
     stretch_start = (int)blockIdx.y * stretch;
     if (block < warm_blocks) {                                 // warm_blocks is a multiple of 8: XCD = block % 8
@@ -469,14 +469,9 @@ __global__ __launch_bounds__(BLOCK) void dispatch_quant_rows_kernel(const u32x4 
   }
 }
 
-template <int J, int U>
-static hipError_t launch_dispatch_ju(const Dims &d, const void *x, const PlanView &p, void *window, int rotate,
-                                     hipStream_t s) {
-  const unsigned units = (unsigned)(d.N / J);
-  const dim3 grid((units + U - 1) / U * (unsigned)kSlices);
-  return launch(dispatch_slices_kernel<128, J, U>, grid, dim3(128), 0, s, (const u32x4 *)x,
-                (const int32_t *)p.row_map, (u32x4 *)window, d.k, d.H16, rotate, d.N);
-}
+// dispatch_units_kernel cuts its slices with 24-bit products (a 32-bit one per lane costs 0.5 % of a layer: T = 3001, H = 4104
+// 74.3 / 74.0 us).  Rows of 2^24 lines (2 GiB) or more are left to the token-order slices, which cut in scalar registers.
+static bool cuts_in_24_bits(const Dims &d) { return (d.H16 + 2 * kLine - 2) / kLine < 1 << 24; }
 
 static hipError_t launch_dispatch_units(const Dims &d, const void *x, const PlanView &p, void *window, bool list,
                                         hipStream_t s) {
@@ -494,22 +489,35 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
     if (u * lanes % kWave == 0) U = u;
   const unsigned magic = (unsigned)(((1ull << 32) + lanes - 1) / lanes);
   const int Q = rotate && lanes <= 40 ? 2 : 1;
-  const bool warm = list && order_streams_x(d);
-  const bool alone = list && aligned && !warm && lanes > 96 && lanes <= 112;
-  if (alone) U = 1, lanes = 128;
-  const int per = U * Q;
-  dim3 grid((unsigned)((d.N + per - 1) / per * kSlices));
+  bool warm = list && order_streams_x(d);
   int stretch = 0, warm_blocks = 0;
+  int64_t warm_grid = 0;
   if (warm) {
     stretch = d.order_tiles * plan_tile_size(d.N);
     const int tokens = stretch / d.k + 2;                      // a stretch may begin and end inside a token
     warm_blocks = (tokens + U * kWarmTokens - 1) / (U * kWarmTokens) * kSlices;
-    grid = dim3((unsigned)(warm_blocks + (stretch + per - 1) / per * kSlices), (unsigned)((d.N + stretch - 1) / stretch));
+    warm_grid = warm_blocks + ((int64_t)stretch + U * Q - 1) / (U * Q) * kSlices;
+    warm = (uint64_t)warm_grid * (uint64_t)(U * lanes) <= kMostThreads;        // (not so from a few thousand branches a token on)
   }
+  const bool alone = list && aligned && !warm && lanes > 96 && lanes <= 112;
+  if (alone) U = 1, lanes = 128;
+  const int per = U * Q;
   auto go = [&](auto kernel) {
-    return launch(kernel, grid, dim3((unsigned)(U * lanes)), 0, s, (const u32x4 *)x,
-                  (const int32_t *)(list ? p.order : p.row_map), (u32x4 *)window, d.k, d.H16, misalign, d.N, lanes, magic,
-                  U, d.T, warm_blocks, stretch);
+    auto part = [&](dim3 grid, int start) {
+      return launch(kernel, grid, dim3((unsigned)(U * lanes)), 0, s, (const u32x4 *)x,
+                    (const int32_t *)(list ? p.order : p.row_map), (u32x4 *)window, d.k, d.H16, misalign, d.N, lanes, magic,
+                    U, d.T, warm_blocks, start);
+    };
+    if (warm) return part(dim3((unsigned)warm_grid, (unsigned)((d.N + stretch - 1) / stretch)), stretch);
+    // one launch, or as many as the limit on its threads asks for (windows of more than about 2 GiB at 16 bytes a row, 57 GiB
+    // at 14 KB): `most` branches each
+    const int64_t most = (int64_t)(kMostThreads / (unsigned)(U * lanes * kSlices)) * per;
+    for (int64_t first = 0; first < d.N; first += most) {
+      const int64_t groups = (std::min(most, d.N - first) + per - 1) / per;
+      const hipError_t e = part(dim3((unsigned)(groups * kSlices)), (int)first);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   };
   if (alone) return rotate ? go(dispatch_units_kernel<1, true, true, true, false, true>)
                            : go(dispatch_units_kernel<1, true, false, true, false, true>);
@@ -528,15 +536,23 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
   return hipErrorInvalidValue;
 }
 
+template <int J, int U>
+static hipError_t launch_dispatch_ju(const Dims &d, const void *x, const PlanView &p, void *window, int rotate,
+                                     hipStream_t s) {
+  const unsigned units = (unsigned)(d.N / J);
+  const dim3 grid((units + U - 1) / U * (unsigned)kSlices);
+  if ((uint64_t)grid.x * 128 > kMostThreads && cuts_in_24_bits(d))
+    return launch_dispatch_units(d, x, p, window, false, s);
+  return launch(dispatch_slices_kernel<128, J, U>, grid, dim3(128), 0, s, (const u32x4 *)x,
+                (const int32_t *)p.row_map, (u32x4 *)window, d.k, d.H16, rotate, d.N);
+}
+
 hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void *window, hipStream_t s) {
-  // dispatch_units_kernel cuts its slices with 24-bit products (a 32-bit one per lane costs 0.5 % of a layer: T = 3001, H =
-  // 4104 74.3 / 74.0 us).  Rows of 2^24 lines (2 GiB) or more are left to the token-order slices, which cut in scalar registers.
-  const bool cuts_in_24_bits = (d.H16 + 2 * kLine - 2) / kLine < 1 << 24;
-  if (d.order_tiles > 0 && p.order && cuts_in_24_bits) return launch_dispatch_units(d, x, p, window, true, s);
+  if (d.order_tiles > 0 && p.order && cuts_in_24_bits(d)) return launch_dispatch_units(d, x, p, window, true, s);
   // Rows that do not start at a cache line, and narrow rows while X is no larger than the Infinity Cache (us per
   // dispatch, units / token-order slices: H = 512, T = 32768 47 / 53; H = 640, T = 10000 20.6 / 21.1).
   const bool x_cold = (int64_t)d.T * d.H16 * 16 > ((int64_t)256 << 20);
-  if (cuts_in_24_bits && (d.H16 % kLine != 0 || ((uintptr_t)window >> 4) % kLine != 0 || (d.H16 < 96 && !x_cold)))
+  if (cuts_in_24_bits(d) && (d.H16 % kLine != 0 || ((uintptr_t)window >> 4) % kLine != 0 || (d.H16 < 96 && !x_cold)))
     return launch_dispatch_units(d, x, p, window, false, s);
   // A workgroup should move a few KB, so that the grid stays within what the dispatcher sustains (about 3000
   // workgroups per microsecond), with its lanes busy.

@@ -83,6 +83,9 @@ inline hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds
   return launch_impl(kernel, grid, block, lds, s, std::index_sequence_for<P...>{}, std::forward<A>(a)...);
 }
 
+// A launch has fewer than 2^32 threads along x (the runtime refuses more).
+constexpr uint64_t kMostThreads = 0xffffffffu;
+
 // Raises a kernel's limit on dynamic LDS (64 KB by default) on the current device.  The limit belongs to the (kernel, device)
 // pair: `raised` is the kernel's own and remembers the devices where it has been done.  A failure is reported and tried
 // again by the next call.

@@ -97,3 +97,24 @@ def test_rows_of_2_gib(moe, H16, with_order):
     assert to_host(plan.row_map)[:k].tolist() == [2, 0, 1]
     for row in range(k):
         assert torch.equal(window[row], x), row
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+def test_more_threads_than_one_launch_may_have(moe, shift):
+    """Rows of one vector, 2^27 + 8 branches: 2^32 threads and more, so the copy is split over two launches."""
+    from paper_2605_06055_amd.layer import to_device
+    T, k, H = (1 << 24) + 1, 8, 8
+    N = T * k
+    print(f"[split] N={N} shift={shift}", flush=True)
+    shape = moe.MoeShape(T=T, H=H, k=k, E=8, R=1, dtype=moe.MOE_DTYPE_BF16, schedule=moe.MOE_SCHEDULE_PREFILL)
+    plan = moe.MoePlan(shape)
+    rows = torch.arange(N, dtype=torch.int64, device="cuda") * 1000003 % N         # 1000003 does not divide N: a permutation
+    plan.row_map.copy_(rows)
+    x = torch.arange(T * 2, dtype=torch.int64, device="cuda").view(T, 2)
+    buf = torch.full(((N + 2) * 2,), -7, dtype=torch.int64, device="cuda")
+    window = buf[shift * 2:shift * 2 + N * 2].view(N, 2)
+    moe.moe_dispatch(shape, x, None, plan, window)
+    torch.cuda.synchronize()
+    for j in range(k):
+        assert torch.equal(window[rows.view(T, k)[:, j]], x), j
+    assert bool((buf[:shift * 2] == -7).all()) and bool((buf[shift * 2 + N * 2:] == -7).all())

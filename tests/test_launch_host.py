@@ -97,3 +97,19 @@ for device in (3, 0, 70):
         assert (word("fake_raises").value == raises) == (fails == 0)
 assert most_lds() > 64 * 1024
 """)
+
+
+def test_dispatch_launches_stay_below_the_thread_limit(run):
+    """Batches whose prefill dispatch has 2^32 threads or more as one launch are split; none is refused."""
+    run("""
+for H16, k, T in ((1, 8, 1 << 24), (1, 7, 38347922), (9, 8, 1 << 24), (64, 8, 1 << 23), (64, 5, 1 << 23), (80, 2, 1 << 25),
+                  (120, 8, 1 << 24), (128, 3, 1 << 23), (456, 512, 36000), (512, 8, 1 << 22), (513, 8, 1 << 21),
+                  (897, 8, 600000), (896, 1, 9000000), (896, 4000, 8000), (4095, 8, 200000), (4096, 4000, 2000),
+                  (4096, 1, 2100000)):
+    for order in (None, 1 << 45):
+        PLAN.dispatch_order = order
+        for shift in (0, 16):                                  # windows that start at a line and inside one
+            s = shape(T=T, H=H16 * 8, k=k)
+            assert refused(moe.moe_dispatch, s, X, None, PLAN, WINDOW + shift, 0) == 0, (H16, k, T, order, shift)
+assert word("fake_launches").value > 17 * 4                   # some were split
+""")
