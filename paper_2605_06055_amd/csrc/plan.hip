@@ -321,9 +321,13 @@ bool plan_uses_workspace(int64_t N) { return N > (int64_t)MOE_PLAN_FUSED_MAX_TIL
 // re-read X too little: us per layer, X not cached, list with bulk reads / the rule above: k = 2: H = 7168, T = 14000 225.5 /
 // 214.6; H = 4096, T = 28000 246 / 266; k = 1: H = 4096, T = 20000 128 / 122; around the line: H = 7168: T = 5000 (72 MB)
 // 217 / 209, 6200 (89 MB) 280 / 294; H = 2560, T = 14000 (72 MB) 219 / 216; H = 4096, T = 11000 (90 MB) 267 / 295.
+// A single-launch plan has one stretch, the whole batch: that much X, read in bulk first, has left the L2s before it is copied.  Such
+// batches (rows of 20 KB and more, degrees of 3 to 8) keep the rule above; us per layer, list with bulk reads / now, fp32: H = 8192:
+// k = 3, T = 3200 175.1 / 159.2; k = 4, T = 3000 203.7 / 198.9; H = 12288, k = 6, T = 1800 241 / 232; H = 16384: k = 5, T = 2400
+// 396.8 / 393.1; k = 6, T = 2000 367.7 / 381.8 (a loss); k = 8, T = 1500 349.7 / 339.5.
 bool order_streams_x(const Dims &d) {
   const int64_t row_bytes = (int64_t)d.H16 * 16;
-  return (int64_t)d.T * row_bytes > ((int64_t)80 << 20) && (d.k >= 3 || (d.k == 2 && row_bytes < 12288));
+  return plan_uses_workspace(d.N) && (int64_t)d.T * row_bytes > ((int64_t)80 << 20) && (d.k >= 3 || (d.k == 2 && row_bytes < 12288));
 }
 
 int plan_order_tiles(const Dims &d) {

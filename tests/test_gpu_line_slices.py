@@ -118,3 +118,18 @@ def test_more_threads_than_one_launch_may_have(moe, shift):
     for j in range(k):
         assert torch.equal(window[rows.view(T, k)[:, j]], x), j
     assert bool((buf[:shift * 2] == -7).all()) and bool((buf[shift * 2 + N * 2:] == -7).all())
+
+
+@pytest.mark.parametrize("T,H,k,dtype,used", [(3200, 8192, 3, "f32", False),   # 100 MiB of X in the one stretch of a single-launch plan
+                                              (4800, 8192, 3, "f32", True)])   # 150 MiB in stretches: read in bulk
+def test_which_plans_carry_the_order_list(moe, T, H, k, dtype, used):
+    from paper_2605_06055_amd.layer import to_device
+    rng = np.random.default_rng(T)
+    shape = moe.MoeShape(T=T, H=H, k=k, E=64, R=8, dtype=moe.MOE_DTYPE_F32 if dtype == "f32" else moe.MOE_DTYPE_BF16,
+                         schedule=moe.MOE_SCHEDULE_PREFILL)
+    plan = moe.MoePlan(shape)
+    plan.dispatch_order.fill_(-77)
+    moe.moe_plan(shape, to_device(wl.random_routing(rng, T, k, 64)), plan)
+    torch.cuda.synchronize()
+    written = plan.dispatch_order[:2 * T * k] != -77
+    assert bool(written.all()) if used else not bool(written.any())
