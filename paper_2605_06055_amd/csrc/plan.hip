@@ -312,8 +312,17 @@ bool plan_uses_workspace(int64_t N) { return N > (int64_t)MOE_PLAN_FUSED_MAX_TIL
 // and for larger X with bulk reads (order_streams_x).
 // Rows of 2 to 4 KB, us per layer with the list / in token order: H = 2048: T = 8192 105.4 / 108.0, 16384 197.0 / 204.3,
 // 32768 388.6 / 407.6; H = 1024: T = 16384 110.0 / 113.4, 65536 405.7 / 426.0.  With slices cut at cache lines and units
-// packed side by side the same holds for every width from 1.5 KB on (sum of the kernels' us): H = 2560, T = 11468
+// packed side by side the same holds for most widths from 1.5 KB on (sum of the kernels' us): H = 2560, T = 11468
 // 190.8 / 202.3; H = 3072, T = 9557 183.9 / 194.5; H = 3584, T = 8192 187.1 / 202.2; H = 768, T = 32768 173.6 / 181.5.
+// It depends on the degree there, since the plan pays for the list per branch, and in token order one unit stores all 2 or 4
+// branches of a token (odd degrees share no loads, larger even ones in part).  us per layer, list / token order:
+//   rows under 2 KB: from a degree of 8 on.  H = 896: T = 11702: k = 2 33.4 / 32.6, k = 6 61.1 / 60.8, k = 8 74.3 / 77.2,
+//     k = 10 90.3 / 94.9; T = 4681: k = 4 28.0 / 26.5, k = 8 38.0 / 37.7; T = 35108: k = 6 158.7 / 161.6 (a loss), k = 8 193.7 / 200.5;
+//   rows of 4 to 8 KB, degrees of 2 and 4: not where a slice has more than 48 vectors (the token-order unit's wave is then
+//     nearly full) and not for degree 4 without bulk reads.  H = 3584: T = 8777: k = 2 72.2 / 70.2, k = 3 91.5 / 103.1, k = 5 131.7 /
+//     156.9, k = 6 150.9 / 152.1, k = 8 185.8 / 199.6; T = 2925: k = 4 44.6 / 43.7; with bulk reads T = 13897: k = 2 124.7 / 123.4,
+//     k = 4 195.3 / 190.0; H = 3200: T = 9830: k = 2 74.5 / 71.9, k = 4 113.7 / 108.3, T = 24576: k = 4 316.9 / 294.3;
+//     H = 2560: T = 12288: k = 2 72.0 / 74.4, k = 4 111.5 / 108.2; T = 19456: k = 2 123.3 / 139.2, k = 4 198.4 / 208.9.
 // Narrower rows pay more for the list in the plan than dispatch gains (H = 640, T = 10000 59.2 / 57.2), and so do
 // batches whose X is in the L2s anyway: H = 2048, T = 1400 26.9 / 26.5; H = 2560, T = 1024 23.5 / 23.1; but H = 3072,
 // T = 1400 (8.6 MB) 34.5 / 35.7.
@@ -335,6 +344,8 @@ int plan_order_tiles(const Dims &d) {
   constexpr int64_t mib = 1 << 20;
   if (d.H16 < 96 || x <= 5 * mib) return 0;
   const bool bulk = order_streams_x(d);
+  if (d.H16 < 128 && d.k < 8 && !bulk) return 0;
+  if (d.H16 > 256 && d.H16 < 512 && (d.k == 2 || d.k == 4) && (d.H16 > 384 || (d.k == 4 && !bulk))) return 0;
   if (!bulk && (row_bytes < 12288 ? window > 1100 * mib : (window > 770 * mib || x > 96 * mib))) return 0;
   const int tile = plan_tile_size(d.N), tiles = plan_tile_count(d.N);
   if (!plan_uses_workspace(d.N)) return tiles;                      // single-launch plan: the batch is one stretch

@@ -121,7 +121,12 @@ def test_more_threads_than_one_launch_may_have(moe, shift):
 
 
 @pytest.mark.parametrize("T,H,k,dtype,used", [(3200, 8192, 3, "f32", False),   # 100 MiB of X in the one stretch of a single-launch plan
-                                              (4800, 8192, 3, "f32", True)])   # 150 MiB in stretches: read in bulk
+                                              (4800, 8192, 3, "f32", True),    # 150 MiB in stretches: read in bulk
+                                              (11702, 896, 6, "bf16", False), (11702, 896, 8, "bf16", True),
+                                              (12288, 2560, 4, "bf16", False), (12288, 2560, 2, "bf16", True),
+                                              (17408, 2560, 4, "bf16", True), (8777, 3200, 2, "bf16", False),
+                                              (8777, 3200, 4, "bf16", False), (8777, 3200, 3, "bf16", True),
+                                              (13897, 3584, 4, "bf16", False), (13897, 3584, 6, "bf16", True)])
 def test_which_plans_carry_the_order_list(moe, T, H, k, dtype, used):
     from paper_2605_06055_amd.layer import to_device
     rng = np.random.default_rng(T)
