@@ -1,5 +1,6 @@
-"""The streaming form of combine at the numbers of results per thread where they move: the last that fit in registers, the
-first held in LDS, the last of one launch, the first of two."""
+"""The streaming form of combine at the numbers of results per thread where they move: the last of the short form, the last
+that fit in registers, the first held in LDS, the last of one launch, the first of two; for rows that are a whole number of
+waves, rows padded to one, and rows over which a thread's column wraps."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -16,15 +17,17 @@ def moe():
     return m
 
 
-@pytest.mark.parametrize("per_thread", [36, 56])
+@pytest.mark.parametrize("per_thread", [28, 36, 56])
 @pytest.mark.parametrize("more", [0, 1])
-@pytest.mark.parametrize("k,dtype", [(6, "bf16"), (8, "f32")])
-def test_results_held_in_registers_and_lds(moe, per_thread, more, k, dtype):
+@pytest.mark.parametrize("k,dtype,H16", [(6, "bf16", 64), (8, "f32", 64), (6, "bf16", 513), (8, "f32", 514), (8, "bf16", 896),
+                                         (8, "bf16", 513)])
+def test_results_held_in_registers_and_lds(moe, per_thread, more, k, dtype, H16):
     threads = torch.cuda.get_device_properties(0).multi_processor_count * 512
     bf16 = dtype == "bf16"
-    H16 = 64
     H = H16 * (8 if bf16 else 4)
-    T = threads * per_thread // H16 + more
+    padded = (H16 + 63) // 64 * 64
+    T = threads * per_thread // padded + more                  # more: one unit a thread more, for some threads
+    assert -(-T * padded // threads) == per_thread + more
     print(f"[held] T={T} H={H} k={k} {dtype}", flush=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(T + k)

@@ -21,13 +21,15 @@ def moe():
     return m
 
 
-@pytest.mark.parametrize("H16", [1, 7, 8, 9, 63, 64, 65, 72, 96, 97, 128, 136, 257, 320, 321, 513, 576, 832, 896, 960, 1000, 4096, 4104, 5001])
+@pytest.mark.parametrize("H16", [1, 7, 8, 9, 63, 64, 65, 72, 96, 97, 128, 136, 257, 320, 321, 513, 576, 776, 832, 840, 896, 960, 1000, 4096,
+                                 4104, 5001])
 @pytest.mark.parametrize("shift", [0, 1, 7])                   # 16-byte vectors from a line to the window's first row
 def test_dispatch_writes_every_vector_once(moe, H16, shift):
     from paper_2605_06055_amd.layer import to_device, to_host
     rng = np.random.default_rng(H16 * 8 + shift)
     H, k, E, R = H16 * 8, (8, 6, 5)[shift % 3], 48, 4
-    T = max(40, min(3000, (6 << 20) // (H * 2)))               # X just past the size from which the list is used
+    T = max(40, min(4000, (6 << 20) // (H * 2)))               # X just past the size from which the list is used
+    listed = H16 >= 96 and (H16 >= 128 or k >= 8)
     N = T * k
     K = wl.random_routing(rng, T, k, E, p_masked=0.04, p_invalid=0.01)
     X = rng.integers(0, 1 << 16, size=(T, H), dtype=np.uint16)                     # any bits: dispatch copies
@@ -41,9 +43,13 @@ def test_dispatch_writes_every_vector_once(moe, H16, shift):
         buf = torch.full(((N + 2) * H + 128,), 0x7B7B, dtype=torch.int16, device="cuda")
         assert buf.data_ptr() % 128 == 0
         window = buf[shift * 8:shift * 8 + N * H].view(N, H)
+        if with_order:
+            plan.dispatch_order.fill_(-77)
         moe.moe_plan(shape, kd, plan)
         moe.moe_dispatch(shape, xd, kd, plan, window)
         torch.cuda.synchronize()
+        if with_order:
+            assert bool((plan.dispatch_order[:2 * N] == -77).any()) != listed
         got = to_host(buf).view(np.uint16)
         rows = got[shift * 8:shift * 8 + N * H].reshape(N, H)
         assert np.array_equal(rows[:ref.window_rows], want)
@@ -52,26 +58,43 @@ def test_dispatch_writes_every_vector_once(moe, H16, shift):
         assert np.all(got[shift * 8 + N * H:] == 0x7B7B)
 
 
-@pytest.mark.parametrize("T,H,k,stride", [(2700, 16392, 3, 0),       # one stretch (single-launch plan), ragged rows
+@pytest.mark.parametrize("T,H,k,stride", [(4200, 16392, 3, 0),       # ragged rows, slices longer than a wave
                                           (9001, 4872, 3, 0),        # stretches that begin and end inside a token
                                           (9000, 4864, 5, 7000),     # unequal slices, dropped branches, ragged last stretch
-                                          (29000, 1536, 2, 0)])      # two branches per unit
+                                          (29000, 1600, 3, 0),       # two branches per unit, rows of 25 lines
+                                          (28500, 1544, 4, 14500),   # two branches per unit, ragged rows, dropped branches
+                                          (29000, 1536, 2, 0)])      # degree 2, equal slices
 def test_dispatch_with_bulk_reads_of_x(moe, T, H, k, stride):
     """X of more than 80 MiB: the list's stretches are read in bulk ahead of their copies."""
+    assert T * H * 2 > 80 << 20
+    dispatch_large(moe, T, H, k, stride, True)
+
+
+@pytest.mark.parametrize("T,H,k,stride,given,used", [(2700, 16392, 3, 0, True, True),      # a single-launch plan: one stretch, no bulk reads
+                                                     (33000, 4096, 8, 0, False, False)])   # no list, X beyond the caches: 8 branches per unit
+def test_dispatch_of_large_x_without_bulk_reads(moe, T, H, k, stride, given, used):
+    dispatch_large(moe, T, H, k, stride, used, given)
+
+
+def dispatch_large(moe, T, H, k, stride, used, given=True):
     from paper_2605_06055_amd.layer import MoeLayer, to_device, to_host
     rng = np.random.default_rng(T)
     E, R = 48, 6
-    assert T * H * 2 > 80 << 20
     K = wl.random_routing(rng, T, k, E, p_masked=0.03, p_invalid=0.01)
     ref = oracle.plan(K, E, R, stride)
-    print(f"[bulk] T={T} H={H} k={k} stride={stride}", flush=True)
+    print(f"[large X] T={T} H={H} k={k} stride={stride} list={used}", flush=True)
     layer = MoeLayer(T, H, k, E, R, region_stride_rows=stride, schedule=moe.MOE_SCHEDULE_PREFILL)
+    layer.plan.dispatch_order.fill_(-77)
+    if not given:
+        layer._plan_struct.dispatch_order = None
     x = torch.randint(-(1 << 15), 1 << 15, (T, H), dtype=torch.int16, device="cuda")
     bits = layer.window.view(torch.int16)
     bits.fill_(0x7B7B)
     layer.dispatch(x.view(torch.bfloat16), to_device(K))
     torch.cuda.synchronize()
+    assert bool((layer.plan.dispatch_order[:2 * T * k] == -77).any()) != used
     assert np.array_equal(to_host(layer.plan.row_map)[:T * k].reshape(T, k), ref.row_map)
+    assert stride == 0 or ref.status[1] > 0
     rows = torch.from_numpy(ref.row_map.reshape(-1).astype(np.int64)).cuda()
     at = torch.full((bits.shape[0],), -1, dtype=torch.int64, device="cuda")
     at[rows[rows >= 0]] = (torch.arange(T * k, device="cuda") // k)[rows >= 0]

@@ -139,9 +139,9 @@ def test_full_size_prefill_configs(moe, name):
 
 
 @pytest.mark.parametrize("T,H,k,E,R", [(19000, 7168, 2, 64, 8),      # X = 272 MB: two branches per dispatch unit
-                                       (33000, 4096, 8, 128, 16)])   # X = 270 MB, one-wave slices: eight per unit
+                                       (33000, 4096, 8, 128, 16)])   # X = 270 MB: along the order list, X read in bulk
 def test_batches_larger_than_the_infinity_cache(moe, T, H, k, E, R):
-    """Token rows of more than 256 MiB: the prefill dispatch switches to larger units (it cannot find X cached)."""
+    """Token rows of more than 256 MiB, which the prefill dispatch cannot find cached."""
     run_workload(moe, wl.Config("big-x", T=T, H=H, k=k, E=E, R=R, seed=T), moe.MOE_SCHEDULE_PREFILL)
 
 
@@ -236,7 +236,7 @@ def test_special_values_in_combine(moe):
 @pytest.mark.parametrize("T,H,k,E,R,dtype", [
     (4000, 4104, 6, 96, 12, np.uint16),      # k = 6; rows of 513 vectors: ragged last wave of every token
     (3100, 2056, 8, 64, 8, np.float32),      # fp32 storage, rows of 514 vectors
-    (16001, 2048, 8, 32, 4, np.uint16),      # two rounds of the persistent grid with a ragged last round
+    (16001, 2048, 8, 32, 4, np.uint16),      # 32 units a thread, fewer for most: one launch, all results in registers
 ])
 def test_combine_streaming_form_with_masked_slots(moe, T, H, k, E, R, dtype):
     """Launches large enough for combine's deferred-store form (T * H * b / 16 above 1.5 Mi vectors, k of 6 or 8)
@@ -597,16 +597,15 @@ def check_order_list(order, K, ref, E):
 
 
 def test_dispatch_order_list(moe):
-    """Where the shape qualifies (rows of at least 12 KB: X up to 96 MiB and windows up to 770 MiB; rows of 8 to
-    12 KB and of 2 to 4 KB: windows up to 1100 MiB) the plan also emits the placed
-    branches sorted by window row inside stretches of tokens, and dispatch walks that list.  The list is checked
+    """Where the shape qualifies (plan_order_tiles: rows of 1.5 KB or more, X of more than 5 MiB, not all degrees) the plan
+    also emits the placed branches sorted by window row inside stretches of tokens, and dispatch walks that list.  The list is checked
     against the oracle's row map, and dispatch must give the same window with and without it."""
     from paper_2605_06055_amd.layer import MoeLayer, to_device, to_host
     rng = np.random.default_rng(91)
     cases = [(777, 7168, 8, 256, 32, 0, False),       # one launch plan: the batch is one stretch
              (6000, 4096, 8, 64, 8, 0, False),        # two launches, two units per workgroup, two stretches of 24 tiles
              (2900, 7168, 8, 256, 32, 0, False),      # two stretches of 12 tiles, ragged last one
-             (7000, 7168, 8, 256, 32, 0, False),      # just under the limit on X (96 MiB): four stretches of 14 tiles
+             (7000, 7168, 8, 256, 32, 0, False),      # 96 MiB of X, read in bulk: five stretches of 11 tiles
              (2600, 4096, 8, 64, 8, 2000, False),     # fixed stride with dropped branches
              (2100, 8200, 6, 48, 4, 0, True),         # several source ranks, ragged row tail
              (1300, 2048, 9, 40, 5, 0, False),        # fp32 storage below (rows of 8 KB)
