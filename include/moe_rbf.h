@@ -123,12 +123,14 @@ typedef struct moe_plan_t {
                                     recvTokenNumPerExpert); the rows a rank region receives (n^recv) are its segment sum */
   int32_t *recv_offset;   /* [E+1]  out, may be NULL: first row of expert e's whole block; [E] = one past the last block */
   int32_t *dispatch_order; /* [2*T*k] optional (NULL: not used): plan state for the PREFILL dispatch.  Where it pays
-                                    (rows of 1.5 KB or more, x of more than 5 MiB, and beyond 80 MiB of x mostly routing degrees of at least 3) the plan also lists the
+                                    (rows of 1.5 KB or more, x of more than 5 MiB, not all routing degrees) the plan also lists the
                                     placed branches as (token, window row) pairs, sorted by window row inside stretches
                                     of about 28 MB of X, and moe_dispatch walks that list instead of the tokens: rows
                                     of one expert are then written together.  Entries of unplaced branches are -1.
                                     The result of moe_dispatch is the same with or without it.  Content and use are
-                                    decided by the shape alone; a DECODE dispatch leaves a valid list too. */
+                                    decided by the shape alone; a DECODE dispatch leaves a valid list too.
+                                    moe_dispatch_quant does not read it: a caller that only dispatches quantised rows
+                                    passes NULL and saves the plan 0.4 to 3 us (5 000 to 130 000 branches). */
   const void *prefetch;    /* optional (NULL: none), read by moe_plan / moe_plan_static only: device memory that the
                                     call should pull into the cache hierarchy while it plans, normally the x of the
                                     moe_dispatch that follows.  The plan kernels are latency-bound and leave the

@@ -148,7 +148,8 @@ def moe_resolve_schedule(shape: MoeShape) -> int:
 
 
 class MoePlan:
-    """Device buffers of ``moe_plan_t`` held as torch tensors (memory plumbing only)."""
+    """Device buffers of ``moe_plan_t`` held as torch tensors (memory plumbing only).  ``with_order=False`` leaves out the
+    order list that only the unquantised prefill dispatch reads."""
 
     def __init__(self, shape: MoeShape, device="cuda", with_send_idx: bool = True, source_count=None,
                  with_order: bool = True):

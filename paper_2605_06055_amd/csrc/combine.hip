@@ -130,7 +130,7 @@ __global__ __launch_bounds__(BLOCK) void combine_rows_kernel(const u32x4 *__rest
 // so a thread holds as many results as the CU has room for: 36 in registers (144 of the 256 VGPRs that 8 waves may take)
 // and 20 in the 160 KB of LDS, which are otherwise idle.  us per layer, X not cached, 28 units and two rounds per launch /
 // up to 56 units and one: H = 7168: T = 5000 209.4 / 204.5, 6200 281 / 273, Zipf 16384 722 / 707; H = 4096: T = 11000
-// 268 / 260.5, group-limited 32768 845 / 830; T = 4096, H = 7168 (28 units either way) 176.3 / 176.2.
+// 268 / 260.5, group-limited 32768 845 / 837.
 // Same arithmetic as combine_rows_kernel
 // (ascending j, one fma per placed branch, one rounding).  Units (token, column) are numbered token-major over
 // columns padded to a multiple of 64, so that a wave stays inside one token: without the padding (H = 4104: 115
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kDeferBlock) void combine_deferred_kernel(const u32
 // lane masks.  us per layer, the form above / this one: k = 6: H = 7168, T = 3000 105.9 / 102.4, T = 4096 139.1 / 134.0; H = 4104, T = 5500
 // 124.2 / 120.2; k = 8: H = 7168: T = 2400 107.1 / 105.7, 3584 155.1 / 152.8, 4096 175.8 / 173.4; H = 1024, T = 28000 178.9 /
 // 177.6; H = 4104, T = 6300 176.0 / 173.9; fp32: H = 2056, T = 5000 138.8 / 138.2.  Not for more units: with 36 results the
-// compiler spills them (H = 7168: T = 4096 211, T = 4600 244 against 193).
+// compiler keeps part of them in scratch memory (H = 7168: T = 4096 211, T = 4600 244 against 193).
 constexpr int kRoundUnits = 28;
 
 template <int DT, int KFIX>

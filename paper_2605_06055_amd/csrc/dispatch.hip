@@ -80,8 +80,8 @@ __device__ __forceinline__ size_t row_offset(int row, int H16) {
 // slices fit the L2 of an XCD, so consecutive workgroups of an XCD write consecutive rows of one expert block and re-read
 // tokens from L2.  Without LIST: in token order, for narrow rows and for rows that do not start at a cache line (ALIGNED =
 // false; their cuts differ from branch to branch).  ROTATE: the slices are not all equal (see above; always so without ALIGNED).
-// A unit takes `lanes` = the longest slice's vectors, and a workgroup is U units side by side without a gap, about
-// 4 waves: units padded to 64 or 128 lanes leave up to half of a wave idle while workgroups can only be started at
+// A unit takes `lanes` = the longest slice's vectors, and a workgroup is U units side by side without a gap: 4 waves or so,
+// up to 10 where only that is a whole number of waves (72 lanes: 8 units, 9 waves).  Units padded to 64 or 128 lanes leave up to half of a wave idle while workgroups can only be started at
 // about 4.7 per ns (H = 4608: 84 us against 95 with 72 of 128 lanes busy).  Unequal short slices leave lanes idle all
 // the same; there Q = 2 consecutive branches per unit pay (H = 640 77 -> 64 us, 768 86 -> 72), while equal or longer
 // slices lose with them (H = 1536 82 -> 88, 3072 81 -> 88, 8192 74 -> 86: more writes in flight arrive in less order).
@@ -93,12 +93,17 @@ __device__ __forceinline__ size_t row_offset(int row, int H16) {
 // us per layer, token order / list / list with bulk reads, X not cached when the layer starts: H = 7168: T = 8192 485 / 420 /
 // 383, 13000 760 / 699 / 602, Zipf 16384 933 / 812 / 725; H = 8192, T = 12000 768 / 656 / 609; H = 4096: T = 24000 633 / 683 /
 // 605, 11000 294 (list) / 268; H = 3072, k = 10, T = 32768 1087 / 908 / 799; H = 4096, k = 3, T = 16000 263 / 212 / 188; X
-// fully cached: H = 7168: T = 8192 356 / 357 / 371, 16384 709 / 718 / 741; H = 4096, T = 20000 505 / 466 / 479.
-// ALONE: one unit per workgroup of 128 threads, its entry in scalar registers.  Slices of 97 to 112 vectors nearly fill two
-// waves that way, and without bulk reads they then do better: us per dispatch, packed / alone: H = 7168: T = 1400 25.4 /
-// 23.4, 2000 38.3 / 35.2, 2800 52.4 / 55.0, 4096 79.4 / 80.9, where the layer with X not cached takes 210 / 197; H = 6656,
-// T = 1400 25.4 / 22.7, 3000 54.3 / 51.5; shorter and longer slices do not (H = 6144, T = 1400 21.3 / 22.4; H = 8192 27.4 /
-// 27.8; H = 4608 17.4 / 22.1).
+// fully cached: H = 7168: T = 8192 356 / 357 / 371, 16384 709 / 718 / 741; H = 4096, T = 20000 505 / 466 / 479.  So a cached X
+// loses 1 to 4 % (k = 4, T = 10000, H = 7168 233 / 246: 6 %), and one that is not wins 8 to 25 %.  The latter decides: X of this size
+// stays cached only while little else runs, and not even always when the kernel in front of the layer has just written
+// it (H = 7168, T = 16384, token order / list with bulk reads: 928 / 757).
+// ALONE: one unit per workgroup of 128 threads, its entry in scalar registers.  Slices of 104 and 112 vectors nearly fill two
+// waves that way, packed they take 13 and 14 waves for 8 units, and without bulk reads they do better alone.  us per layer, packed /
+// alone, T = 700, 1400, 2800, 4096: H = 6400 36.8 / 35.9, 64.3 / 61.7, 115.1 / 111.0, 164.5 / 158.0; H = 6656 37.2 / 36.4, 64.1 /
+// 62.1, 115.2 / 113.5, 165.4 / 160.1; H = 6912 38.2 / 37.1, 65.4 / 63.7, 119.2 / 119.3, 170.6 / 165.6; H = 7168 38.7 / 37.9,
+// 66.5 / 65.3, 120.9 / 124.4, 174.7 / 172.8 (with X not cached 210 / 197).  Shorter and longer slices do not: H = 5632 33.0 / 33.6,
+// 55.2 / 56.7, 98.0 / 101.0, 137.6 / 141.1; H = 7424 (120 vectors) 40.1 / 39.2, 69.3 / 68.1, 126.9 / 127.7, 181.1 / 184.9; H = 7680
+// 40.3 / 39.9, 70.2 / 70.7, 129.0 / 134.4, 184.5 / 188.5; H = 8192 42.0 / 42.0, 73.8 / 75.2, 136.0 / 138.3, 189.7 / 190.5.
 template <int Q, bool LIST, bool ROTATE, bool ALIGNED, bool WARM, bool ALONE = false>
 __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__restrict__ X,
                                                              const int32_t *__restrict__ entries,

@@ -159,8 +159,8 @@ __device__ __forceinline__ void write_plan_tables(const int *own, const int *oth
   }
   // With several sources g also counts the other ranks' rows, so the own counts of a rank's experts are summed here,
   // one wave per rank.  (One thread per rank was a chain of E_r dependent LDS reads that the whole launch waited
-  // for: with R = 1 the decode dispatch of 222 tokens took 13.2 us at E = 256 and the plan of 24 576 branches 27 us
-  // at E = 512, against 7.9 and 9.1 us now.)
+  // for: with R = 1 the decode dispatch of 222 tokens of H = 2048 took 13.1 us at E = 256 and the plan of 24 576 branches
+  // 28.8 us at E = 512, against 5.5 and 12.5 us now, in replayed graphs.)
   if (others) {
     for (int r = threadIdx.x / kWave; r < d.R; r += nthreads / kWave) {
       int c = 0;
