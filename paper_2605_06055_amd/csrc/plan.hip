@@ -325,7 +325,8 @@ bool plan_uses_workspace(int64_t N) { return N > (int64_t)MOE_PLAN_FUSED_MAX_TIL
 //     H = 2560: T = 12288: k = 2 72.0 / 74.4, k = 4 111.5 / 108.2; T = 19456: k = 2 123.3 / 139.2, k = 4 198.4 / 208.9.
 // Narrower rows pay more for the list in the plan than dispatch gains (H = 640, T = 10000 59.2 / 57.2), and so do
 // batches whose X is in the L2s anyway: H = 2048, T = 1400 26.9 / 26.5; H = 2560, T = 1024 23.5 / 23.1; but H = 3072,
-// T = 1400 (8.6 MB) 34.5 / 35.7.
+// T = 1400 (8.6 MB) 34.5 / 35.7.  (Plan and dispatch, with the list / without: H = 4096, T = 500 17.1 / 16.2, H = 7168, T = 128
+// 11.7 / 11.4; a dispatch alone, on a plan that is kept, is up to 0.6 us slower without: T = 128 4.0 / 4.2, T = 300 8.7 / 9.2.)
 // From 80 MiB of X on the list is used at every window size with X read in bulk (order_streams_x), except for degrees that
 // re-read X too little: us per layer, X not cached, list with bulk reads / the rule above: k = 2: H = 7168, T = 14000 225.5 /
 // 214.6; H = 4096, T = 28000 246 / 266; k = 1: H = 4096, T = 20000 128 / 122; around the line: H = 7168: T = 5000 (72 MB)
