@@ -228,42 +228,74 @@ __global__ __launch_bounds__(kDeferBlock) void combine_deferred_kernel(const u32
 }
 
 // The form for at most 28 units a thread (one launch, no LDS): the loop that the compiler unrolls by itself, with the tests as
-// lane masks.  us per layer, the form above / this one: k = 6: H = 7168, T = 3000 105.9 / 102.4, T = 4096 139.1 / 134.0; H = 4104, T = 5500
-// 124.2 / 120.2; k = 8: H = 7168: T = 2400 107.1 / 105.7, 3584 155.1 / 152.8, 4096 175.8 / 173.4; H = 1024, T = 28000 178.9 /
-// 177.6; H = 4104, T = 6300 176.0 / 173.9; fp32: H = 2056, T = 5000 138.8 / 138.2.  Not for more units: with 36 results the
-// compiler keeps part of them in scratch memory (H = 7168: T = 4096 211, T = 4600 244 against 193).
+// lane masks.  us per layer, the form above / this one: k = 6: H = 7168, T = 3000 105.9 / 102.3, T = 4096 139.1 / 134.6; H = 4104, T = 5500
+// 124.2 / 120.9; k = 8: H = 7168: T = 2400 107.1 / 106.4, 3584 155.1 / 154.3, 4096 175.8 / 175.8; H = 1024, T = 28000 178.9 /
+// 178.1; H = 4104, T = 6300 176.0 / 174.2; fp32: H = 2056, T = 5000 138.8 / 138.2.  Not for more units: with 36 results the
+// compiler keeps part of them in scratch memory (H = 7168: T = 4096 211, T = 4600 244 against 193).  The unit's code is written
+// out and the loop over `base`, which runs once, stays: as a call of combine_unit the compiler schedules it otherwise, which costs
+// fp32 rows up to 1.7 % (H = 3584, T = 4000, k = 6 132.7 / 134.8; H = 896, T = 9984, k = 8 111.1 / 112.4) and gains 0.5 % on
+// bf16 rows of 14 KB; without the loop H = 896, T = 9984 takes 111.7 and bf16 rows move by 0.8 % either way.
 constexpr int kRoundUnits = 28;
 
 template <int DT, int KFIX>
 __global__ __launch_bounds__(kDeferBlock) void combine_round_kernel(const u32x4 *__restrict__ Yexp,
-                                                                    const float *__restrict__ W,
-                                                                    const int32_t *__restrict__ row_map,
-                                                                    u32x4 *__restrict__ Y, int k_arg, int H16,
-                                                                    int cols_pad, int units, int dq, int dr) {
+                                                                       const float *__restrict__ W,
+                                                                       const int32_t *__restrict__ row_map,
+                                                                       u32x4 *__restrict__ Y, int k_arg, int H16,
+                                                                       int cols_pad, int units, int dq, int dr,
+                                                                       int first) {
+  // this launch covers units [first, units)
   constexpr int R = kRoundUnits;
   const int k = KFIX > 0 ? KFIX : k_arg;
+  constexpr int G = KFIX > 0 ? (KFIX < kGather ? KFIX : kGather) : kGather;
   const int nthreads = (int)gridDim.x * kDeferBlock;
-  const long long u0 = (int)blockIdx.x * kDeferBlock + (int)threadIdx.x;
+  const int g = (int)blockIdx.x * kDeferBlock + (int)threadIdx.x;
   const int32_t *rm = (const int32_t *)__builtin_assume_aligned(row_map, 16);
   const float *wt = (const float *)__builtin_assume_aligned(W, 16);
-  const int t0 = (int)(u0 / cols_pad), col0 = (int)(u0 - (long long)t0 * cols_pad);
-  u32x4 res[R];
-  int t = t0, col = col0;
+  for (long long base = first; base < units; base += (long long)nthreads * R) {
+    const long long u0 = base + g;
+    const int t0 = (int)(u0 / cols_pad), col0 = (int)(u0 - (long long)t0 * cols_pad);
+    u32x4 res[R];
+    int t = t0, col = col0;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    if (u0 + (long long)r * nthreads < units && col < H16)       // the first test is uniform per wave
-      res[r] = combine_unit<DT, KFIX>(Yexp, wt, rm, t, col, k, H16);
-    col += dr;
-    t += dq;
-    if (col >= cols_pad) col -= cols_pad, ++t;
-  }
-  t = t0, col = col0;
+    for (int r = 0; r < R; ++r) {
+      if (u0 + (long long)r * nthreads < units && col < H16) {     // the first test is uniform per wave
+        const int ts = uniform(t);
+        const int32_t *rows = rm + (size_t)ts * k;
+        const float *w = wt + (size_t)ts * k;
+        Acc<DT> acc;
+        acc.zero();
+        for (int j0 = 0; j0 < k; j0 += G) {
+          int row[G];
+          float wj[G];
+          u32x4 y[G];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    if (u0 + (long long)r * nthreads < units && col < H16) store_stream(Y + (size_t)t * (size_t)H16 + col, res[r]);
-    col += dr;
-    t += dq;
-    if (col >= cols_pad) col -= cols_pad, ++t;
+          for (int u = 0; u < G; ++u) {
+            const bool in = (KFIX > 0 && KFIX % G == 0) || j0 + u < k;
+            row[u] = in ? uniform(rows[j0 + u]) : -1;
+            wj[u] = in ? __uint_as_float(uniform(__float_as_uint(w[j0 + u]))) : 0.0f;
+          }
+#pragma unroll
+          for (int u = 0; u < G; ++u)
+            y[u] = row[u] >= 0 ? load_stream(Yexp + (size_t)row[u] * (size_t)H16 + col) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int u = 0; u < G; ++u)
+            if (row[u] >= 0) acc.fma(wj[u], y[u]);
+        }
+        res[r] = acc.result();
+      }
+      col += dr;
+      t += dq;
+      if (col >= cols_pad) col -= cols_pad, ++t;
+    }
+    t = t0, col = col0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (u0 + (long long)r * nthreads < units && col < H16) store_stream(Y + (size_t)t * (size_t)H16 + col, res[r]);
+      col += dr;
+      t += dq;
+      if (col >= cols_pad) col -= cols_pad, ++t;
+    }
   }
 }
 
@@ -290,7 +322,7 @@ static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out,
   if (per_thread <= kRoundUnits) {
     auto once = [&](auto kernel) {
       return launch(kernel, dim3(grid), dim3(kDeferBlock), 0, s, (const u32x4 *)expert_out, W, (const int32_t *)p.row_map,
-                    (u32x4 *)y, d.k, d.H16, cols_pad, units, nthreads / cols_pad, nthreads % cols_pad);
+                    (u32x4 *)y, d.k, d.H16, cols_pad, units, nthreads / cols_pad, nthreads % cols_pad, 0);
     };
     if (d.k == 8) return once(combine_round_kernel<DT, 8>);
     if (d.k == 6) return once(combine_round_kernel<DT, 6>);
