@@ -261,10 +261,7 @@ __global__ __launch_bounds__(BLOCK) void decode_dispatch_kernel(const u32x4 *__r
   float scale = 0.0f;
   if (QUANT) {
     __shared__ float red[BLOCK / kWave];
-    bool has[V];
-#pragma unroll
-    for (int x = 0; x < V; ++x) has[x] = col0 + x * BLOCK < d.H16;
-    scale = quantise_row<BLOCK, V>(v, has, q, red);
+    scale = quantise_row<BLOCK, V>(v, q, red);
   }
 
   // Several source ranks: rows of the other sources in front of a slot's sub-block =
@@ -435,6 +432,160 @@ __global__ __launch_bounds__(BLOCK) void decode_dispatch_kernel(const u32x4 *__r
   }
 }
 
+// Decode dispatch of larger batches, where every workgroup's counting over all ids is what the launch waits for.  A workgroup
+// takes up to 8 consecutive branches: all of TT tokens, or (TT = 1) one of GROUPS parts of a token's slots.  It counts the ids
+// once into an LDS histogram (low 16 bits: the expert's branches; high 16 bits: those in front of the workgroup's
+// first; at most MOE_DECODE_MAX_BRANCHES = 8192), then each wave takes a slot and sums the counts of the experts below.
+// Compares and ballots (decode_dispatch_kernel) cost 8 instructions per id and slot, this one LDS atomic per id, but two barriers
+// more; figures of both at decode_by_hist.  What is left at T = 512, H = 7168, k = 8 (13.7 us): 66 MB at the scattered-write rate
+// 10.6, launch 1.7, the ids' round trip and the counting.  Short code counts: the trips over the ids are not unrolled, since each
+// jump into code that is not cached costs 0.1 to 0.2 us here, and two trips requested ahead are no better than one.
+template <int MOST, int V, int TT, int GROUPS, bool QUANT, bool MULTI>
+__global__ __launch_bounds__(MOST) void decode_hist_kernel(const u32x4 *__restrict__ X, const int32_t *__restrict__ K,
+                                                            void *__restrict__ window_any,
+                                                            float *__restrict__ window_scale, Dims d, PlanView p,
+                                                            int chunks, int width, int per_group) {
+  static_assert(TT == 1 || GROUPS == 1, "a workgroup takes whole tokens or part of one");
+  const int block = (int)blockDim.x, waves = block / kWave;      // whole waves, at most MOST threads
+  constexpr int kSlots = 8;                                     // slots ranked together
+  extern __shared__ int lds[];
+  __shared__ int rows[kSlots];
+  __shared__ float red[QUANT ? TT * (MOST / kWave) : 1];
+  if (blockIdx.x == 0) {                 // the tables workgroup goes first: it is the longest one
+    tables_from_ids_block(K, d, p, lds);
+    return;
+  }
+  const int b = (int)blockIdx.x - 1;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid / kWave);
+  // workgroup -> (first token, chunk, slot group); the workgroups of a token share an XCD (see decode_dispatch_kernel)
+  const int sets = (d.T + TT - 1) / TT, per_set = chunks * GROUPS;
+  int set, rem;
+  if (per_set == 1) {
+    set = b, rem = 0;
+  } else if (b >= (sets & ~7) * per_set) {
+    set = b / per_set;
+    rem = b - set * per_set;
+  } else {
+    const int q = b >> 3, sq = q / per_set;
+    set = sq * 8 + (b & 7);
+    rem = q - sq * per_set;
+  }
+  const int c = rem / GROUPS, t0 = set * TT;
+  const int jlo = GROUPS == 1 ? 0 : (rem % GROUPS) * per_group;
+  const int first = t0 * d.k + jlo;                             // the workgroup's branches: [first, first + slots)
+  const int slots = TT == 1 ? min(d.k - jlo, per_group) : min(TT, d.T - t0) * d.k;
+  if (slots <= 0) return;
+
+  // everything that comes from memory is requested up front
+  const int col0 = c * width + tid, end = min(c * width + width, d.H16);
+  u32x4 v[TT][V];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+    for (int x = 0; x < V; ++x) {
+      const int col = col0 + x * block;
+      const u32x4 *src = X + (size_t)(t0 + tt) * (size_t)d.H16 + col;
+      v[tt][x] = (TT == 1 || t0 + tt < d.T) && col < end ? (GROUPS > 1 ? *src : load_stream(src)) : u32x4{0u, 0u, 0u, 0u};
+    }
+  i32x4 next = load_ids(K, tid, d.N);
+  int my_e = lane < min(kSlots, slots) ? K[first + lane] : -1;
+
+  int *hist = lds;                       // [E]
+  for (int e = tid; e < d.E; e += block) hist[e] = 0;
+  __syncthreads();
+#pragma unroll 1
+  for (int q = tid; 4 * q < d.N; q += block) {
+    const i32x4 ids = next;
+    next = load_ids(K, q + block, d.N);
+    const int ahead = first - 4 * q;                            // id n of the piece is in front <=> n < ahead
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+      if ((unsigned)ids[n] < (unsigned)d.E) atomicAdd(&hist[ids[n]], n < ahead ? 0x10001 : 1);
+  }
+  if (QUANT) {
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const float amax = wave_amax(v[tt]);
+      if (lane == 0) red[tt * waves + wave] = amax;
+    }
+  }
+  __syncthreads();
+  u32x2 q[TT][V];
+  float scale[TT];
+  if (QUANT) {
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) scale[tt] = quantise_with(v[tt], red + tt * waves, waves, q[tt]);
+  }
+
+  const bool fixed = d.stride > 0;
+  for (int j0 = 0; j0 < slots; j0 += kSlots) {
+    const int nb = min(kSlots, slots - j0);
+    if (j0 > 0) {                        // the previous slots are now in front too
+      __syncthreads();
+      if (wave == 0 && (unsigned)my_e < (unsigned)d.E) atomicAdd(&hist[my_e], 0x10000);
+      my_e = lane < nb ? K[first + j0 + lane] : -1;
+      __syncthreads();
+    }
+    for (int u = wave; u < nb; u += waves) {
+      const int e = __builtin_amdgcn_readlane(my_e, u);
+      int s = -1, row = -1;
+      if ((unsigned)e < (unsigned)d.E) {
+        const int rank = fixed ? e / d.Er : 0, lo = fixed ? rank * d.Er : 0;
+        int below = 0;
+        for (int x0 = 0; x0 < e; x0 += 4 * kWave) {
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            const int x = x0 + n * kWave + lane;
+            below += x >= lo && x < e ? hist[x] & 0xffff : 0;
+          }
+        }
+        below = __builtin_amdgcn_readlane(wave_inclusive_scan(below), kWave - 1);
+        s = (hist[e] >> 16) + __popcll(__ballot(my_e == e) & ((1ull << u) - 1ull));
+        row = (fixed ? (int)(rank * d.stride) : 0) + below + s;
+        if (fixed && row >= (int)((rank + 1) * d.stride)) row = -1;
+      }
+      if (lane == 0) {
+        rows[u] = row;
+        if (c == 0) {
+          const int n = first + j0 + u;
+          if (p.send_idx) p.send_idx[n] = s;
+          p.row_map[n] = row;
+          if (d.order_tiles > 0) {        // a later prefill-schedule dispatch on this plan walks the order list
+            p.order[2 * n] = TT == 1 ? t0 : n / d.k;
+            p.order[2 * n + 1] = row;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    const int row_of = rows[lane & (kSlots - 1)];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const int u0 = TT == 1 ? 0 : tt * d.k, u1 = TT == 1 ? nb : min(u0 + d.k, nb);
+      for (int u = u0; u < u1; ++u) {
+        const int r = __builtin_amdgcn_readlane(row_of, u);
+        if (r < 0) continue;
+        if (QUANT) {
+          u32x2 *dst = (u32x2 *)window_any + (size_t)r * (size_t)d.H16;  // H bytes per row = H16 8-byte units
+#pragma unroll
+          for (int x = 0; x < V; ++x) {
+            const int col = col0 + x * block;
+            if (col < end) __builtin_nontemporal_store(q[tt][x], dst + col);
+          }
+          if (tid == 0) window_scale[r] = scale[tt];
+        } else {
+          u32x4 *dst = (u32x4 *)window_any + (size_t)r * (size_t)d.H16;
+#pragma unroll
+          for (int x = 0; x < V; ++x) {
+            const int col = col0 + x * block;
+            if (col < end) store_stream(dst + col, v[tt][x]);
+          }
+        }
+      }
+    }
+  }
+}
+
 // Quantised dispatch with the row map from moe_plan: one workgroup per token holds the whole row,
 // quantises it once and stores the codes and the scale to the k destination rows.
 template <int BLOCK, int V>
@@ -456,7 +607,7 @@ __global__ __launch_bounds__(BLOCK) void dispatch_quant_rows_kernel(const u32x4 
     v[x] = has[x] ? src[col] : u32x4{0u, 0u, 0u, 0u};
   }
   u32x2 q[V];
-  const float scale = quantise_row<BLOCK, V>(v, has, q, red);
+  const float scale = quantise_row<BLOCK, V>(v, q, red);
   const int32_t *rows = row_map + (size_t)t * k;
   for (int j0 = 0; j0 < k; j0 += 8) {
     int row[8];
@@ -604,6 +755,60 @@ hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void
   return hipErrorInvalidValue;
 }
 
+// Which kernel a decode batch takes: compares and ballots while the counting is small (fewer barriers), the histogram beyond.
+// us per dispatch, ballots / histogram, in replayed graphs on cold buffers:
+//   k = 8: H = 7168: T = 160 5.6 / 6.0, 192 6.9 / 6.6, 512 14.8 / 13.7; H = 5120 and 6144 (chunks of 5 and 6 waves): T = 256 6.4 / 6.5
+//          and 7.2 / 7.3, 320 7.7 / 7.6 and 8.7 / 8.3, 448 11.0 / 9.7 and 12.1 / 11.0; H = 2048: T = 192 5.0 / 4.2, 512 9.8 / 6.5;
+//   k = 5, 4, 3, 2, 1: H = 4096, T = 256 5.2 / 4.8, 4.7 / 4.5, 4.4 / 4.3, 3.9 / 4.0, 3.7 / 3.7; T = 1024 16.8 / 13.9, 14.6 / 9.7,
+//          12.3 / 8.0, 10.2 / 6.1, 7.7 / 5.3; H = 1024, k = 1, T = 5000 51.5 / 8.0;
+//   quantised: k = 8: H = 7168, T = 64 3.7 / 4.2, 128 4.9 / 4.8, 512 12.6 / 9.3; k = 1 to 5, H = 4096, T = 64 4.05 to 4.4 / 3.75 to 4.2.
+static bool decode_by_hist(const Dims &d, bool quant) {
+  if (d.k < 6) return quant || d.N > 600;
+  if (quant) return d.N > 1024;
+  return d.N > (d.H16 > 512 && d.H16 <= 832 ? 2304 : 1408);
+}
+
+template <int V, int TT, int G, bool QUANT>
+static hipError_t launch_decode_hist_shape(const Dims &d, const void *x, const int32_t *K, const PlanView &p,
+                                           void *window, float *window_scale, hipStream_t s) {
+  constexpr int kMost = QUANT ? 1024 : 512;
+  // chunks of nearly the same length, and as many waves as a chunk needs, but enough to count the ids
+  const int chunks = (d.H16 + kMost * V - 1) / (kMost * V);
+  const int width = ((d.H16 + chunks - 1) / chunks + kLine - 1) / kLine * kLine;
+  // (7 waves: 8.  H = 7168, T = 512 14.3 / 13.6 us; but 5 and 6 waves stay: H = 5120, T = 400 9.2 / 10.9)
+  int threads = std::max(256, ((width + V - 1) / V + kWave - 1) / kWave * kWave);
+  if (threads == 7 * kWave) threads = 8 * kWave;
+  const int per_group = (d.k + G - 1) / G;
+  const size_t lds = (size_t)(4 * d.E + 1 + 2) * sizeof(int);
+  const dim3 grid((unsigned)((d.T + TT - 1) / TT) * (unsigned)(chunks * G) + 1u);
+  return launch(decode_hist_kernel<kMost, V, TT, G, QUANT, false>, grid, dim3((unsigned)threads), lds, s, (const u32x4 *)x, K,
+                window, window_scale, d, p, chunks, width, per_group);
+}
+
+// How many branches a workgroup takes.  Degrees of 6 and more: a token's slots, in one workgroup or two.  More workgroups spread
+// the stores, fewer repeat the counting less: us per dispatch, two / one, k = 8: H = 4096 (8 waves): T = 256 5.5 / 5.6, 320 6.5 / 6.4, 512
+// 9.7 / 9.0; H = 2048 (4 waves): T = 512 6.5 / 6.6; H = 5120 (5 waves, 2 vectors a lane): T = 512 11.1 / 11.6; H = 7168: T = 384
+// 12.0 / 11.1, 512 13.7 / 14.3; quantised H = 7168: T = 256 5.8 / 5.9, 384 9.1 / 7.4, 512 10.1 / 9.3.
+// Smaller degrees: whole tokens, up to 8 branches, as long as about 384 workgroups remain (k = 4, H = 4096, T = 800: two tokens 8.0,
+// one 10.1; quantised T = 512: 5.5 / 5.1, T = 800 7.2 / 8.9).
+template <int V, bool QUANT>
+static hipError_t launch_decode_hist(const Dims &d, const void *x, const int32_t *K, const PlanView &p, void *window,
+                                     float *window_scale, hipStream_t s) {
+  if (d.k >= 6) {
+    const bool whole = d.H16 > 256 && (QUANT ? d.N > 2560 : d.H16 <= 512 && d.N > 2304);
+    return whole ? launch_decode_hist_shape<V, 1, 1, QUANT>(d, x, K, p, window, window_scale, s)
+                 : launch_decode_hist_shape<V, 1, 2, QUANT>(d, x, K, p, window, window_scale, s);
+  }
+  constexpr int kMost = QUANT ? 8 / V : 8;       // tokens whose rows fit in registers (with their codes)
+  const int chunks = QUANT ? 1 : (d.H16 + 512 * V - 1) / (512 * V);
+  int tt = d.k >= 5 ? 1 : d.k >= 3 ? 2 : d.k == 2 ? 4 : 8;
+  while (tt > 1 && (tt > kMost || (int64_t)d.T * chunks < (int64_t)tt * 384)) tt /= 2;
+  if (tt == 1) return launch_decode_hist_shape<V, 1, 1, QUANT>(d, x, K, p, window, window_scale, s);
+  if (tt == 2) return launch_decode_hist_shape<V, 2, 1, QUANT>(d, x, K, p, window, window_scale, s);
+  if (tt == 4) return launch_decode_hist_shape<V, 4 < kMost ? 4 : kMost, 1, QUANT>(d, x, K, p, window, window_scale, s);
+  return launch_decode_hist_shape<V, kMost, 1, QUANT>(d, x, K, p, window, window_scale, s);
+}
+
 template <int B, int V, int SB, int G>
 static hipError_t launch_decode_dispatch_shape(const Dims &d, const void *x, const int32_t *K, const PlanView &p,
                                                void *window, hipStream_t s) {
@@ -620,6 +825,9 @@ static hipError_t launch_decode_dispatch_shape(const Dims &d, const void *x, con
 
 hipError_t launch_decode_dispatch(const Dims &d, const void *x, const int32_t *K, const PlanView &p, void *window,
                                   hipStream_t s) {
+  if (!p.source_count && decode_by_hist(d, false))
+    return d.H16 <= 512 ? launch_decode_hist<1, false>(d, x, K, p, window, nullptr, s)
+                        : launch_decode_hist<2, false>(d, x, K, p, window, nullptr, s);
   // With a routing degree of at least 6 the slots of a token are split over 4 workgroups of 8 waves (2 slots
   // each), or over 2 (4 slots each) once the batch is so large that the counting, which every workgroup of a
   // token repeats over all ids, outweighs the better spread of the stores.  Measured, k = 8, us per dispatch
@@ -695,6 +903,11 @@ static hipError_t launch_decode_quant_bv(const Dims &d, const void *x, const int
 
 hipError_t launch_decode_dispatch_quant(const Dims &d, const void *x, const int32_t *K, const PlanView &p,
                                         void *window_q, float *window_scale, hipStream_t s) {
+  if (!p.source_count && decode_by_hist(d, true)) {
+    if (d.H16 <= 512) return launch_decode_hist<1, true>(d, x, K, p, window_q, window_scale, s);
+    if (d.H16 <= 2048) return launch_decode_hist<2, true>(d, x, K, p, window_q, window_scale, s);
+    return launch_decode_hist<4, true>(d, x, K, p, window_q, window_scale, s);
+  }
 #define GO(B_, V_) return launch_decode_quant_bv<B_, V_>(d, x, K, p, window_q, window_scale, s)
   MOE_QUANT_DECODE_SHAPES(GO);
 #undef GO

@@ -178,9 +178,22 @@ __device__ __forceinline__ void write_plan_tables(const int *own, const int *oth
   }
 }
 
+// The routing ids of a workgroup, requested in pieces of 16 bytes.  Piece q holds ids 4q..4q+3; past the last id: -1.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ i32x4 load_ids(const int32_t *__restrict__ K, int q, int N) {
+  const int i = 4 * q;
+  if (i + 4 <= N) return ((const i32x4 *)K)[q];
+  i32x4 v = {-1, -1, -1, -1};
+  if (i < N) v[0] = K[i];
+  if (i + 1 < N) v[1] = K[i + 1];
+  if (i + 2 < N) v[2] = K[i + 2];
+  return v;
+}
+
 // One workgroup builds the whole histogram from the routing ids themselves (counts only: LDS integer
 // atomics) and writes the tables.  Used where no per-tile histograms exist: the fused decode dispatch and
 // the single-launch plan.  LDS: 4E + 3 ints.  Must be called by every thread of the workgroup.
+// The launch waits for this workgroup, so the next trip's ids are requested ahead of this one's counting.
 __device__ __forceinline__ void tables_from_ids_block(const int32_t *__restrict__ K, const Dims &d, const PlanView &p,
                                                     int *lds) {
   const int E = d.E, tid = threadIdx.x, nthreads = blockDim.x;
@@ -191,6 +204,9 @@ __device__ __forceinline__ void tables_from_ids_block(const int32_t *__restrict_
   int *misc = pre + E;         // [2]
   __shared__ unsigned long long others_rows;
   const bool multi = p.source_count != nullptr;
+  const bool few = d.N <= nthreads;      // one id a thread: shorter code, 0.3 us less for a batch of one token
+  const int only = few && tid < d.N ? K[tid] : -1;
+  i32x4 next = few ? i32x4{-1, -1, -1, -1} : load_ids(K, tid, d.N);
   for (int e = tid; e < E; e += nthreads) {
     total[e] = 0;
     others[e] = 0;
@@ -198,10 +214,20 @@ __device__ __forceinline__ void tables_from_ids_block(const int32_t *__restrict_
   }
   if (tid == 0) misc[0] = 0, others_rows = 0;
   __syncthreads();
-  for (int i = tid; i < d.N; i += nthreads) {
-    const int e = K[i];
-    if (e >= 0 && e < E) atomicAdd(&total[e], 1);
+  auto count = [&](int e) {
+    if ((unsigned)e < (unsigned)E) atomicAdd(&total[e], 1);
     else if (e != -1) atomicAdd(&misc[0], 1);
+  };
+  if (few) {
+    count(only);
+  } else {
+#pragma unroll 1
+    for (int q = tid; 4 * q < d.N; q += nthreads) {
+      const i32x4 ids = next;
+      next = load_ids(K, q + nthreads, d.N);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) count(ids[n]);
+    }
   }
   if (multi) sum_columns<true>(p.source_count, d.R, E, d.me, others, pre, E, &others_rows);
   __syncthreads();

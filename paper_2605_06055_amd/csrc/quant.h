@@ -28,27 +28,27 @@ __device__ __forceinline__ float wave_max_nonneg(float v) {   // maximum over th
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), kWave - 1));
 }
 
-// Quantises the row held by the workgroup.  v[x] is the thread's x-th vector (has[x] false past the row's
-// end).  q[x] receives the 8 codes of vector x; the return value is the row's scale.
-// red[] is LDS scratch of BLOCK/64 floats; contains a barrier.
-template <int BLOCK, int V>
-__device__ __forceinline__ float quantise_row(const u32x4 (&v)[V], const bool (&has)[V], u32x2 (&q)[V], float *red) {
+// Maximum magnitude over a wave's part of a row.  v[x] is the thread's x-th vector, zero past the row's end.
+template <int V>
+__device__ __forceinline__ float wave_amax(const u32x4 (&v)[V]) {
   float amax = 0.0f;
 #pragma unroll
   for (int x = 0; x < V; ++x) {
-    if (!has[x]) continue;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       amax = fmaxf(amax, fabsf(__uint_as_float(v[x][i] << 16)));
       amax = fmaxf(amax, fabsf(__uint_as_float(v[x][i] & 0xffff0000u)));
     }
   }
-  amax = wave_max_nonneg(amax);
-  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = amax;
-  __syncthreads();
+  return wave_max_nonneg(amax);
+}
+
+// The codes of a thread's vectors, given the magnitudes of the row's waves: q[x] receives the 8 codes of vector x; the return
+// value is the row's scale.
+template <int V>
+__device__ __forceinline__ float quantise_with(const u32x4 (&v)[V], const float *amax_of_wave, int waves, u32x2 (&q)[V]) {
   float m = 0.0f;
-#pragma unroll
-  for (int w = 0; w < BLOCK / kWave; ++w) m = fmaxf(m, red[w]);
+  for (int w = 0; w < waves; ++w) m = fmaxf(m, amax_of_wave[w]);
   const float scale = m == 0.0f ? 1.0f : m / 448.0f;
   const float inv = m == 0.0f ? 1.0f : 448.0f / m;
 #pragma unroll
@@ -67,6 +67,15 @@ __device__ __forceinline__ float quantise_row(const u32x4 (&v)[V], const bool (&
     q[x] = u32x2{(unsigned)lo, (unsigned)hi};
   }
   return scale;
+}
+
+// Quantises the row held by the workgroup (see above).  red[] is LDS scratch of BLOCK/64 floats; contains a barrier.
+template <int BLOCK, int V>
+__device__ __forceinline__ float quantise_row(const u32x4 (&v)[V], u32x2 (&q)[V], float *red) {
+  const float amax = wave_amax(v);
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = amax;
+  __syncthreads();
+  return quantise_with(v, red, BLOCK / kWave, q);
 }
 
 }  // namespace moe_rbf
