@@ -191,24 +191,19 @@ __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__rest
 
 // QUANT: the workgroup holds a whole row (chunks == 1), quantises it once and fans the codes and the
 // row's scale out instead of the bf16 payload.
-// MULTI: plan->source_count is given (several source ranks); compiled apart so that the single-source
-// kernel, which is latency-bound, carries none of that code.
 // SB: slots of a token ranked together (one LDS exchange per SB slots).  The slots of a token may be split
 // over `groups` workgroups (each ranks and stores only its own slots of the chunk): more, smaller
 // workgroups spread the stores over all compute units and shorten each one's counting.
 // GROUPS is a compile-time constant so that the index arithmetic in front of the first loads stays short.
-template <int BLOCK, int V, int SB, int GROUPS, bool QUANT, bool MULTI>
+template <int BLOCK, int V, int SB, int GROUPS, bool QUANT>
 __global__ __launch_bounds__(BLOCK) void decode_dispatch_kernel(const u32x4 *__restrict__ X,
                                                                 const int32_t *__restrict__ K,
                                                                 void *__restrict__ window_any,
                                                                 float *__restrict__ window_scale, Dims d, PlanView p,
                                                                 int chunks, int per_group) {
   constexpr int groups = GROUPS;
-  extern __shared__ int lds[];                                  // tables workgroup; several-sources prefix tables
+  extern __shared__ int lds[];                                  // tables workgroup
   __shared__ int part[(BLOCK / kWave) * SB];            // per-wave packed counts of a slot batch
-  __shared__ int part_m[(BLOCK / kWave) * SB];          // per-wave rows of the other source ranks
-  __shared__ int part_v[BLOCK / kWave];                         // per-wave number of ids inside [0,E)
-  __shared__ unsigned long long part_w[BLOCK / kWave];          // per-wave rows of the other source ranks, 64-bit
   constexpr int kWaves = BLOCK / kWave;
   const int per_token = chunks * groups;
   if (blockIdx.x == 0) {                 // the tables workgroup goes first: it is the longest one
@@ -264,51 +259,6 @@ __global__ __launch_bounds__(BLOCK) void decode_dispatch_kernel(const u32x4 *__r
     scale = quantise_row<BLOCK, V>(v, q, red);
   }
 
-  // Several source ranks: rows of the other sources in front of a slot's sub-block =
-  // (their rows in the experts below e, inside the region for fixed stride) + (rows of lower ranks for e),
-  // i.e. sums over parts of the count matrix M.  A thread owns a few columns of M and keeps, per column, the
-  // sum over the other ranks and the sum over the lower ranks; a slot's two terms are then masked sums of
-  // these over the workgroup (wave reduction + the LDS exchange the id counts use anyway).
-  constexpr bool multi = MULTI;
-  constexpr int kCols = MULTI ? (MOE_MAX_EXPERTS + BLOCK - 1) / BLOCK : 1;     // columns a thread may own
-  int col_all[kCols], col_pre[kCols], col_id[kCols];
-#pragma unroll
-  for (int q2 = 0; q2 < kCols; ++q2) col_all[q2] = col_pre[q2] = 0, col_id[q2] = -1;
-  unsigned long long wave_rows = 0;                  // rows of the other sources counted by this wave's threads
-  if (multi) {
-    unsigned long long wide = 0;
-    constexpr int kRows = 16;                       // rows of M requested together (8: 7.56 us, 16: 7.37, 32: 8.25 at T = 128, 32 sources)
-    const int parts = max(1, BLOCK / d.E);          // threads per column when the matrix is narrow
-    const int part = parts > 1 ? tid / d.E : 0;
-#pragma unroll
-    for (int q2 = 0; q2 < kCols; ++q2) {
-      const int col = parts > 1 ? tid - part * d.E : tid + q2 * BLOCK;
-      const bool live = parts > 1 ? (q2 == 0 && part < parts) : col < d.E;
-      if (!live) continue;
-      col_id[q2] = col;
-      const int32_t *m = p.source_count + col;
-      int all = 0, pre = 0;
-      for (int r0 = part; r0 < d.R; r0 += parts * kRows) {
-        int mv[kRows];
-#pragma unroll
-        for (int u = 0; u < kRows; ++u) {
-          const int r = r0 + u * parts;
-          mv[u] = (r < d.R && r != d.me) ? m[(size_t)r * d.E] : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < kRows; ++u) {
-          all += mv[u];
-          wide += (unsigned)mv[u];
-          if (r0 + u * parts < d.me) pre += mv[u];
-        }
-      }
-      col_all[q2] = all;
-      col_pre[q2] = pre;
-    }
-    wave_rows = wave_sum_u64(wide);
-  }
-  bool overflow = false;                            // rows of all sources together do not fit in int32
-
   const bool fixed = d.stride > 0;
   for (int j0 = jg0; j0 < jg1; j0 += SB) {
     // lane u < SB of every wave owns slot j0+u
@@ -326,7 +276,6 @@ __global__ __launch_bounds__(BLOCK) void decode_dispatch_kernel(const u32x4 *__r
       front[u] = 0;
     }
     // wave-wide counts by ballot: they land in scalar registers, no lane reduction is needed
-    int n_valid = 0;
     for (int i0 = 0, pass = 0; i0 < d.N; i0 += BLOCK, ++pass) {
       const int i = i0 + tid;
       int x;
@@ -338,7 +287,6 @@ __global__ __launch_bounds__(BLOCK) void decode_dispatch_kernel(const u32x4 *__r
         x = i < d.N ? K[i] : -1;
       }
       const int ahead = first + j0 - i;               // slot u is behind id i  <=>  u + ahead > 0
-      if (multi && j0 == jg0) n_valid += __popcll(__ballot((unsigned)x < (unsigned)d.E));
       // ids outside [0,E) never satisfy either test: as unsigned values they are huge (or x > e)
       if (fixed) {
 #pragma unroll
@@ -352,52 +300,24 @@ __global__ __launch_bounds__(BLOCK) void decode_dispatch_kernel(const u32x4 *__r
       for (int u = 0; u < SB; ++u)
         front[u] += __popcll(__ballot(x == e[u]) & __ballot(ahead + u > 0));   // two masks, and-ed as scalars
     }
-    int mine_m = 0;                                   // lane u: this wave's rows of other sources in front of slot u
-    if (multi) {
-#pragma unroll
-      for (int u = 0; u < SB; ++u) {
-        int cu = 0;
-#pragma unroll
-        for (int q2 = 0; q2 < kCols; ++q2) {
-          cu += (unsigned)(col_id[q2] - lo[u]) < (unsigned)(e[u] - lo[u]) ? col_all[q2] : 0;
-          cu += col_id[q2] == e[u] ? col_pre[q2] : 0;
-        }
-        const int tot = __builtin_amdgcn_readlane(wave_inclusive_scan(cu), kWave - 1);
-        mine_m = lane == u ? tot : mine_m;
-      }
-    }
     if (j0 > jg0) __syncthreads();                      // the previous batch's exchange has been read
     {
       int mine = 0;                                   // lane u carries this wave's packed counts of slot u
 #pragma unroll
       for (int u = 0; u < SB; ++u) mine = lane == u ? below[u] + (front[u] << 16) : mine;
-      if (lane < SB) {
-        part[wave * SB + lane] = mine;
-        if (multi) part_m[wave * SB + lane] = mine_m;
-      }
-      if (multi && j0 == jg0 && lane == 0) part_v[wave] = n_valid, part_w[wave] = wave_rows;
+      if (lane < SB) part[wave * SB + lane] = mine;
     }
     __syncthreads();
-    if (multi && j0 == jg0) {
-      unsigned long long all_rows = 0;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) all_rows += part_w[w] + (unsigned)part_v[w];
-      overflow = all_rows >= (1ull << 31);
-    }
-    int packed = 0, ahead_m = 0;
+    int packed = 0;
     if (lane < SB) {
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) packed += part[w * SB + lane];
-      if (multi)
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) ahead_m += part_m[w * SB + lane];
     }
     int s = -1, row = -1;
     if (own && my_valid) {
       s = packed >> 16;
       row = (fixed ? (int)(my_rank * d.stride) : 0) + (packed & 0xffff) + s;
-      row += ahead_m;
-      if ((fixed && row >= (int)((my_rank + 1) * d.stride)) || overflow) row = -1;
+      if (fixed && row >= (int)((my_rank + 1) * d.stride)) row = -1;
     }
     if (own && c == 0 && wave == 0) {
       if (p.send_idx) p.send_idx[first + j0 + lane] = s;
@@ -451,6 +371,7 @@ __global__ __launch_bounds__(MOST) void decode_hist_kernel(const u32x4 *__restri
   extern __shared__ int lds[];
   __shared__ int rows[kSlots];
   __shared__ float red[QUANT ? TT * (MOST / kWave) : 1];
+  __shared__ unsigned long long all_rows;                       // of all sources
   if (blockIdx.x == 0) {                 // the tables workgroup goes first: it is the longest one
     tables_from_ids_block(K, d, p, lds);
     return;
@@ -489,10 +410,16 @@ __global__ __launch_bounds__(MOST) void decode_hist_kernel(const u32x4 *__restri
     }
   i32x4 next = load_ids(K, tid, d.N);
   int my_e = lane < min(kSlots, slots) ? K[first + lane] : -1;
+  SourceSums sums;
+  if (MULTI) sums.request(p.source_count, d);
 
   int *hist = lds;                       // [E]
-  for (int e = tid; e < d.E; e += block) hist[e] = 0;
+  int *pre = hist + d.E;                 // [E]  several source ranks only: branches of the ranks below this one
+  int *post = pre + d.E;                 // [E]  ... above this one
+  for (int e = tid; e < (MULTI ? 3 : 1) * d.E; e += block) hist[e] = 0;
+  if (MULTI && tid == 0) all_rows = 0;
   __syncthreads();
+  int valid = 0;
 #pragma unroll 1
   for (int q = tid; 4 * q < d.N; q += block) {
     const i32x4 ids = next;
@@ -500,7 +427,14 @@ __global__ __launch_bounds__(MOST) void decode_hist_kernel(const u32x4 *__restri
     const int ahead = first - 4 * q;                            // id n of the piece is in front <=> n < ahead
 #pragma unroll
     for (int n = 0; n < 4; ++n)
-      if ((unsigned)ids[n] < (unsigned)d.E) atomicAdd(&hist[ids[n]], n < ahead ? 0x10001 : 1);
+      if ((unsigned)ids[n] < (unsigned)d.E) {
+        atomicAdd(&hist[ids[n]], n < ahead ? 0x10001 : 1);
+        if (MULTI) ++valid;
+      }
+  }
+  if (MULTI) {
+    const unsigned long long rows_of_wave = sums.add(p.source_count, d, pre, post, valid);
+    if (lane == 0) atomicAdd(&all_rows, rows_of_wave);
   }
   if (QUANT) {
 #pragma unroll
@@ -518,6 +452,7 @@ __global__ __launch_bounds__(MOST) void decode_hist_kernel(const u32x4 *__restri
   }
 
   const bool fixed = d.stride > 0;
+  const bool overflow = MULTI && all_rows >= (1ull << 31);      // rows are int32: if they do not fit, nothing is placed
   for (int j0 = 0; j0 < slots; j0 += kSlots) {
     const int nb = min(kSlots, slots - j0);
     if (j0 > 0) {                        // the previous slots are now in front too
@@ -536,13 +471,13 @@ __global__ __launch_bounds__(MOST) void decode_hist_kernel(const u32x4 *__restri
 #pragma unroll
           for (int n = 0; n < 4; ++n) {
             const int x = x0 + n * kWave + lane;
-            below += x >= lo && x < e ? hist[x] & 0xffff : 0;
+            if (x >= lo && x < e) below += (hist[x] & 0xffff) + (MULTI ? pre[x] + post[x] : 0);
           }
         }
         below = __builtin_amdgcn_readlane(wave_inclusive_scan(below), kWave - 1);
         s = (hist[e] >> 16) + __popcll(__ballot(my_e == e) & ((1ull << u) - 1ull));
-        row = (fixed ? (int)(rank * d.stride) : 0) + below + s;
-        if (fixed && row >= (int)((rank + 1) * d.stride)) row = -1;
+        row = (fixed ? (int)(rank * d.stride) : 0) + below + (MULTI ? pre[e] : 0) + s;
+        if ((fixed && row >= (int)((rank + 1) * d.stride)) || overflow) row = -1;
       }
       if (lane == 0) {
         rows[u] = row;
@@ -762,7 +697,9 @@ hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void
 //   k = 5, 4, 3, 2, 1: H = 4096, T = 256 5.2 / 4.8, 4.7 / 4.5, 4.4 / 4.3, 3.9 / 4.0, 3.7 / 3.7; T = 1024 16.8 / 13.9, 14.6 / 9.7,
 //          12.3 / 8.0, 10.2 / 6.1, 7.7 / 5.3; H = 1024, k = 1, T = 5000 51.5 / 8.0;
 //   quantised: k = 8: H = 7168, T = 64 3.7 / 4.2, 128 4.9 / 4.8, 512 12.6 / 9.3; k = 1 to 5, H = 4096, T = 64 4.05 to 4.4 / 3.75 to 4.2.
-static bool decode_by_hist(const Dims &d, bool quant) {
+// With several source ranks always the histogram, to which the other ranks' rows are added.
+static bool decode_by_hist(const Dims &d, const PlanView &p, bool quant) {
+  if (p.source_count) return true;
   if (d.k < 6) return quant || d.N > 600;
   if (quant) return d.N > 1024;
   return d.N > (d.H16 > 512 && d.H16 <= 832 ? 2304 : 1408);
@@ -776,26 +713,33 @@ static hipError_t launch_decode_hist_shape(const Dims &d, const void *x, const i
   const int chunks = (d.H16 + kMost * V - 1) / (kMost * V);
   const int width = ((d.H16 + chunks - 1) / chunks + kLine - 1) / kLine * kLine;
   // (7 waves: 8.  H = 7168, T = 512 14.3 / 13.6 us; but 5 and 6 waves stay: H = 5120, T = 400 9.2 / 10.9)
-  int threads = std::max(256, ((width + V - 1) / V + kWave - 1) / kWave * kWave);
+  int threads = std::max(p.source_count ? 512 : 256, ((width + V - 1) / V + kWave - 1) / kWave * kWave);
   if (threads == 7 * kWave) threads = 8 * kWave;
   const int per_group = (d.k + G - 1) / G;
   const size_t lds = (size_t)(4 * d.E + 1 + 2) * sizeof(int);
   const dim3 grid((unsigned)((d.T + TT - 1) / TT) * (unsigned)(chunks * G) + 1u);
-  return launch(decode_hist_kernel<kMost, V, TT, G, QUANT, false>, grid, dim3((unsigned)threads), lds, s, (const u32x4 *)x, K,
-                window, window_scale, d, p, chunks, width, per_group);
+  auto go = [&](auto kernel) {
+    return launch(kernel, grid, dim3((unsigned)threads), lds, s, (const u32x4 *)x, K, window, window_scale, d, p, chunks, width,
+                  per_group);
+  };
+  return p.source_count ? go(decode_hist_kernel<kMost, V, TT, G, QUANT, true>)
+                        : go(decode_hist_kernel<kMost, V, TT, G, QUANT, false>);
 }
 
 // How many branches a workgroup takes.  Degrees of 6 and more: a token's slots, in one workgroup or two.  More workgroups spread
 // the stores, fewer repeat the counting less: us per dispatch, two / one, k = 8: H = 4096 (8 waves): T = 256 5.5 / 5.6, 320 6.5 / 6.4, 512
 // 9.7 / 9.0; H = 2048 (4 waves): T = 512 6.5 / 6.6; H = 5120 (5 waves, 2 vectors a lane): T = 512 11.1 / 11.6; H = 7168: T = 384
-// 12.0 / 11.1, 512 13.7 / 14.3; quantised H = 7168: T = 256 5.8 / 5.9, 384 9.1 / 7.4, 512 10.1 / 9.3.
+// 12.0 / 11.1, 512 13.7 / 14.3; quantised H = 7168: T = 256 5.8 / 5.9, 384 9.1 / 7.4, 512 10.1 / 9.3.  With several sources every
+// workgroup also adds up the count matrix, so one workgroup pays earlier: 32 sources, H = 7168: T = 64 5.3 / 5.65, 128 6.7 / 6.4, 512
+// 16.1 / 14.0; k = 10, T = 300 10.7 / 10.8.
 // Smaller degrees: whole tokens, up to 8 branches, as long as about 384 workgroups remain (k = 4, H = 4096, T = 800: two tokens 8.0,
 // one 10.1; quantised T = 512: 5.5 / 5.1, T = 800 7.2 / 8.9).
 template <int V, bool QUANT>
 static hipError_t launch_decode_hist(const Dims &d, const void *x, const int32_t *K, const PlanView &p, void *window,
                                      float *window_scale, hipStream_t s) {
   if (d.k >= 6) {
-    const bool whole = d.H16 > 256 && (QUANT ? d.N > 2560 : d.H16 <= 512 && d.N > 2304);
+    const bool whole = p.source_count ? d.N >= 1024 && d.k <= 8
+                                      : d.H16 > 256 && (QUANT ? d.N > 2560 : d.H16 <= 512 && d.N > 2304);
     return whole ? launch_decode_hist_shape<V, 1, 1, QUANT>(d, x, K, p, window, window_scale, s)
                  : launch_decode_hist_shape<V, 1, 2, QUANT>(d, x, K, p, window, window_scale, s);
   }
@@ -816,16 +760,13 @@ static hipError_t launch_decode_dispatch_shape(const Dims &d, const void *x, con
   const int per_group = ((d.k + G - 1) / G + SB - 1) / SB * SB;
   const size_t lds = (size_t)(4 * d.E + 1 + 2) * sizeof(int);
   const dim3 grid((unsigned)d.T * (unsigned)(chunks * G) + 1u);
-  if (p.source_count)
-    return launch(decode_dispatch_kernel<B, V, SB, G, false, true>, grid, dim3(B), lds, s, (const u32x4 *)x, K, window,
-                  (float *)nullptr, d, p, chunks, per_group);
-  return launch(decode_dispatch_kernel<B, V, SB, G, false, false>, grid, dim3(B), lds, s, (const u32x4 *)x, K, window,
+  return launch(decode_dispatch_kernel<B, V, SB, G, false>, grid, dim3(B), lds, s, (const u32x4 *)x, K, window,
                 (float *)nullptr, d, p, chunks, per_group);
 }
 
 hipError_t launch_decode_dispatch(const Dims &d, const void *x, const int32_t *K, const PlanView &p, void *window,
                                   hipStream_t s) {
-  if (!p.source_count && decode_by_hist(d, false))
+  if (decode_by_hist(d, p, false))
     return d.H16 <= 512 ? launch_decode_hist<1, false>(d, x, K, p, window, nullptr, s)
                         : launch_decode_hist<2, false>(d, x, K, p, window, nullptr, s);
   // With a routing degree of at least 6 the slots of a token are split over 4 workgroups of 8 waves (2 slots
@@ -835,10 +776,8 @@ hipError_t launch_decode_dispatch(const Dims &d, const void *x, const int32_t *K
   //   H = 7168: T = 16: 3.9 / 3.5 / 3.5, T = 64: 4.2 / 4.0 / 4.1, T = 128: 5.4 / 4.9 / 4.8, T = 144: 6.0 / 5.5 / 5.2,
   //             T = 256: 8.8 / 8.0 / 7.7, T = 512: 16.3 / 14.6 / 14.5;
   //   H = 4096: T = 128: 4.7 / 4.2 / 4.2, T = 256: 6.3 / 5.7 / 6.2, T = 512: 11.0 / 11.2 / 12.4.
-  // With several source ranks every workgroup also sums the columns of the count matrix, so two groups are the
-  // better trade there (T = 128, 32 sources: 8.0 / 7.6 / 7.8 us with one / two / four groups).
   if (d.k >= 6) {
-    if (d.N <= 1536 && !p.source_count) return launch_decode_dispatch_shape<512, 2, 2, 4>(d, x, K, p, window, s);
+    if (d.N <= 1536) return launch_decode_dispatch_shape<512, 2, 2, 4>(d, x, K, p, window, s);
     return launch_decode_dispatch_shape<512, 2, 4, 2>(d, x, K, p, window, s);
   }
   // Few slots per token: one workgroup per token and chunk.  Every workgroup of a token repeats the
@@ -880,10 +819,7 @@ static hipError_t launch_decode_quant_shape(const Dims &d, const void *x, const 
   const size_t lds = (size_t)(4 * d.E + 1 + 2) * sizeof(int);
   const int per_group = ((d.k + G - 1) / G + SB - 1) / SB * SB;
   const dim3 grid((unsigned)d.T * (unsigned)G + 1u);
-  if (p.source_count)
-    return launch(decode_dispatch_kernel<B, V, SB, G, true, true>, grid, dim3(B), lds, s, (const u32x4 *)x, K, window_q,
-                  window_scale, d, p, 1, per_group);
-  return launch(decode_dispatch_kernel<B, V, SB, G, true, false>, grid, dim3(B), lds, s, (const u32x4 *)x, K, window_q,
+  return launch(decode_dispatch_kernel<B, V, SB, G, true>, grid, dim3(B), lds, s, (const u32x4 *)x, K, window_q,
                 window_scale, d, p, 1, per_group);
 }
 
@@ -894,7 +830,7 @@ template <int B, int V>
 static hipError_t launch_decode_quant_bv(const Dims &d, const void *x, const int32_t *K, const PlanView &p,
                                          void *window_q, float *window_scale, hipStream_t s) {
   if (d.k >= 6) {
-    if (d.N <= 1536 && !p.source_count)
+    if (d.N <= 1536)
       return launch_decode_quant_shape<B, V, 2, 4>(d, x, K, p, window_q, window_scale, s);
     return launch_decode_quant_shape<B, V, 4, 2>(d, x, K, p, window_q, window_scale, s);
   }
@@ -903,7 +839,7 @@ static hipError_t launch_decode_quant_bv(const Dims &d, const void *x, const int
 
 hipError_t launch_decode_dispatch_quant(const Dims &d, const void *x, const int32_t *K, const PlanView &p,
                                         void *window_q, float *window_scale, hipStream_t s) {
-  if (!p.source_count && decode_by_hist(d, true)) {
+  if (decode_by_hist(d, p, true)) {
     if (d.H16 <= 512) return launch_decode_hist<1, true>(d, x, K, p, window_q, window_scale, s);
     if (d.H16 <= 2048) return launch_decode_hist<2, true>(d, x, K, p, window_q, window_scale, s);
     return launch_decode_hist<4, true>(d, x, K, p, window_q, window_scale, s);

@@ -86,9 +86,9 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
   int *total = lds;                    // [E+1]  c^exp, then the number of invalid ids
   int *g = total + E + 1;              // [E+1]  exclusive scan of the block sizes over all experts
   int *before = g + E + 1;             // [E]    branches of expert e in earlier tiles
-  int *others = before + E;            // [E]    branches of the other source ranks (several sources only)
-  int *pre = others + E;               // [E]    branches of the source ranks below this one
-  int *wcur = pre + E;                 // [waves][E] segment histograms, then running s per wave segment
+  int *pre = before + E;               // [E]    branches of the source ranks below this one (several sources only)
+  int *post = pre + E;                 // [E]    ... above this one
+  int *wcur = post + E;                // [waves][E] segment histograms, then running s per wave segment
   int *misc = wcur + kPlanWaves * E;   // [2]    scratch
   // dispatch order list: counts inside this tile's sorted stretch (a run of d.order_tiles tiles)
   int *st_total = FUSED ? total : misc + 2;             // [E+1]  branches of expert e in the whole stretch
@@ -123,15 +123,17 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
       tables_from_ids_block(K, d, p, lds);
       return;
     }
+    SourceSums sums;
+    if (multi) sums.request(p.source_count, d);
     for (int e = tid; e <= E; e += kPlanBlock) total[e] = 0;
-    for (int e = tid; e < 2 * E; e += kPlanBlock) others[e] = 0;     // others and pre
+    for (int e = tid; e < 2 * E; e += kPlanBlock) pre[e] = 0;        // pre and post
     __syncthreads();
-    sum_columns<false>(tile_hist, tiles, E + 1, 0, total, nullptr, 0);
-    if (multi) sum_columns<true>(p.source_count, d.R, E, d.me, others, pre, E, &others_rows);
+    sum_columns(tile_hist, tiles, E + 1, 0, total, nullptr, 0);
+    if (multi) add_sources(sums, p.source_count, d, pre, post, &others_rows);
     __syncthreads();
-    if (wave == 0) wave_exclusive_scan_lds(total, g, E, -1, multi ? others : nullptr);
+    if (wave == 0) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
     __syncthreads();
-    write_plan_tables(total, multi ? others : nullptr, multi ? pre : nullptr, g, d, p, total[E], misc,
+    write_plan_tables(total, multi ? pre : nullptr, g, d, p, total[E], misc,
                       multi && rows_overflow(others_rows, g[E]));
     return;
   }
@@ -158,8 +160,10 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
     }
   }
 
+  SourceSums sums;
+  if (multi) sums.request(p.source_count, d);
   for (int e = tid; e <= E; e += kPlanBlock) total[e] = 0;
-  for (int e = tid; e < 3 * E; e += kPlanBlock) before[e] = 0;       // before, others and pre
+  for (int e = tid; e < 3 * E; e += kPlanBlock) before[e] = 0;       // before, pre and post
   for (int x = tid; x < kPlanWaves * E; x += kPlanBlock) wcur[x] = 0;
   if (!FUSED && ordered)
     for (int e = tid; e < 2 * E + 1; e += kPlanBlock) st_total[e] = 0;                // st_total and st_before
@@ -183,9 +187,9 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
     if (ordered)
       sum_columns_stretch(tile_hist, tiles, E + 1, me, st0, st1, total, before, st_total, st_before, E);
     else
-      sum_columns<false>(tile_hist, tiles, E + 1, me, total, before, E);
+      sum_columns(tile_hist, tiles, E + 1, me, total, before, E);
   }
-  if (multi) sum_columns<true>(p.source_count, d.R, E, d.me, others, pre, E, &others_rows);
+  if (multi) add_sources(sums, p.source_count, d, pre, post, &others_rows);
   // histogram of each wave's segment (counts only: atomics are order-free here)
   for (int rd = 0; rd < rounds; ++rd) {
     const long long i = seg_start + (long long)rd * kWave + lane;
@@ -193,7 +197,7 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
     if (e >= 0 && e < E) atomicAdd(&wcur[wave * E + e], 1);
   }
   __syncthreads();
-  if (!FUSED && wave == 0) wave_exclusive_scan_lds(total, g, E, -1, multi ? others : nullptr);
+  if (!FUSED && wave == 0) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
   if (!FUSED && ordered && wave == 1) wave_exclusive_scan_lds(st_total, st_excl, E);
   // exclusive prefix of the segment counts over the 16 waves, seeded with the count in earlier tiles:
   // element (e, w) sits in lane w of a 16-lane row, so one DPP row scan does it
@@ -209,7 +213,7 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
   }
   __syncthreads();
   if (FUSED) {
-    if (wave == 0) wave_exclusive_scan_lds(total, g, E, -1, multi ? others : nullptr);
+    if (wave == 0) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
     if (ordered && wave == 1) wave_exclusive_scan_lds(st_total, st_excl, E);
     __syncthreads();
   }
@@ -260,23 +264,25 @@ __global__ __launch_bounds__(kPlanBlock) void plan_empty_kernel(Dims d, PlanView
   const int E = d.E;
   int *total = lds;                    // [E]   zeros
   int *g = total + E;                  // [E+1]
-  int *others = g + E + 1;             // [E]
-  int *pre = others + E;               // [E]
-  int *misc = pre + E;                 // [2]
+  int *pre = g + E + 1;                // [E]
+  int *post = pre + E;                 // [E]
+  int *misc = post + E;                // [2]
   __shared__ unsigned long long others_rows;
   const bool multi = p.source_count != nullptr;
+  SourceSums sums;
+  if (multi) sums.request(p.source_count, d);
   for (int e = threadIdx.x; e < E; e += kPlanBlock) {
     total[e] = 0;
-    others[e] = 0;
     pre[e] = 0;
+    post[e] = 0;
   }
   if (threadIdx.x == 0) others_rows = 0;
   __syncthreads();
-  if (multi) sum_columns<true>(p.source_count, d.R, E, d.me, others, pre, E, &others_rows);
+  if (multi) add_sources(sums, p.source_count, d, pre, post, &others_rows);
   __syncthreads();
-  if (threadIdx.x < kWave) wave_exclusive_scan_lds(total, g, E, -1, multi ? others : nullptr);
+  if (threadIdx.x < kWave) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
   __syncthreads();
-  write_plan_tables(total, multi ? others : nullptr, multi ? pre : nullptr, g, d, p, 0, misc,
+  write_plan_tables(total, multi ? pre : nullptr, g, d, p, 0, misc,
                     multi && rows_overflow(others_rows, g[E]));
 }
 

@@ -5,11 +5,11 @@
 // each other; inside an expert's block the sub-blocks of the source ranks follow each other in rank
 // order.  With
 //   own[e]    = branches this rank sends to expert e                     (c^exp)
-//   others[e] = branches all OTHER source ranks send to e                (column sum of M without row me)
 //   pre[e]    = branches the source ranks BELOW this one send to e       (column sum of M over rows < me)
-//   g         = exclusive scan over e of own + others
+//   post[e]   = branches the source ranks ABOVE this one send to e       (column sum of M over rows > me)
+//   g         = exclusive scan over e of own + pre + post
 // the block of expert e starts at  B[e] = region_start(d) + g[e] - g[d*E_r]  and this rank's sub-block at
-// o_{e,me} = B[e] + pre[e].  With one source rank others = pre = 0.
+// o_{e,me} = B[e] + pre[e].  With one source rank pre = post = 0.
 //
 // Row numbers are int32.  With several sources the row total is device data (the sum of M); it is also
 // accumulated in 64 bits, and when it reaches 2^31 no branch is placed and status[2] reports it.
@@ -35,21 +35,17 @@ __device__ __forceinline__ int region_row_limit(int e, const Dims &d) {
 
 // Sums columns of a row-major int matrix src[rows][cols] with all threads of the workgroup: the columns
 // are split over `parts` groups of threads that take every parts-th row; partial sums meet in LDS with
-// integer atomics (counts: order-free).  all_sum[col] += sum over rows (without row `me` if SKIP_ME);
+// integer atomics (counts: order-free).  all_sum[col] += sum over rows;
 // before_sum[col] += sum over rows < me (if before_sum is given; only columns < before_cols).
-// grand (optional, LDS, zeroed by the caller) += the sum of everything counted in all_sum, in 64 bits.
 // The targets must hold their starting values before the call; the caller synchronises afterwards.
-template <bool SKIP_ME>
 __device__ __forceinline__ void sum_columns(const int32_t *__restrict__ src, int rows, int cols, int me,
-                                            int *all_sum, int *before_sum, int before_cols,
-                                            unsigned long long *grand = nullptr) {
+                                            int *all_sum, int *before_sum, int before_cols) {
   const int nthreads = blockDim.x;
   const int parts = max(1, nthreads / cols);
   const int tid = threadIdx.x;
-  const bool live = parts == 1 || tid < parts * cols;      // every thread stays for the wave-wide sum below
+  if (parts > 1 && tid >= parts * cols) return;
   const int part = parts == 1 ? 0 : tid / cols;
-  unsigned long long wide = 0;
-  for (int col = parts == 1 ? tid : tid - part * cols; live && col < cols; col += nthreads) {
+  for (int col = parts == 1 ? tid : tid - part * cols; col < cols; col += nthreads) {
     int all = 0, bef = 0;
     const int32_t *p = src + col;
     for (int r0 = part; r0 < rows; r0 += parts * 16) {
@@ -57,22 +53,112 @@ __device__ __forceinline__ void sum_columns(const int32_t *__restrict__ src, int
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const int r = r0 + u * parts;
-        v[u] = (r < rows && !(SKIP_ME && r == me)) ? p[(size_t)r * cols] : 0;
+        v[u] = r < rows ? p[(size_t)r * cols] : 0;
       }
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         all += v[u];
-        wide += (unsigned)v[u];
         if (r0 + u * parts < me) bef += v[u];
       }
     }
     if (all) atomicAdd(&all_sum[col], all);
     if (before_sum && bef && col < before_cols) atomicAdd(&before_sum[col], bef);
   }
-  if (grand) {                                             // one 64-bit LDS atomic per wave
-    const unsigned long long wave_rows = wave_sum_u64(wide);
-    if (lane_id() == 0 && wave_rows) atomicAdd(grand, wave_rows);
+}
+
+// a / b for 0 <= a < 2^20, 0 < b <= 1024 and quotients below 1024 or so: the error of the reciprocal stays below the 0.5 / b that is
+// between the exact value and the next integer.
+__device__ __forceinline__ int small_div(int a, int b) {
+  return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
+}
+
+// Rows of the other source ranks: column sums of M (R x E) below and above this rank's row, added up in LDS by all threads of a
+// workgroup of at least 512.  What bounds it is the round trip, and the instructions that every workgroup repeats: a thread takes
+// four columns (16-byte loads, all of them in flight for 32 ranks and 256 experts) over a run of consecutive ranks on one side of
+// this one, so that it adds to one array only.  (Where rows are not whole pieces of 16 bytes: one column at a time.)
+// us per decode dispatch, 32 sources, E = 256, k = 8, H = 7168, with a column per thread, two sums and a 64-bit one for each element and
+// reductions over the wave for each slot / now: T = 1 5.3 / 4.7, 64 6.0 / 5.3, 128 7.35 / 6.4, 512 18.2 / 14.0; plan of 5870 branches,
+// E = 64 8.15 / 6.8, of 32 768 13.0 / 11.7.
+struct SourceSums {
+  static constexpr int kRows = 4;        // rows requested together
+  static constexpr int kShort = 128;     // rows of a run whose total needs 32 bits only, if its elements are below 2^15
+  u32x4 v[kRows];
+  int quad, first, end;                  // four columns, and the run of ranks
+  bool below;
+
+  __device__ __forceinline__ void load(const int32_t *__restrict__ M, const Dims &d, int r) {
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+      v[u] = r + u < end ? ((const u32x4 *)(M + (size_t)(r + u) * (size_t)d.E))[quad] : u32x4{0u, 0u, 0u, 0u};
   }
+  __device__ __forceinline__ void request(const int32_t *__restrict__ M, const Dims &d) {
+    first = end = 0;
+    if (d.E % 4 != 0) return;
+    const int quads = d.E >> 2, parts = small_div((int)blockDim.x, quads);     // E <= 1024: at least two parts
+    const int part = small_div((int)threadIdx.x, quads);
+    quad = (int)threadIdx.x - part * quads;
+    const int lower = d.me, upper = d.R - 1 - d.me;            // ranks on the two sides
+    const int parts_below = lower == 0 ? 0 : upper == 0 ? parts : min(max(small_div(parts * lower, d.R - 1), 1), parts - 1);
+    below = part < parts_below;
+    const int n = below ? lower : upper, share = below ? parts_below : parts - parts_below, start = below ? 0 : d.me + 1;
+    const int each = n > 0 ? small_div(n + share - 1, share) : 0;
+    first = start + (below ? part : part - parts_below) * each;
+    end = part < parts ? min(start + n, first + each) : first;
+    load(M, d, first);
+  }
+  // pre[e], post[e] += the sums; they start at zero.  Returns the wave's total plus that of `more`, exact below 2^31 (and at
+  // least 2^31 otherwise).
+  __device__ __forceinline__ unsigned long long add(const int32_t *__restrict__ M, const Dims &d, int *pre, int *post, int more) {
+    u32x4 sum = {0u, 0u, 0u, 0u};
+    unsigned any = d.E % 4 != 0 || end - first > kShort ? ~0u : 0u;
+    for (int r = first; r < end; r += kRows) {
+      if (r > first) load(M, d, r);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum[i] += v[0][i] + v[1][i] + v[2][i] + v[3][i];
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) any |= v[u][0] | v[u][1] | v[u][2] | v[u][3];
+    }
+    if (first < end) {
+      int *to = (below ? pre : post) + 4 * quad;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) atomicAdd(to + i, (int)sum[i]);
+    }
+    if (__ballot(any >= 1u << 15) == 0)
+      return (unsigned)__builtin_amdgcn_readlane(
+          wave_inclusive_scan((int)(sum[0] + sum[1] + sum[2] + sum[3]) + more), kWave - 1);
+    return add_wide(M, d, pre, post, more);
+  }
+  // The total in 64 bits, from memory again; where rows are not whole pieces of 16 bytes, the sums too.
+  __device__ __forceinline__ unsigned long long add_wide(const int32_t *__restrict__ M, const Dims &d, int *pre, int *post,
+                                                         int more) {
+    unsigned wide = (unsigned)more;
+    if (d.E % 4 != 0) {
+      for (int col = (int)threadIdx.x; col < d.E; col += (int)blockDim.x) {
+        int low = 0, high = 0;
+#pragma unroll 8
+        for (int r = 0; r < d.R; ++r) {
+          const int n = r != d.me ? M[(size_t)r * d.E + col] : 0;
+          (r < d.me ? low : high) += n;
+          wide = __builtin_elementwise_add_sat(wide, (unsigned)n);
+        }
+        pre[col] = low, post[col] = high;
+      }
+    } else {
+      for (int r = first; r < end; ++r) {
+        const u32x4 n = ((const u32x4 *)(M + (size_t)r * (size_t)d.E))[quad];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wide = __builtin_elementwise_add_sat(wide, n[i]);
+      }
+    }
+    return wave_sum_u64(wide);
+  }
+};
+
+// The sums of a requested SourceSums; rows (LDS, zeroed by the caller) += the total in 64 bits.
+__device__ __forceinline__ void add_sources(SourceSums &sums, const int32_t *__restrict__ M, const Dims &d, int *pre, int *post,
+                                            unsigned long long *rows) {
+  const unsigned long long wave_rows = sums.add(M, d, pre, post, 0);
+  if (lane_id() == 0 && wave_rows) atomicAdd(rows, wave_rows);
 }
 
 // The tile histograms summed once for a workgroup that also emits the dispatch order list: besides the sums
@@ -116,7 +202,7 @@ __device__ __forceinline__ void sum_columns_stretch(const int32_t *__restrict__ 
 }
 
 // Do the rows of all sources together reach 2^31?  others_rows: 64-bit sum of the other sources' counts;
-// all_rows_low: the int32 sum (possibly wrapped) of own + others; this rank's own count is below 2^31, so
+// all_rows_low: the int32 sum (possibly wrapped) of own and others; this rank's own count is below 2^31, so
 // it is the difference of the two low words.
 __device__ __forceinline__ bool rows_overflow(unsigned long long others_rows, int all_rows_low) {
   const unsigned own = (unsigned)all_rows_low - (unsigned)others_rows;
@@ -124,12 +210,12 @@ __device__ __forceinline__ bool rows_overflow(unsigned long long others_rows, in
 }
 
 // One workgroup writes expert_count, rank_count, expert_offset, region_base, recv_count, recv_offset and
-// status from LDS copies of own[0..E), others/pre (nullptr with a single
+// status from LDS copies of own[0..E), pre (nullptr with a single
 // source rank) and g[0..E].  Must be called by every thread of the workgroup.
 // Branches dropped for capacity: this rank's sub-block of expert e covers rows [o, o + own); the part at
 // or past the region's end is dropped.  overflow: the row total does not fit in int32 (the offset tables
 // are then meaningless and status[2] says so).
-__device__ __forceinline__ void write_plan_tables(const int *own, const int *others, const int *pre, const int *g,
+__device__ __forceinline__ void write_plan_tables(const int *own, const int *pre, const int *g,
                                                   const Dims &d, const PlanView &p, int n_invalid, int *lds_counter,
                                                   bool overflow = false) {
   const int nthreads = blockDim.x;
@@ -141,7 +227,7 @@ __device__ __forceinline__ void write_plan_tables(const int *own, const int *oth
     const int c = own[e];
     const int block = expert_first_row(g, e, d);
     const int o = block + (pre ? pre[e] : 0);
-    const int all = c + (others ? others[e] : 0);
+    const int all = g[e + 1] - g[e];                                    // own and the other sources'
     p.expert_count[e] = c;
     p.expert_offset[e] = o;
     if (p.recv_count) p.recv_count[e] = all;
@@ -155,13 +241,13 @@ __device__ __forceinline__ void write_plan_tables(const int *own, const int *oth
   }
   for (int r = threadIdx.x; r < d.R; r += nthreads) {
     p.region_base[r] = fixed ? (int)(r * d.stride) : g[r * d.Er];
-    if (!others) p.rank_count[r] = g[(r + 1) * d.Er] - g[r * d.Er];     // own counts are all there is in g
+    if (!pre) p.rank_count[r] = g[(r + 1) * d.Er] - g[r * d.Er];     // own counts are all there is in g
   }
   // With several sources g also counts the other ranks' rows, so the own counts of a rank's experts are summed here,
   // one wave per rank.  (One thread per rank was a chain of E_r dependent LDS reads that the whole launch waited
   // for: with R = 1 the decode dispatch of 222 tokens of H = 2048 took 13.1 us at E = 256 and the plan of 24 576 branches
   // 28.8 us at E = 512, against 5.5 and 12.5 us now, in replayed graphs.)
-  if (others) {
+  if (pre) {
     for (int r = threadIdx.x / kWave; r < d.R; r += nthreads / kWave) {
       int c = 0;
       for (int e = r * d.Er + lane_id(); e < (r + 1) * d.Er; e += kWave) c += own[e];
@@ -199,18 +285,20 @@ __device__ __forceinline__ void tables_from_ids_block(const int32_t *__restrict_
   const int E = d.E, tid = threadIdx.x, nthreads = blockDim.x;
   int *total = lds;            // [E]
   int *g = total + E;          // [E+1]
-  int *others = g + E + 1;     // [E]  several source ranks only
-  int *pre = others + E;       // [E]
-  int *misc = pre + E;         // [2]
+  int *pre = g + E + 1;        // [E]  several source ranks only
+  int *post = pre + E;         // [E]
+  int *misc = post + E;        // [2]
   __shared__ unsigned long long others_rows;
   const bool multi = p.source_count != nullptr;
   const bool few = d.N <= nthreads;      // one id a thread: shorter code, 0.3 us less for a batch of one token
   const int only = few && tid < d.N ? K[tid] : -1;
   i32x4 next = few ? i32x4{-1, -1, -1, -1} : load_ids(K, tid, d.N);
+  SourceSums sums;
+  if (multi) sums.request(p.source_count, d);
   for (int e = tid; e < E; e += nthreads) {
     total[e] = 0;
-    others[e] = 0;
     pre[e] = 0;
+    post[e] = 0;
   }
   if (tid == 0) misc[0] = 0, others_rows = 0;
   __syncthreads();
@@ -229,12 +317,11 @@ __device__ __forceinline__ void tables_from_ids_block(const int32_t *__restrict_
       for (int n = 0; n < 4; ++n) count(ids[n]);
     }
   }
-  if (multi) sum_columns<true>(p.source_count, d.R, E, d.me, others, pre, E, &others_rows);
+  if (multi) add_sources(sums, p.source_count, d, pre, post, &others_rows);
   __syncthreads();
-  if (tid < kWave) wave_exclusive_scan_lds(total, g, E, -1, multi ? others : nullptr);
+  if (tid < kWave) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
   __syncthreads();
-  write_plan_tables(total, multi ? others : nullptr, multi ? pre : nullptr, g, d, p, misc[0], misc + 1,
-                    multi && rows_overflow(others_rows, g[E]));
+  write_plan_tables(total, multi ? pre : nullptr, g, d, p, misc[0], misc + 1, multi && rows_overflow(others_rows, g[E]));
 }
 
 }  // namespace moe_rbf

@@ -60,3 +60,32 @@ def test_decode_dispatch(moe, T, H, k, E, R, stride, quant):
     for got, exp in ((p.expert_count, ref.c_exp), (p.rank_count, ref.c_rank), (p.expert_offset, ref.expert_offset),
                      (p.region_base, ref.region_base), (p.status[:3], ref.status)):
         assert np.array_equal(to_host(got), exp)
+
+
+@pytest.mark.parametrize("T,k,E,R,me", [(3, 8, 256, 32, 0), (3, 8, 256, 32, 31), (130, 8, 256, 32, 16), (200, 8, 512, 256, 100),
+                                        (150, 4, 6, 3, 1), (40, 2, 1024, 2, 1), (64, 6, 12, 12, 5), (64, 6, 1024, 1024, 1023),
+                                        (601, 1, 4, 1, 0), (700, 3, 20, 5, 2), (100, 17, 36, 9, 8)])
+@pytest.mark.parametrize("most", [50, 40000])                 # elements of the count matrix (40000: its total is taken in 64 bits)
+@pytest.mark.parametrize("schedule", ["decode", "prefill"])
+def test_several_sources(moe, T, k, E, R, me, most, schedule):
+    from paper_2605_06055_amd.layer import MoeLayer, to_device, to_host
+    rng = np.random.default_rng(T + E + R + me)
+    K = wl.random_routing(rng, T, k, E, p_masked=0.05, p_invalid=0.02)
+    M = rng.integers(0, most, size=(R, E)).astype(np.int32)
+    if most > 50:
+        M[rng.random((R, E)) > 20 / (R * E)] = 0               # few of them: the window stays small
+    ref = oracle.plan_multi(K, M, me, E, R)
+    print(f"[sources] T={T} k={k} E={E} R={R} me={me} most={most} rows={ref.window_rows} {schedule}", flush=True)
+    X = rng.integers(0, 1 << 15, size=(T, 8), dtype=np.uint16)
+    layer = MoeLayer(T, 8, k, E, R, schedule=moe.MOE_SCHEDULE_DECODE if schedule == "decode" else moe.MOE_SCHEDULE_PREFILL,
+                     rank_id=me, source_count=to_device(M), window_rows=max(1, ref.window_rows))
+    layer.window.view(torch.int16).fill_(0x7B7B)
+    layer.dispatch(to_device(X), to_device(K))
+    p, N = layer.plan, T * k
+    assert np.array_equal(to_host(p.row_map)[:N].reshape(T, k), ref.row_map)
+    assert np.array_equal(to_host(p.send_idx)[:N].reshape(T, k), ref.s)
+    for got, exp in ((p.expert_count, ref.c_exp), (p.rank_count, ref.c_rank), (p.expert_offset, ref.expert_offset),
+                     (p.recv_count, ref.recv_count), (p.recv_offset, ref.recv_offset), (p.status[:3], ref.status)):
+        assert np.array_equal(to_host(got), exp)
+    want = oracle.dispatch(X, ref.row_map, max(1, ref.window_rows), fill=np.uint16(0x7B7B))
+    assert to_host(layer.window).tobytes() == want.tobytes()
