@@ -1,4 +1,4 @@
-"""ctypes binding of libmoe_rbf.so (argument marshalling only)."""
+"""Binding of libmoe_rbf.so (argument marshalling only): native code for the usual arguments (_marshal), ctypes for the rest."""
 from __future__ import annotations
 
 import ctypes
@@ -10,6 +10,7 @@ MOE_SCHEDULE_AUTO, MOE_SCHEDULE_PREFILL, MOE_SCHEDULE_DECODE = 0, 1, 2
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _lib = None
+_native = None          # the _marshal module, where torch is there
 
 
 class MoeError(RuntimeError):
@@ -83,8 +84,30 @@ def load_library():
                   "moe_dispatch",
                   "moe_dispatch_quant", "moe_combine"):
             getattr(lib, f).restype = ctypes.c_int
+        _use_native(lib)
         _lib = lib
     return _lib
+
+
+def _use_native(lib) -> None:
+    """Hands the entry points to the native marshalling, which reads torch tensors; raises if it has not been built."""
+    global _native
+    try:
+        import torch  # noqa: F401  (its libraries have to be loaded first)
+    except ImportError:
+        return
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise ImportError(f"_marshal.so cannot be loaded ({e}): build it with `python -m paper_2605_06055_amd.build`") from e
+    at = [ctypes.cast(getattr(lib, f), ctypes.c_void_p).value
+          for f in ("moe_plan", "moe_plan_static", "moe_dispatch", "moe_dispatch_quant", "moe_combine")]
+    _marshal.use(*at, MoeShape, _PlanStruct, MoePlan, _raise)
+    _native = _marshal
+
+
+def _raise(code: int, where: str) -> None:
+    raise MoeError(code, where)
 
 
 def moe_strerror(code: int) -> str:
@@ -125,6 +148,8 @@ def _first_stream() -> int:
     names = ("_cuda_getCurrentRawStream", "_cuda_getDevice", "_cuda_isInBadFork")
     if all(hasattr(torch._C, n) for n in names):
         raw, _device, _bad_fork = (getattr(torch._C, n) for n in names)
+        if _native is not None:
+            _native.streams(raw, _device, _bad_fork)
         _raw_stream = raw                       # set last: other threads test this one
     return handle
 
@@ -183,37 +208,48 @@ def _plan_struct(plan) -> _PlanStruct:
     return plan.struct() if isinstance(plan, MoePlan) else plan
 
 
-# A pass of a small decode batch takes less time on the GPU (6.3 us) than these calls took in Python (15 us, 9.9 now), so
-# they do what marshalling needs and no more; structures go in as they are (ctypes passes them by reference where the
-# argument type is a pointer to them).
+def _slow(name: str, shape, before, plan, after, stream) -> int:
+    """A call by way of ctypes: before the library is loaded and for arguments that the native marshalling does not read (it then
+    returns None), with ctypes' conversions and errors."""
+    lib = load_library()
+    return getattr(lib, name)(shape, *map(_ptr, before), _plan_struct(plan), *map(_ptr, after), _stream(stream))
+
+
 def moe_plan(shape: MoeShape, topk_idx, plan, stream=None) -> None:
-    code = (_lib or load_library()).moe_plan(shape, _ptr(topk_idx), _plan_struct(plan), _stream(stream))
+    code = _native.plan(shape, topk_idx, plan, stream) if _native else None
+    if code is None:
+        code = _slow("moe_plan", shape, (topk_idx,), plan, (), stream)
     if code:
         raise MoeError(code, "moe_plan")
 
 
 def moe_plan_static(shape: MoeShape, topk_idx, plan, stream=None) -> None:
-    code = (_lib or load_library()).moe_plan_static(shape, _ptr(topk_idx), _plan_struct(plan), _stream(stream))
+    code = _native.plan_static(shape, topk_idx, plan, stream) if _native else None
+    if code is None:
+        code = _slow("moe_plan_static", shape, (topk_idx,), plan, (), stream)
     if code:
         raise MoeError(code, "moe_plan_static")
 
 
 def moe_dispatch(shape: MoeShape, x, topk_idx, plan, window, stream=None) -> None:
-    code = (_lib or load_library()).moe_dispatch(shape, _ptr(x), _ptr(topk_idx), _plan_struct(plan), _ptr(window),
-                                                 _stream(stream))
+    code = _native.dispatch(shape, x, topk_idx, plan, window, stream) if _native else None
+    if code is None:
+        code = _slow("moe_dispatch", shape, (x, topk_idx), plan, (window,), stream)
     if code:
         raise MoeError(code, "moe_dispatch")
 
 
 def moe_dispatch_quant(shape: MoeShape, x, topk_idx, plan, window_q, window_scale, stream=None) -> None:
-    code = (_lib or load_library()).moe_dispatch_quant(shape, _ptr(x), _ptr(topk_idx), _plan_struct(plan),
-                                                       _ptr(window_q), _ptr(window_scale), _stream(stream))
+    code = _native.dispatch_quant(shape, x, topk_idx, plan, window_q, window_scale, stream) if _native else None
+    if code is None:
+        code = _slow("moe_dispatch_quant", shape, (x, topk_idx), plan, (window_q, window_scale), stream)
     if code:
         raise MoeError(code, "moe_dispatch_quant")
 
 
 def moe_combine(shape: MoeShape, expert_out, topk_w, plan, y, stream=None) -> None:
-    code = (_lib or load_library()).moe_combine(shape, _ptr(expert_out), _ptr(topk_w), _plan_struct(plan), _ptr(y),
-                                                _stream(stream))
+    code = _native.combine(shape, expert_out, topk_w, plan, y, stream) if _native else None
+    if code is None:
+        code = _slow("moe_combine", shape, (expert_out, topk_w), plan, (y,), stream)
     if code:
         raise MoeError(code, "moe_combine")

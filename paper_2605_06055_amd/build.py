@@ -1,4 +1,4 @@
-"""Builds the HIP library for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Builds the HIP library for gfx950 with hipcc (cross-compiles without a GPU) and the binding's native half."""
 from __future__ import annotations
 
 import os
@@ -38,5 +38,22 @@ def build_library(out: str = LIB, defines: dict | None = None, verbose: bool = F
     return out
 
 
+def build_marshal(out: str = os.path.join(PKG, "_marshal.so")) -> str:
+    """The binding's native argument marshalling (host code; reads torch tensors, so it is built against this torch)."""
+    import sysconfig
+    import torch
+    at = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-isystem", os.path.join(at, "include"), "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-o", out, os.path.join(CSRC, "marshal.cpp"), "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-Wl,-rpath," + os.path.join(at, "lib")]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed:\n{res.stdout}{res.stderr}")
+    return out
+
+
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_marshal())
