@@ -59,29 +59,25 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
   return (unsigned long long)s0 + ((unsigned long long)s1 << 20) + ((unsigned long long)s2 << 40);
 }
 
-// Exclusive prefix sum of total[0..E) into g[0..E], g[E] = grand total; executed by ONE wave
-// (all 64 lanes of it must call).  Each lane owns a run of consecutive experts; E <= 1024.
-// `more` (optional): two further arrays of E counts, one behind the other, that are added element-wise.
-__device__ __forceinline__ void wave_exclusive_scan_lds(const int *total, int *g, int E, const int *more = nullptr) {
-  constexpr int kMaxPer = 16;
+// Exclusive prefix sum of count(e) over the experts into g[0..E], g[E] = grand total.  Wave w (of `waves` that call, whole
+// waves) takes the experts 64 w .. 64 w + 63, 64 (w + waves) ..; what stands in front of them it sums itself, so that no barrier is
+// needed, and the lanes' accesses are consecutive.  (One wave with a run of experts per lane: plan of 9600 branches, E = 1024 10.7 us
+// against 9.3, E = 512 7.3 / 6.6, E = 256 6.2 / 6.0.)
+template <typename F>
+__device__ __forceinline__ void exclusive_scan_lds(F &&count, int *g, int E, int w, int waves) {
   const int lane = lane_id();
-  const int per = (E + kWave - 1) / kWave;
-  const int b = lane * per;
-  int c[kMaxPer];
-#pragma unroll
-  for (int x = 0; x < kMaxPer; ++x)
-    c[x] = (x < per && b + x < E) ? total[b + x] + (more ? more[b + x] + more[E + b + x] : 0) : 0;
-  int sum = 0;
-#pragma unroll
-  for (int x = 0; x < kMaxPer; ++x) sum += c[x];
-  const int incl = wave_inclusive_scan(sum);
-  int run = incl - sum;
-#pragma unroll
-  for (int x = 0; x < kMaxPer; ++x) {
-    if (x < per && b + x < E) g[b + x] = run;
-    run += c[x];
+  for (; w * kWave < E; w += waves) {
+    int low = 0, own = 0;
+    for (int x = 0; x <= w; ++x) {
+      const int e = x * kWave + lane;
+      low += own;
+      own = e < E ? count(e) : 0;
+    }
+    const int base = w > 0 ? __builtin_amdgcn_readlane(wave_inclusive_scan(low), kWave - 1) : 0;
+    const int incl = base + wave_inclusive_scan(own), e = w * kWave + lane;
+    if (e < E) g[e] = incl - own;
+    if (e == E - 1) g[E] = incl;
   }
-  if (lane == kWave - 1) g[E] = incl;
 }
 
 // Streaming 16-byte accesses: the payload is touched once by these kernels.

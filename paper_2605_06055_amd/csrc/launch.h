@@ -44,7 +44,7 @@ struct Dims {
 // Branches per plan tile for N routed branches (1024, doubled until at most 512 tiles remain) and the tile count.
 int plan_tile_size(int64_t N);
 int plan_tile_count(int64_t N);
-// Does launch_plan read and write its tile_hist scratch for N branches?  (Small batches are planned by one
+// May launch_plan read and write its tile_hist scratch for N branches?  (Small batches are planned by one
 // launch that counts every id itself and may be given tile_hist == nullptr.)
 bool plan_uses_workspace(int64_t N);
 // Plan tiles per sorted stretch of the dispatch order list for this shape; 0 = dispatch walks the branches in

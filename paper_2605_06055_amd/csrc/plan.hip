@@ -16,7 +16,7 @@
 //                            are used for COUNTS only, which do not depend on order.  One extra workgroup
 //                            writes the count/offset tables.
 // Both kernels are latency-bound (a few microseconds): loads are requested before LDS is cleared and
-// the serial chain is kept to three barriers.  Small batches skip pass 1 (see plan_rank_kernel with FUSED).
+// the serial chain is kept to three barriers.  Small batches skip pass 1.
 #include "device_utils.h"
 #include "launch.h"
 #include "plan_tables.h"
@@ -27,6 +27,12 @@ constexpr int kPlanBlock = 1024;                  // 16 waves
 constexpr int kPlanWaves = kPlanBlock / kWave;
 constexpr int kPlanMinTile = kPlanBlock;          // one branch per thread
 constexpr int kPlanMaxTiles = 512;
+constexpr int kCopies = 4;                        // of each count of a single-launch plan
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int sum4(const int *p) {
+  const i32x4 v = *(const i32x4 *)p;
+  return (v[0] + v[1]) + (v[2] + v[3]);
+}
 
 // Every pass-2 workgroup sums the histograms of all tiles, so many tiles cost more than long ones from about
 // 200 000 branches on.  Measured, us per plan with tiles of 1024 / 2048 / 4096 branches: 32 768 branches
@@ -42,14 +48,16 @@ int plan_tile_count(int64_t N) {
   return tiles < 1 ? 1 : (int)tiles;
 }
 
+template <bool PACKED>
 __global__ __launch_bounds__(kPlanBlock) void plan_tile_hist_kernel(const int32_t *__restrict__ K, int N, int E,
                                                                      int tile, int32_t *__restrict__ tile_hist) {
-  extern __shared__ int hist[];  // [E+1]
+  extern __shared__ int hist[];  // [E+1], padded to pairs of words if PACKED
   const long long start = (long long)blockIdx.x * tile;
   const long long end = min(start + (long long)tile, (long long)N);
   const long long i0 = start + threadIdx.x;
   const int first_id = i0 < end ? K[i0] : -1;     // requested before the histogram is cleared
-  for (int e = threadIdx.x; e <= E; e += kPlanBlock) hist[e] = 0;
+  const int pitch = hist_pitch<PACKED>(E);
+  for (int e = threadIdx.x; e < (PACKED ? 2 : 1) * pitch; e += kPlanBlock) hist[e] = 0;
   __syncthreads();
   for (long long i = i0; i < end; i += kPlanBlock) {
     const int e = i == i0 ? first_id : K[i];
@@ -57,8 +65,8 @@ __global__ __launch_bounds__(kPlanBlock) void plan_tile_hist_kernel(const int32_
     else if (e != -1) atomicAdd(&hist[E], 1);
   }
   __syncthreads();
-  int32_t *out = tile_hist + (size_t)blockIdx.x * (E + 1);
-  for (int e = threadIdx.x; e <= E; e += kPlanBlock) out[e] = hist[e];
+  int32_t *out = tile_hist + (size_t)blockIdx.x * pitch;
+  for (int w = threadIdx.x; w < pitch; w += kPlanBlock) out[w] = PACKED ? hist[2 * w] | hist[2 * w + 1] << 16 : hist[w];
 }
 
 // Inclusive prefix sum inside each row of 16 consecutive lanes (DPP row shifts).
@@ -73,29 +81,35 @@ __device__ __forceinline__ int row16_inclusive_scan(int v) {
 // Pass 2.  Workgroups 0..tiles-1 rank one tile each; workgroup `tiles` writes the count/offset tables.
 // A tile is split into 16 contiguous wave segments (64 branches each when the tile is 1024 branches).
 // FUSED: there was no pass 1.  Every workgroup counts the ids outside its own tile itself (in front of the
-// tile -> `before`, behind it -> `total`), which costs N LDS atomics per workgroup instead of a launch:
-// worth it for batches of up to about twelve thousand branches.
+// tile, and all others), which costs N LDS atomics per workgroup instead of a launch (see plan_in_one_launch).
+// What bounds it is the chain: launch, round trip for the ids, LDS atomics, barrier, scans, barrier, stores.  Rows of the
+// segment histograms have odd length: with rows of E words an expert's 16 counts lay in one LDS bank, and their prefix took 16
+// cycles an access (plan of 6656 branches, E = 256 8.1 / 6.2 us, of 7040, E = 512 10.1 / 7.3).  Two or four elements of that prefix in flight per
+// thread are slower (+0.1, +0.2 us: the code is longer).
+// With one copy of each count popular experts serialise the atomics: 12 000 branches of degree 1, Zipf, 16 experts 8.5 us, with four 6.7;
+// uniform 6656, E = 256 6.0 / 5.9.
 // WARM: the grid carries spare workgroups that read the caller's prefetch range (compiled apart so that the
 // usual plan carries none of it).
-template <bool FUSED, bool WARM>
+template <bool FUSED, bool WARM, bool PACKED>
 __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__restrict__ K,
                                                                 const int32_t *__restrict__ tile_hist, int tiles,
                                                                 int tile, Dims d, PlanView p, WarmRange warm) {
   extern __shared__ int lds[];
   const int E = d.E;
-  int *total = lds;                    // [E+1]  c^exp, then the number of invalid ids
-  int *g = total + E + 1;              // [E+1]  exclusive scan of the block sizes over all experts
-  int *before = g + E + 1;             // [E]    branches of expert e in earlier tiles
-  int *pre = before + E;               // [E]    branches of the source ranks below this one (several sources only)
+  // Branches of expert e (slot E: invalid ids) in four ranges of tiles: in front of this tile's sorted stretch (a run of
+  // d.order_tiles tiles), in front of the tile inside it, from the tile to the stretch's end, behind it.  FUSED (the whole batch is one
+  // stretch): in front of the tile and all others, each in kCopies counts, one for every kCopies-th lane, so that a popular
+  // expert's atomics do not all meet in one word.
+  int *range = lds;                    // [4][E+1];  FUSED: [2][E][kCopies]
+  int *g = range + (FUSED ? 2 * kCopies * E : 4 * (E + 1));        // [E+1]  exclusive scan of the block sizes over all experts
+  int *st_excl = g + E + 1;            // [E+1]  exclusive scan of the stretch's counts
+  int *pre = st_excl + E + 1;          // [E]    branches of the source ranks below this one (several sources only)
   int *post = pre + E;                 // [E]    ... above this one
-  int *wcur = post + E;                // [waves][E] segment histograms, then running s per wave segment
-  int *misc = wcur + kPlanWaves * E;   // [2]    scratch
-  // dispatch order list: counts inside this tile's sorted stretch (a run of d.order_tiles tiles)
-  int *st_total = FUSED ? total : misc + 2;             // [E+1]  branches of expert e in the whole stretch
-  int *st_before = FUSED ? before : st_total + E + 1;   // [E]    ... in the stretch's tiles in front of this one
-  int *st_excl = misc + 2 + (E + 1) + E;                // [E+1]  exclusive scan of st_total over the experts
+  int *misc = post + E;                // [2]    scratch
+  int *wcur = misc + 2;                // [waves][E+1] segment histograms, then running s per wave segment.  The odd row length
+  const int wrow = E | 1;              // spreads an expert's 16 counts over the LDS banks
   __shared__ unsigned long long others_rows;   // rows of the other source ranks, 64-bit
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const int tid = threadIdx.x, wave = uniform(tid / kWave), lane = tid % kWave;
   const int me = blockIdx.x;
   const bool multi = p.source_count != nullptr;
   if (tid == 0) others_rows = 0;
@@ -125,23 +139,22 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
     }
     SourceSums sums;
     if (multi) sums.request(p.source_count, d);
-    for (int e = tid; e <= E; e += kPlanBlock) total[e] = 0;
+    for (int e = tid; e < 4 * (E + 1); e += kPlanBlock) range[e] = 0;
     for (int e = tid; e < 2 * E; e += kPlanBlock) pre[e] = 0;        // pre and post
     __syncthreads();
-    sum_columns(tile_hist, tiles, E + 1, 0, total, nullptr, 0);
+    sum_tile_hists<PACKED>(tile_hist, tiles, tile, E, tiles, tiles, tiles, range);          // all in the first range
     if (multi) add_sources(sums, p.source_count, d, pre, post, &others_rows);
     __syncthreads();
-    if (wave == 0) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
+    exclusive_scan_lds([&](int e) { return range[e] + (multi ? pre[e] + post[e] : 0); }, g, E, wave, kPlanWaves);
     __syncthreads();
-    write_plan_tables(total, multi ? pre : nullptr, g, d, p, total[E], misc,
-                      multi && rows_overflow(others_rows, g[E]));
+    write_plan_tables(range, multi ? pre : nullptr, g, d, p, range[E], misc, multi && rows_overflow(others_rows, g[E]));
     return;
   }
 
   // The sorted stretch this tile belongs to (FUSED: the whole batch is one stretch)
   const bool ordered = d.order_tiles > 0;
-  const int st0 = ordered ? (me / d.order_tiles) * d.order_tiles : 0;
-  const int st1 = ordered ? min(tiles, st0 + d.order_tiles) : 0;
+  const int st0 = !ordered ? me : FUSED ? 0 : (me / d.order_tiles) * d.order_tiles;
+  const int st1 = !ordered ? me : FUSED ? tiles : min(tiles, st0 + d.order_tiles);
   const int seg = tile / kPlanWaves;
   const long long seg_start = (long long)me * tile + (long long)wave * seg;
   const int rounds = seg / kWave;
@@ -162,11 +175,10 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
 
   SourceSums sums;
   if (multi) sums.request(p.source_count, d);
-  for (int e = tid; e <= E; e += kPlanBlock) total[e] = 0;
-  for (int e = tid; e < 3 * E; e += kPlanBlock) before[e] = 0;       // before, pre and post
-  for (int x = tid; x < kPlanWaves * E; x += kPlanBlock) wcur[x] = 0;
-  if (!FUSED && ordered)
-    for (int e = tid; e < 2 * E + 1; e += kPlanBlock) st_total[e] = 0;                // st_total and st_before
+  for (int e = tid; e < (FUSED ? 2 * kCopies * E : 4 * (E + 1)); e += kPlanBlock) range[e] = 0;
+  for (int e = tid; e < 2 * E; e += kPlanBlock) pre[e] = 0;          // pre and post
+  for (int x = tid; x < kPlanWaves * wrow; x += kPlanBlock) wcur[x] = 0;
+  int *rest = range + kCopies * E, *const copy = range + lane % kCopies, *const rest_copy = rest + lane % kCopies;   // FUSED
   __syncthreads();
   if (FUSED) {
     for (int i0 = 0; i0 < d.N; i0 += kBatch * kPlanBlock) {
@@ -179,51 +191,47 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const int e = other[u];
-        if (e >= 0 && e < E) atomicAdd(i0 + u * kPlanBlock + tid < tile_start ? &before[e] : &total[e], 1);
+        if (e >= 0 && e < E) atomicAdd((i0 + u * kPlanBlock + tid < tile_start ? copy : rest_copy) + e * kCopies, 1);
         other[u] = next[u];
       }
     }
   } else {
-    if (ordered)
-      sum_columns_stretch(tile_hist, tiles, E + 1, me, st0, st1, total, before, st_total, st_before, E);
-    else
-      sum_columns(tile_hist, tiles, E + 1, me, total, before, E);
+    sum_tile_hists<PACKED>(tile_hist, tiles, tile, E, st0, me, st1, range);
   }
   if (multi) add_sources(sums, p.source_count, d, pre, post, &others_rows);
   // histogram of each wave's segment (counts only: atomics are order-free here)
   for (int rd = 0; rd < rounds; ++rd) {
     const long long i = seg_start + (long long)rd * kWave + lane;
     const int e = rd == 0 ? id_first : (i < d.N ? K[i] : -1);
-    if (e >= 0 && e < E) atomicAdd(&wcur[wave * E + e], 1);
+    if (e >= 0 && e < E) {
+      atomicAdd(&wcur[wave * wrow + e], 1);
+      if (FUSED) atomicAdd(rest_copy + e * kCopies, 1);  // the tile's own ids complete the counts
+    }
   }
   __syncthreads();
-  if (!FUSED && wave == 0) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
-  if (!FUSED && ordered && wave == 1) wave_exclusive_scan_lds(st_total, st_excl, E);
+  auto in_front = [&](int e) { return FUSED ? sum4(range + e * kCopies) : range[e] + range[E + 1 + e]; };
+  auto all = [&](int e) {
+    return in_front(e) + (FUSED ? sum4(rest + e * kCopies) : range[2 * (E + 1) + e] + range[3 * (E + 1) + e]);
+  };
+  auto in_stretch = [&](int e) { return FUSED ? all(e) : range[E + 1 + e] + range[2 * (E + 1) + e]; };
+  exclusive_scan_lds([&](int e) { return all(e) + (multi ? pre[e] + post[e] : 0); }, g, E, wave, kPlanWaves);
+  if (ordered) exclusive_scan_lds(in_stretch, st_excl, E, kPlanWaves - 1 - wave, kPlanWaves);
   // exclusive prefix of the segment counts over the 16 waves, seeded with the count in earlier tiles:
   // element (e, w) sits in lane w of a 16-lane row, so one DPP row scan does it
-  for (int x0 = 0; x0 < kPlanWaves * E; x0 += kPlanBlock) {
-    const int x = x0 + tid;
+  for (int x = tid; x < kPlanWaves * E; x += kPlanBlock) {
     const int e = x / kPlanWaves, w = x % kPlanWaves;
-    const bool in = x < kPlanWaves * E;
-    const int c = in ? wcur[w * E + e] : 0;
+    const int c = wcur[w * wrow + e];
     const int incl = row16_inclusive_scan(c);
-    if (in) wcur[w * E + e] = before[e] + incl - c;
-    // FUSED: total[e] held the ids behind the tile; the last wave's lane adds those in front and the tile's own
-    if (FUSED && in && w == kPlanWaves - 1) total[e] += before[e] + incl;
+    wcur[w * wrow + e] = in_front(e) + incl - c;
   }
   __syncthreads();
-  if (FUSED) {
-    if (wave == 0) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
-    if (ordered && wave == 1) wave_exclusive_scan_lds(st_total, st_excl, E);
-    __syncthreads();
-  }
 
   // rows are int32: if the blocks of all sources together do not fit, nothing is placed
   const bool overflow = multi && rows_overflow(others_rows, g[E]);
   // stable ranks inside each wave segment: 64 branches per round, rounds in index order.  Lanes with
   // the same id all read the segment's running count, then the lowest of them advances it.
   const int bits = id_bits(E);
-  int *mine = wcur + wave * E;
+  int *mine = wcur + wave * wrow;
   for (int rd = 0; rd < rounds; ++rd) {
     const long long i = seg_start + (long long)rd * kWave + lane;
     const bool in = i < d.N;
@@ -249,7 +257,7 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
       typedef int i32x2 __attribute__((ext_vector_type(2)));
       i32x2 *list = (i32x2 *)p.order;
       const long long st_base = (long long)st0 * tile;
-      if (valid) list[st_base + st_excl[e] + st_before[e] + (s - before[e])] = i32x2{(int)i / d.k, row};
+      if (valid) list[st_base + st_excl[e] + (FUSED ? s : s - range[e])] = i32x2{(int)i / d.k, row};
       if (in && (int)(i - st_base) >= st_excl[E]) list[i] = i32x2{-1, -1};
     }
     // the next round of this wave must see this round's counter updates
@@ -280,7 +288,8 @@ __global__ __launch_bounds__(kPlanBlock) void plan_empty_kernel(Dims d, PlanView
   __syncthreads();
   if (multi) add_sources(sums, p.source_count, d, pre, post, &others_rows);
   __syncthreads();
-  if (threadIdx.x < kWave) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
+  exclusive_scan_lds([&](int e) { return total[e] + (multi ? pre[e] + post[e] : 0); }, g, E, uniform((int)threadIdx.x / kWave),
+                     kPlanWaves);
   __syncthreads();
   write_plan_tables(total, multi ? pre : nullptr, g, d, p, 0, misc,
                     multi && rows_overflow(others_rows, g[E]));
@@ -291,14 +300,21 @@ hipError_t launch_plan_empty(const Dims &d, const PlanView &p, hipStream_t s) {
   return launch(plan_empty_kernel, dim3(1), dim3(kPlanBlock), lds, s, d, p);
 }
 
-// Largest batch (in tiles of 1024 branches) planned with one launch.  Measured, E = 256, graph replay:
-// one launch / two launches = 7.6 / 8.9 us at 8192 branches, 8.6 / 9.1 at 16384 (9.3 / 9.1 with Zipf
-// routing, whose hot bins serialise the LDS atomics), 10.7 / 9.2 at 32768, 26 / 11.7 at 131072.
+// Largest batch (in tiles of 1024 branches) that needs no workspace.
 #ifndef MOE_PLAN_FUSED_MAX_TILES
 #define MOE_PLAN_FUSED_MAX_TILES 12
 #endif
 
 bool plan_uses_workspace(int64_t N) { return N > (int64_t)MOE_PLAN_FUSED_MAX_TILES * kPlanMinTile; }
+
+// Batches planned with one launch: all that need no workspace, and further ones whose order list is one stretch (such a plan sorts
+// the whole batch).  us per plan, two launches / one: k = 8: 17 920 branches, E = 256 9.0 / 7.6, Zipf 8.4 / 7.3; k = 6: 18 006, E = 96
+// 8.1 / 7.1, 24 576, E = 256 8.7 / 7.6, E = 64 7.3 / 6.9; 28 672, E = 96 7.85 / 7.85, E = 256 8.85 / 8.3; 32 768 9.2 / 9.0; degrees below 4, where
+// a popular expert may have a large part of all branches: Zipf, 18 000 of degree 1, E = 16 7.5 / 8.6, of degree 3 7.0 / 7.2.
+static bool plan_in_one_launch(const Dims &d, int tiles) {
+  if (!plan_uses_workspace(d.N)) return true;
+  return d.k >= 4 && d.N <= 28 * kPlanMinTile && (d.order_tiles == 0 || d.order_tiles >= tiles);
+}
 
 // Measured on the same buffers, k = 8 unless noted, us per LAYER (plan + dispatch + combine) with the list / in token
 // order, with stretches of about 28 MB of X (3.5 MB per XCD, most of its L2), which did best:
@@ -364,34 +380,43 @@ int plan_order_tiles(const Dims &d) {
   return (int)((tiles + n - 1) / n);
 }
 
-template <bool FUSED>
+template <bool FUSED, bool PACKED>
 static hipError_t launch_plan_rank(const Dims &d, const int32_t *K, const PlanView &p, const int32_t *tile_hist,
                                    int tiles, int tile, const WarmRange &warm, hipStream_t s) {
-  const size_t lds = (size_t)(5 * d.E + 2 + kPlanWaves * d.E + 2 + 3 * d.E + 2) * sizeof(int);
-  if (lds > 64 * 1024) {   // beyond the default dynamic LDS limit (E > ~800)
+  const size_t lds = (size_t)((FUSED ? 2 * kCopies * d.E : 4 * (d.E + 1)) + 2 * (d.E + 1) + 2 * d.E + 2 + kPlanWaves * (d.E | 1)) *
+                     sizeof(int);
+  if (lds > 64 * 1024) {   // beyond the default dynamic LDS limit (E > ~580)
     static RaisedOn raised_warm, raised_plain;
-    const hipError_t e = warm.ptr ? raise_lds_limit((const void *)plan_rank_kernel<FUSED, true>, 128 * 1024, raised_warm)
-                                  : raise_lds_limit((const void *)plan_rank_kernel<FUSED, false>, 128 * 1024, raised_plain);
+    const hipError_t e = warm.ptr
+        ? raise_lds_limit((const void *)plan_rank_kernel<FUSED, true, PACKED>, 128 * 1024, raised_warm)
+        : raise_lds_limit((const void *)plan_rank_kernel<FUSED, false, PACKED>, 128 * 1024, raised_plain);
     if (e != hipSuccess) return e;
   }
   if (!warm.ptr)
-    return launch(plan_rank_kernel<FUSED, false>, dim3(tiles + 1), dim3(kPlanBlock), lds, s, K, tile_hist, tiles, tile,
+    return launch(plan_rank_kernel<FUSED, false, PACKED>, dim3(tiles + 1), dim3(kPlanBlock), lds, s, K, tile_hist, tiles, tile,
                   d, p, warm);
   // spare workgroups for plan->prefetch: 8192 vectors (128 KB) each
   const unsigned spare = (unsigned)((warm.vecs + 8191) / 8192);
-  return launch(plan_rank_kernel<FUSED, true>, dim3(tiles + 1 + spare), dim3(kPlanBlock), lds, s, K, tile_hist, tiles,
+  return launch(plan_rank_kernel<FUSED, true, PACKED>, dim3(tiles + 1 + spare), dim3(kPlanBlock), lds, s, K, tile_hist, tiles,
                 tile, d, p, warm);
+}
+
+template <bool PACKED>
+static hipError_t launch_plan_passes(const Dims &d, const int32_t *K, const PlanView &p, int32_t *tile_hist, int tiles, int tile,
+                                     const WarmRange &warm, hipStream_t s) {
+  const size_t lds = (size_t)hist_pitch<PACKED>(d.E) * (PACKED ? 2 : 1) * sizeof(int);
+  const hipError_t err = launch(plan_tile_hist_kernel<PACKED>, dim3(tiles), dim3(kPlanBlock), lds, s, K, d.N, d.E, tile, tile_hist);
+  if (err != hipSuccess) return err;
+  return launch_plan_rank<false, PACKED>(d, K, p, tile_hist, tiles, tile, warm, s);
 }
 
 hipError_t launch_plan(const Dims &d, const int32_t *K, const PlanView &p, int32_t *tile_hist, const WarmRange &warm,
                        hipStream_t s) {
   const int tile = plan_tile_size(d.N);
   const int tiles = plan_tile_count(d.N);
-  if (!plan_uses_workspace(d.N)) return launch_plan_rank<true>(d, K, p, nullptr, tiles, tile, warm, s);
-  const size_t lds1 = (size_t)(d.E + 1) * sizeof(int);
-  hipError_t err = launch(plan_tile_hist_kernel, dim3(tiles), dim3(kPlanBlock), lds1, s, K, d.N, d.E, tile, tile_hist);
-  if (err != hipSuccess) return err;
-  return launch_plan_rank<false>(d, K, p, tile_hist, tiles, tile, warm, s);
+  if (plan_in_one_launch(d, tiles)) return launch_plan_rank<true, true>(d, K, p, nullptr, tiles, tile, warm, s);
+  return tile < 65536 ? launch_plan_passes<true>(d, K, p, tile_hist, tiles, tile, warm, s)
+                      : launch_plan_passes<false>(d, K, p, tile_hist, tiles, tile, warm, s);
 }
 
 }  // namespace moe_rbf

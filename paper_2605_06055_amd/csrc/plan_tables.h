@@ -33,39 +33,6 @@ __device__ __forceinline__ int region_row_limit(int e, const Dims &d) {
   return d.stride > 0 ? (int)((e / d.Er + 1) * d.stride) : 0x7fffffff;
 }
 
-// Sums columns of a row-major int matrix src[rows][cols] with all threads of the workgroup: the columns
-// are split over `parts` groups of threads that take every parts-th row; partial sums meet in LDS with
-// integer atomics (counts: order-free).  all_sum[col] += sum over rows;
-// before_sum[col] += sum over rows < me (if before_sum is given; only columns < before_cols).
-// The targets must hold their starting values before the call; the caller synchronises afterwards.
-__device__ __forceinline__ void sum_columns(const int32_t *__restrict__ src, int rows, int cols, int me,
-                                            int *all_sum, int *before_sum, int before_cols) {
-  const int nthreads = blockDim.x;
-  const int parts = max(1, nthreads / cols);
-  const int tid = threadIdx.x;
-  if (parts > 1 && tid >= parts * cols) return;
-  const int part = parts == 1 ? 0 : tid / cols;
-  for (int col = parts == 1 ? tid : tid - part * cols; col < cols; col += nthreads) {
-    int all = 0, bef = 0;
-    const int32_t *p = src + col;
-    for (int r0 = part; r0 < rows; r0 += parts * 16) {
-      int v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int r = r0 + u * parts;
-        v[u] = r < rows ? p[(size_t)r * cols] : 0;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        all += v[u];
-        if (r0 + u * parts < me) bef += v[u];
-      }
-    }
-    if (all) atomicAdd(&all_sum[col], all);
-    if (before_sum && bef && col < before_cols) atomicAdd(&before_sum[col], bef);
-  }
-}
-
 // a / b for 0 <= a < 2^20, 0 < b <= 1024 and quotients below 1024 or so: the error of the reciprocal stays below the 0.5 / b that is
 // between the exact value and the next integer.
 __device__ __forceinline__ int small_div(int a, int b) {
@@ -161,43 +128,64 @@ __device__ __forceinline__ void add_sources(SourceSums &sums, const int32_t *__r
   if (lane_id() == 0 && wave_rows) atomicAdd(rows, wave_rows);
 }
 
-// The tile histograms summed once for a workgroup that also emits the dispatch order list: besides the sums
-// over all rows (all_sum) and over the rows in front of `me` (before_sum, columns < before_cols) it needs the
-// same two sums restricted to the rows [st0, st1) of its stretch (st_all, st_before).  Same row split as
-// sum_columns; one pass over the source instead of two.
-__device__ __forceinline__ void sum_columns_stretch(const int32_t *__restrict__ src, int rows, int cols, int me,
-                                                    int st0, int st1, int *all_sum, int *before_sum, int *st_all,
-                                                    int *st_before, int before_cols) {
-  const int nthreads = blockDim.x;
+// Tile histograms in the plan's workspace.  PACKED: 16-bit counts, rows of round4(E + 1) of them (8-byte pieces; never more bytes than
+// E + 1 words): for tiles of fewer than 2^16 branches.  Otherwise words, rows of E + 1.  Slot E counts the invalid ids.
+template <bool PACKED>
+__device__ __host__ __forceinline__ int hist_pitch(int E) { return PACKED ? (E + 4) / 4 * 2 : E + 1; }     // in words
+
+// Sums the tile histograms over four ranges of tiles, [0, b0), [b0, b1), [b1, b2), [b2, tiles), into sums[range * (E + 1) + e] (LDS, zeroed
+// by the caller, who also synchronises) with all threads of the workgroup.  Every workgroup of the plan's second launch reads all
+// histograms, so what bounds it is the instructions and round trips per row: a thread takes four columns in one 8-byte piece over a
+// run of consecutive tiles, adds them in pairs of 16 bits, and adds to LDS only where a range or its run ends (or before a count can
+// pass 16 bits).  us per plan, one column per thread with a select per row and range / now (with the bank conflicts of the wave
+// prefix gone, see plan_rank_kernel): 32 768 branches, E = 256 10.7 / 9.2, E = 512 14.2 / 10.7; 82 560, E = 512 20.0 / 12.9; 131 072, E = 128
+// 13.5 / 11.7, E = 1024 34.4 / 21.9.
+template <bool PACKED>
+__device__ __forceinline__ void sum_tile_hists(const int32_t *__restrict__ hist, int tiles, int tile, int E, int b0, int b1, int b2,
+                                               int *sums) {
+  constexpr int kWords = PACKED ? 2 : 1, kBatch = 8;           // tiles requested together
+  const int pitch = hist_pitch<PACKED>(E), cols = pitch / kWords;
+  const int nthreads = (int)blockDim.x;
   const int parts = max(1, nthreads / cols);
-  const int tid = threadIdx.x;
-  if (parts > 1 && tid >= parts * cols) return;
-  const int part = parts == 1 ? 0 : tid / cols;
-  for (int col = parts == 1 ? tid : tid - part * cols; col < cols; col += nthreads) {
-    int all = 0, bef = 0, s_all = 0, s_bef = 0;
-    const int32_t *p = src + col;
-    for (int r0 = part; r0 < rows; r0 += parts * 16) {
-      int v[16];
+  const int part = parts > 1 ? small_div((int)threadIdx.x, cols) : 0;
+  if (part >= parts) return;
+  const int each = (tiles + parts - 1) / parts;
+  const int most = PACKED ? 65535 / tile : 0x7fffffff;         // rows whose packed sums fit
+  const int first = part * each, end = min(tiles, first + each);
+  for (int col = (int)threadIdx.x - part * cols; col < cols; col += nthreads) {
+    const unsigned *src = (const unsigned *)hist + (size_t)col * kWords;
+    unsigned acc[kWords] = {}, v[kBatch][kWords];
+    int held = 0;
+    auto flush = [&](int r) {                                  // rows up to r - 1 are in acc
+      int *to = sums + (r <= b0 ? 0 : r <= b1 ? 1 : r <= b2 ? 2 : 3) * (E + 1) + col * (PACKED ? 4 : 1);
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int r = r0 + u * parts;
-        v[u] = r < rows ? p[(size_t)r * cols] : 0;
+      for (int w = 0; w < kWords; ++w) {
+        if (!PACKED) atomicAdd(to, (int)acc[w]);
+        else if (acc[w]) {                                     // (the padding past slot E stays zero)
+          if (acc[w] & 0xffffu) atomicAdd(to + 2 * w, (int)(acc[w] & 0xffffu));
+          if (acc[w] >> 16) atomicAdd(to + 2 * w + 1, (int)(acc[w] >> 16));
+        }
+        acc[w] = 0;
       }
+      held = 0;
+    };
+    for (int r0 = first; r0 < end; r0 += kBatch) {
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int r = r0 + u * parts;
-        const int in_stretch = (r >= st0 && r < st1) ? v[u] : 0;
-        all += v[u];
-        s_all += in_stretch;
-        if (r < me) bef += v[u], s_bef += in_stretch;
+      for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) v[u][w] = r0 + u < end ? src[(size_t)(r0 + u) * pitch + w] : 0u;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int r = r0 + u;
+        if (r < end) {
+          if (held > 0 && (r == b0 || r == b1 || r == b2 || held == most)) flush(r);
+#pragma unroll
+          for (int w = 0; w < kWords; ++w) acc[w] += v[u][w];  // no carry between the halves
+          ++held;
+        }
       }
     }
-    if (all) atomicAdd(&all_sum[col], all);
-    if (s_all) atomicAdd(&st_all[col], s_all);
-    if (col < before_cols) {
-      if (bef) atomicAdd(&before_sum[col], bef);
-      if (s_bef) atomicAdd(&st_before[col], s_bef);
-    }
+    if (held > 0) flush(end);
   }
 }
 
@@ -319,7 +307,7 @@ __device__ __forceinline__ void tables_from_ids_block(const int32_t *__restrict_
   }
   if (multi) add_sources(sums, p.source_count, d, pre, post, &others_rows);
   __syncthreads();
-  if (tid < kWave) wave_exclusive_scan_lds(total, g, E, multi ? pre : nullptr);
+  exclusive_scan_lds([&](int e) { return total[e] + (multi ? pre[e] + post[e] : 0); }, g, E, uniform(tid / kWave), nthreads / kWave);
   __syncthreads();
   write_plan_tables(total, multi ? pre : nullptr, g, d, p, misc[0], misc + 1, multi && rows_overflow(others_rows, g[E]));
 }
