@@ -18,10 +18,6 @@
 
 namespace moe_rbf {
 
-#ifndef MOE_COMBINE_BLOCK
-#define MOE_COMBINE_BLOCK 128
-#endif
-
 constexpr int kGather = 8;  // rows fetched together
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -82,7 +78,8 @@ struct Acc<MOE_DTYPE_F32> {
   }
 };
 
-// KFIX > 0: the routing degree is the compile-time constant KFIX (straight-line code, no bounds tests);
+// KFIX > 0: the routing degree is the compile-time constant KFIX (straight-line code, no bounds tests, all rows at once; us per
+// combine, rows taken 8 at a time / this: T = 300, H = 4096: k = 5 4.4 / 4.25, k = 10 6.9 / 6.3);
 // KFIX == 0: any k, rows taken kGather at a time.
 template <int BLOCK, int DT, int KFIX>
 __global__ __launch_bounds__(BLOCK) void combine_rows_kernel(const u32x4 *__restrict__ Yexp,
@@ -100,7 +97,7 @@ __global__ __launch_bounds__(BLOCK) void combine_rows_kernel(const u32x4 *__rest
   const u32x4 *base = Yexp + col;
   Acc<DT> acc;
   acc.zero();
-  constexpr int G = KFIX > 0 ? (KFIX < kGather ? KFIX : kGather) : kGather;
+  constexpr int G = KFIX > 0 ? KFIX : kGather;
   for (int j0 = 0; j0 < k; j0 += G) {
     int row[G];
     float wj[G];
@@ -131,6 +128,12 @@ __global__ __launch_bounds__(BLOCK) void combine_rows_kernel(const u32x4 *__rest
 // and 20 in the 160 KB of LDS, which are otherwise idle.  us per layer, X not cached, 28 units and two rounds per launch /
 // up to 56 units and one: H = 7168: T = 5000 209.4 / 204.5, 6200 281 / 273, Zipf 16384 722 / 707; H = 4096: T = 11000
 // 268 / 260.5, group-limited 32768 845 / 837.
+// K: the routing degree; G: its rows that are in flight together.  Degrees of 10 and 5 take this form too, the former 5 rows at a time:
+// us per combine, combine_rows_kernel / this with 2, 5, 8, 10 rows in flight: k = 10: H = 3456, T = 25255 341 / 381, 290, 304, 298; H = 2048,
+// T = 12000 92 / 113, 87, -, -.  us per layer: k = 10: H = 7168, T = 8000 414 / 389; H = 1032, T = 24000 253 / 236; k = 5: H = 7168, T = 8000 230 / 226;
+// H = 5120, T = 16000 358 / 351; not where more than an eighth of the padded columns is idle (H = 1600, T = 24000 163 / 168; H = 2176,
+// T = 6000 60.4 / 63.1).  k = 8 with 4 rows in flight: H = 4096, T = 16000 388 / 384, but Zipf H = 7168, T = 16384 710 / 721 and H = 640,
+// T = 28000 118 / 132; k = 6 with 3: 6 % slower.
 // Same arithmetic as combine_rows_kernel
 // (ascending j, one fma per placed branch, one rounding).  Units (token, column) are numbered token-major over
 // columns padded to a multiple of 64, so that a wave stays inside one token: without the padding (H = 4104: 115
@@ -147,24 +150,24 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F &&f
   (void)(f(std::integral_constant<int, I>{}) && ...);
 }
 
-template <int DT, int KFIX>
+template <int DT, int K, int G>
 __device__ __forceinline__ u32x4 combine_unit(const u32x4 *__restrict__ Yexp, const float *__restrict__ wt,
-                                              const int32_t *__restrict__ rm, int t, int col, int k, int H16) {
-  constexpr int G = KFIX > 0 ? (KFIX < kGather ? KFIX : kGather) : kGather;
+                                              const int32_t *__restrict__ rm, int t, int col, int H16) {
+  static_assert(K % G == 0, "whole rounds of rows");
   const int ts = uniform(t);
-  const int32_t *rows = rm + (size_t)ts * k;
-  const float *w = wt + (size_t)ts * k;
+  const int32_t *rows = rm + (size_t)ts * K;
+  const float *w = wt + (size_t)ts * K;
   Acc<DT> acc;
   acc.zero();
-  for (int j0 = 0; j0 < k; j0 += G) {
+#pragma unroll
+  for (int j0 = 0; j0 < K; j0 += G) {
     int row[G];
     float wj[G];
     u32x4 y[G];
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      const bool in = (KFIX > 0 && KFIX % G == 0) || j0 + u < k;
-      row[u] = in ? uniform(rows[j0 + u]) : -1;
-      wj[u] = in ? __uint_as_float(uniform(__float_as_uint(w[j0 + u]))) : 0.0f;
+      row[u] = uniform(rows[j0 + u]);
+      wj[u] = __uint_as_float(uniform(__float_as_uint(w[j0 + u])));
     }
 #pragma unroll
     for (int u = 0; u < G; ++u)
@@ -176,16 +179,15 @@ __device__ __forceinline__ u32x4 combine_unit(const u32x4 *__restrict__ Yexp, co
   return acc.result();
 }
 
-template <int DT, int KFIX>
+template <int DT, int K, int G>
 __global__ __launch_bounds__(kDeferBlock) void combine_deferred_kernel(const u32x4 *__restrict__ Yexp,
                                                                        const float *__restrict__ W,
                                                                        const int32_t *__restrict__ row_map,
-                                                                       u32x4 *__restrict__ Y, int k_arg, int H16,
+                                                                       u32x4 *__restrict__ Y, int H16,
                                                                        int cols_pad, int units, int dq, int dr,
                                                                        int first, int in_lds) {
   // this launch covers units [first, units), at most in_lds + kDeferRegs a thread
   extern __shared__ u32x4 held[];
-  const int k = KFIX > 0 ? KFIX : k_arg;
   const int nthreads = (int)gridDim.x * kDeferBlock;
   const int g = (int)blockIdx.x * kDeferBlock + (int)threadIdx.x;
   const int32_t *rm = (const int32_t *)__builtin_assume_aligned(row_map, 16);
@@ -204,12 +206,12 @@ __global__ __launch_bounds__(kDeferBlock) void combine_deferred_kernel(const u32
   };
 #pragma unroll 1
   for (int r = 0; r < in_lds && u < units; ++r) {
-    if (col < H16) held[r * kDeferBlock + threadIdx.x] = combine_unit<DT, KFIX>(Yexp, wt, rm, t, col, k, H16);
+    if (col < H16) held[r * kDeferBlock + threadIdx.x] = combine_unit<DT, K, G>(Yexp, wt, rm, t, col, H16);
     step();
   }
   unrolled(std::make_integer_sequence<int, kDeferRegs>{}, [&](auto r) {
     if (u >= units) return false;
-    if (col < H16) res[r] = combine_unit<DT, KFIX>(Yexp, wt, rm, t, col, k, H16);
+    if (col < H16) res[r] = combine_unit<DT, K, G>(Yexp, wt, rm, t, col, H16);
     step();
     return true;
   });
@@ -237,17 +239,15 @@ __global__ __launch_bounds__(kDeferBlock) void combine_deferred_kernel(const u32
 // bf16 rows of 14 KB; without the loop H = 896, T = 9984 takes 111.7 and bf16 rows move by 0.8 % either way.
 constexpr int kRoundUnits = 28;
 
-template <int DT, int KFIX>
+template <int DT, int K>
 __global__ __launch_bounds__(kDeferBlock) void combine_round_kernel(const u32x4 *__restrict__ Yexp,
                                                                        const float *__restrict__ W,
                                                                        const int32_t *__restrict__ row_map,
-                                                                       u32x4 *__restrict__ Y, int k_arg, int H16,
+                                                                       u32x4 *__restrict__ Y, int H16,
                                                                        int cols_pad, int units, int dq, int dr,
                                                                        int first) {
   // this launch covers units [first, units)
-  constexpr int R = kRoundUnits;
-  const int k = KFIX > 0 ? KFIX : k_arg;
-  constexpr int G = KFIX > 0 ? (KFIX < kGather ? KFIX : kGather) : kGather;
+  constexpr int R = kRoundUnits, G = K;
   const int nthreads = (int)gridDim.x * kDeferBlock;
   const int g = (int)blockIdx.x * kDeferBlock + (int)threadIdx.x;
   const int32_t *rm = (const int32_t *)__builtin_assume_aligned(row_map, 16);
@@ -261,19 +261,18 @@ __global__ __launch_bounds__(kDeferBlock) void combine_round_kernel(const u32x4 
     for (int r = 0; r < R; ++r) {
       if (u0 + (long long)r * nthreads < units && col < H16) {     // the first test is uniform per wave
         const int ts = uniform(t);
-        const int32_t *rows = rm + (size_t)ts * k;
-        const float *w = wt + (size_t)ts * k;
+        const int32_t *rows = rm + (size_t)ts * K;
+        const float *w = wt + (size_t)ts * K;
         Acc<DT> acc;
         acc.zero();
-        for (int j0 = 0; j0 < k; j0 += G) {
+        for (int j0 = 0; j0 < K; j0 += G) {
           int row[G];
           float wj[G];
           u32x4 y[G];
 #pragma unroll
           for (int u = 0; u < G; ++u) {
-            const bool in = (KFIX > 0 && KFIX % G == 0) || j0 + u < k;
-            row[u] = in ? uniform(rows[j0 + u]) : -1;
-            wj[u] = in ? __uint_as_float(uniform(__float_as_uint(w[j0 + u]))) : 0.0f;
+            row[u] = uniform(rows[j0 + u]);
+            wj[u] = __uint_as_float(uniform(__float_as_uint(w[j0 + u])));
           }
 #pragma unroll
           for (int u = 0; u < G; ++u)
@@ -319,14 +318,12 @@ static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out,
   const int grid = device_cus();
   const int nthreads = grid * kDeferBlock;
   const long long per_thread = ((long long)units + nthreads - 1) / nthreads;
-  if (per_thread <= kRoundUnits) {
+  if (per_thread <= kRoundUnits && (d.k == 8 || d.k == 6)) {
     auto once = [&](auto kernel) {
       return launch(kernel, dim3(grid), dim3(kDeferBlock), 0, s, (const u32x4 *)expert_out, W, (const int32_t *)p.row_map,
-                    (u32x4 *)y, d.k, d.H16, cols_pad, units, nthreads / cols_pad, nthreads % cols_pad, 0);
+                    (u32x4 *)y, d.H16, cols_pad, units, nthreads / cols_pad, nthreads % cols_pad, 0);
     };
-    if (d.k == 8) return once(combine_round_kernel<DT, 8>);
-    if (d.k == 6) return once(combine_round_kernel<DT, 6>);
-    return hipErrorInvalidValue;
+    return d.k == 8 ? once(combine_round_kernel<DT, 8>) : once(combine_round_kernel<DT, 6>);
   }
   // As few launches as can hold all results, of equal length.
   const long long launches = (per_thread + kDeferRegs + kDeferLds - 1) / (kDeferRegs + kDeferLds);
@@ -342,16 +339,18 @@ static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out,
     for (long long first = 0; first < units; first += per) {
       const long long end = first + per < units ? first + per : units;
       const hipError_t e = launch(kernel, dim3(grid), dim3(kDeferBlock), lds, s, (const u32x4 *)expert_out, W,
-                                  (const int32_t *)p.row_map, (u32x4 *)y, d.k, d.H16, cols_pad, (int)end,
+                                  (const int32_t *)p.row_map, (u32x4 *)y, d.H16, cols_pad, (int)end,
                                   nthreads / cols_pad, nthreads % cols_pad, (int)first, in_lds);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
   };
-  static RaisedOn raised8, raised6;
+  static RaisedOn raised10, raised8, raised6, raised5;
   switch (d.k) {
-    case 8: return go(combine_deferred_kernel<DT, 8>, raised8);
-    case 6: return go(combine_deferred_kernel<DT, 6>, raised6);
+    case 10: return go(combine_deferred_kernel<DT, 10, 5>, raised10);
+    case 8: return go(combine_deferred_kernel<DT, 8, 8>, raised8);
+    case 6: return go(combine_deferred_kernel<DT, 6, 6>, raised6);
+    case 5: return go(combine_deferred_kernel<DT, 5, 5>, raised5);
     default: return hipErrorInvalidValue;      // other routing degrees keep combine_rows_kernel (see launch_combine)
   }
 }
@@ -366,9 +365,12 @@ static hipError_t launch_combine_dt(const Dims &d, const void *expert_out, const
                   d.k, d.H16, chunks);
   };
   switch (d.k) {
+    case 10: return go(combine_rows_kernel<B, DT, 10>);
     case 8: return go(combine_rows_kernel<B, DT, 8>);
     case 6: return go(combine_rows_kernel<B, DT, 6>);
+    case 5: return go(combine_rows_kernel<B, DT, 5>);
     case 4: return go(combine_rows_kernel<B, DT, 4>);
+    case 3: return go(combine_rows_kernel<B, DT, 3>);
     case 2: return go(combine_rows_kernel<B, DT, 2>);
     case 1: return go(combine_rows_kernel<B, DT, 1>);
     default: return go(combine_rows_kernel<B, DT, 0>);
@@ -381,22 +383,31 @@ hipError_t launch_combine(const Dims &d, const void *expert_out, const float *W,
   // two-wave workgroups once it streams.  Measured, H = 7168, k = 8, 64 / 128 threads: T = 128: 4.61 / 4.74 us,
   // T = 1024: 22.5 / 22.7, T = 2048: 43.1 / 43.0, T = 4096: 88.1 / 86.9.
   const bool small = (int64_t)d.T * d.H16 <= (int64_t)1536 * 1024;
-  // Streaming launches with a routing degree of 6 or 8 take the deferred-store form.  Measured inside layers,
+  // Streaming launches with a routing degree of 5, 6, 8 or 10 take the deferred-store form.  Measured inside layers,
   // us per layer deferred / not: H = 7168: T = 2048 91.5 / 92.2, 3072 136.2 / 138.3, 4096 180.4 / 185.2,
   // 6144 264.9 / 267.7, 8192 348.1 / 355.2, 16384 702.9 / 713.1, Zipf 16384 673.5 / 681.8; H = 4096: T = 4096
-  // 103.4 / 104.3, 16384 380.2 / 387.5, group-limited 32768 846.6 / 848.5; k = 4, T = 4096: 104.1 / 103.4 (no gain:
-  // smaller degrees, and degrees without a compile-time form, whose results array the compiler would spill, stay).
-  const int cols_pad = (d.H16 + 63) / 64 * 64;
+  // 103.4 / 104.3, 16384 380.2 / 387.5, group-limited 32768 846.6 / 848.5; degrees of 5 and 10: see there; k = 4: T = 4096
+  // 104.1 / 103.4, H = 2176, T = 24000 96 / 86 (a combine), k = 3: H = 7168, T = 8000 83 / 74 (smaller degrees, and degrees without a
+  // compile-time form, whose results array the compiler would spill, stay).
+  // The others: rows of an odd number of waves that is a multiple of 3 take workgroups of 3 waves, so that no workgroup is half
+  // idle.  us per layer, 2 waves / 3: T = 20000: H = 1152: k = 1 50.8 / 48.2, k = 3 73.2 / 68.4, k = 5 104.9 / 98.5; H = 1536, k = 4 109.3 / 105.9;
+  // H = 4104, k = 2 205.7 / 202.4, k = 5 405.7 / 400.3.  (Of one wave: H = 4104, k = 5 417; of 5 or 7 where the row has as many: no gain.  The
+  // columns past the last whole wave of several tokens packed into one wave: H = 4104, k = 6 33.3 / 34.3 a combine, H = 640, k = 8 51 / 56.)
+  const int cols_pad = (d.H16 + 63) / 64 * 64, waves = cols_pad / kWave;
+  const bool threes = waves % 2 == 1 && waves % 3 == 0;
+  const bool held = d.k == 10 || d.k == 8 || d.k == 6 || (d.k == 5 && !threes && cols_pad * 7 <= d.H16 * 8);
   const long long units = (long long)d.T * cols_pad;
-  if (!small && (d.k == 8 || d.k == 6) && units < 0x7fffffffLL)
+  if (!small && held && units < 0x7fffffffLL)
     return d.dtype == MOE_DTYPE_BF16
                ? launch_combine_deferred<MOE_DTYPE_BF16>(d, expert_out, W, p, y, cols_pad, (int)units, s)
                : launch_combine_deferred<MOE_DTYPE_F32>(d, expert_out, W, p, y, cols_pad, (int)units, s);
-  if (d.dtype == MOE_DTYPE_BF16)
-    return small ? launch_combine_dt<MOE_DTYPE_BF16, 64>(d, expert_out, W, p, y, s)
-                 : launch_combine_dt<MOE_DTYPE_BF16, MOE_COMBINE_BLOCK>(d, expert_out, W, p, y, s);
-  return small ? launch_combine_dt<MOE_DTYPE_F32, 64>(d, expert_out, W, p, y, s)
-               : launch_combine_dt<MOE_DTYPE_F32, MOE_COMBINE_BLOCK>(d, expert_out, W, p, y, s);
+  auto rows = [&](auto dtype) {
+    constexpr int DT = decltype(dtype)::value;
+    if (small) return launch_combine_dt<DT, 64>(d, expert_out, W, p, y, s);
+    return threes ? launch_combine_dt<DT, 192>(d, expert_out, W, p, y, s) : launch_combine_dt<DT, 128>(d, expert_out, W, p, y, s);
+  };
+  return d.dtype == MOE_DTYPE_BF16 ? rows(std::integral_constant<int, MOE_DTYPE_BF16>{})
+                                   : rows(std::integral_constant<int, MOE_DTYPE_F32>{});
 }
 
 }  // namespace moe_rbf

@@ -1,0 +1,62 @@
+"""Combine at the degrees and widths that choose its form: 5 and 10 rows with results held back (at the numbers of results per thread
+where they move), rows of 3 and 9 waves in workgroups of 3, one row past and short of them, small launches."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def moe():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_06055_amd as m
+    m.load_library()
+    return m
+
+
+STREAMS = 1536 * 1024                                          # vectors of Y beyond which a launch streams
+
+
+def cases():
+    threads = 256 * 512
+    for k, dtype, H16 in ((10, "bf16", 144), (10, "f32", 513), (5, "bf16", 256), (5, "f32", 224)):
+        padded = (H16 + 63) // 64 * 64
+        yield k, dtype, H16, STREAMS // H16 + 1
+        for per_thread in (36, 56):
+            for more in (0, 1):
+                yield k, dtype, H16, threads * per_thread // padded + more
+    for k in (1, 2, 3, 4, 5, 7):
+        for H16 in (128, 129, 192, 193, 513, 576):
+            yield k, "bf16", H16, STREAMS // H16 + 1
+    for k in (3, 5, 10, 11):
+        for H16 in (1, 64, 129, 513):
+            yield k, "f32", H16, 77
+
+
+@pytest.mark.parametrize("k,dtype,H16,T", list(cases()))
+def test_combine(moe, k, dtype, H16, T):
+    bf16 = dtype == "bf16"
+    H = H16 * (8 if bf16 else 4)
+    print(f"[forms] T={T} H={H} k={k} {dtype}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T + k)
+    storage = torch.bfloat16 if bf16 else torch.float32
+    # small integers: every product and partial sum is exact in fp32, so only the last rounding is left
+    out = torch.randint(-8, 9, (T * k, H), generator=gen, device="cuda", dtype=torch.int8).to(storage)
+    w = torch.randint(-4, 5, (T, k), generator=gen, device="cuda").float()
+    rows = torch.randperm(T * k, generator=gen, device="cuda").to(torch.int32).view(T, k)
+    rows[torch.rand((T, k), generator=gen, device="cuda") < 0.05] = -1
+    shape = moe.MoeShape(T=T, H=H, k=k, E=16, R=2, dtype=moe.MOE_DTYPE_BF16 if bf16 else moe.MOE_DTYPE_F32,
+                         schedule=moe.MOE_SCHEDULE_PREFILL)
+    plan = moe.MoePlan(shape)
+    plan.row_map.copy_(rows.view(-1))
+    y = torch.full((T + 1, H), 77.0, dtype=storage, device="cuda")
+    moe.moe_combine(shape, out, w, plan, y[:T])
+    want = torch.zeros((T, H), dtype=torch.float32, device="cuda")
+    for j in range(k):
+        at = rows[:, j].long()
+        want += torch.where(at[:, None] >= 0, w[:, j:j + 1] * out[at.clamp_min(0)].float(), 0.0)
+    assert torch.equal(y[:T], want.to(storage))
+    assert bool((y[T] == 77.0).all())
