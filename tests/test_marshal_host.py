@@ -124,3 +124,14 @@ def test_native_and_ctypes_marshalling_agree(tmp_path):
     res = subprocess.run([sys.executable, "-c", CHILD, ROOT], env=dict(os.environ, MOE_RBF_LIB=so), capture_output=True, text=True,
                          timeout=300)
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-3000:]
+
+
+def test_native_marshalling_has_no_thread_local_storage():
+    """One would slow down every thread-local access of the libraries that are there already (see build_marshal)."""
+    import struct
+    import paper_2605_06055_amd as moe
+    with open(os.path.join(os.path.dirname(moe.__file__), "_marshal.so"), "rb") as f:
+        elf = f.read()
+    offset, size, count = struct.unpack_from("<Q", elf, 32)[0], *struct.unpack_from("<HH", elf, 54)
+    kinds = [struct.unpack_from("<I", elf, offset + i * size)[0] for i in range(count)]
+    assert 1 in kinds and 7 not in kinds                       # PT_LOAD, PT_TLS
