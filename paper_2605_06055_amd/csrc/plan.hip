@@ -94,7 +94,7 @@ template <bool FUSED, bool WARM, bool PACKED>
 __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__restrict__ K,
                                                                 const int32_t *__restrict__ tile_hist, int tiles,
                                                                 int tile, Dims d, PlanView p, WarmRange warm) {
-  extern __shared__ int lds[];
+  extern __shared__ __align__(16) int lds[];     // sum4 reads 16 bytes at a time
   const int E = d.E;
   // Branches of expert e (slot E: invalid ids) in four ranges of tiles: in front of this tile's sorted stretch (a run of
   // d.order_tiles tiles), in front of the tile inside it, from the tile to the stretch's end, behind it.  FUSED (the whole batch is one
