@@ -253,3 +253,25 @@ def moe_combine(shape: MoeShape, expert_out, topk_w, plan, y, stream=None) -> No
         code = _slow("moe_combine", shape, (expert_out, topk_w), plan, (y,), stream)
     if code:
         raise MoeError(code, "moe_combine")
+
+
+def _bind(shape, plan, prefill, x, topk_idx, topk_w, window, expert_out, y, stream):
+    """A layer's two calls on fixed addresses, (dispatch, combine): natively, or by way of ctypes for what the native marshalling
+    does not read (it then returns None)."""
+    lib = load_library()
+    calls = _native.bind(shape, plan, prefill, x, topk_idx, topk_w, window, expert_out, y, stream) if _native else None
+    if calls is not None:
+        return calls.dispatch, calls.combine
+    vp = ctypes.c_void_p
+    shape, plan = ctypes.byref(shape), ctypes.byref(plan)
+    x, topk_idx, topk_w, window, expert_out, y, stream = map(vp, (x, topk_idx, topk_w, window, expert_out, y, stream))
+
+    def dispatch():
+        if prefill:
+            _check(lib.moe_plan(shape, topk_idx, plan, stream), "moe_plan")
+        _check(lib.moe_dispatch(shape, x, topk_idx, plan, window, stream), "moe_dispatch")
+
+    def combine():
+        _check(lib.moe_combine(shape, expert_out, topk_w, plan, y, stream), "moe_combine")
+
+    return dispatch, combine

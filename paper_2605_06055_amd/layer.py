@@ -62,9 +62,7 @@ class MoeLayer:
         """Pre-marshalled calls for a serving loop that re-runs the layer on the same buffers: returns
         (dispatch, combine) callables whose arguments were read once.  The stream is the one
         current at bind time unless given."""
-        B.load_library()
         st = B._stream(stream) or 0
         self._bound_keepalive = (x, topk_idx, topk_w)
-        calls = B._native.bind(self.shape, self._plan_struct, self.schedule == B.MOE_SCHEDULE_PREFILL,
-                               *(B._ptr(t) for t in (x, topk_idx, topk_w, self.window, self.expert_out, self.y)), st)
-        return calls.dispatch, calls.combine
+        return B._bind(self.shape, self._plan_struct, self.schedule == B.MOE_SCHEDULE_PREFILL,
+                       *(B._ptr(t) for t in (x, topk_idx, topk_w, self.window, self.expert_out, self.y)), st)
