@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
 from typing import Optional
 
 MOE_DTYPE_BF16, MOE_DTYPE_F32 = 0, 1
@@ -10,7 +11,7 @@ MOE_SCHEDULE_AUTO, MOE_SCHEDULE_PREFILL, MOE_SCHEDULE_DECODE = 0, 1, 2
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _lib = None
-_native = None          # the _marshal module, where torch is there
+_native = None          # the _marshal module, where it can be used
 
 
 class MoeError(RuntimeError):
@@ -90,20 +91,24 @@ def load_library():
 
 
 def _use_native(lib) -> None:
-    """Hands the entry points to the native marshalling, which reads torch tensors; raises if it has not been built."""
+    """Hands the entry points to the native marshalling.  It reads torch tensors and Python objects by their layout: where it has not
+    been built, or for another torch or Python, every call goes by way of ctypes."""
     global _native
     try:
-        import torch  # noqa: F401  (its libraries have to be loaded first)
+        import torch                   # its libraries have to be loaded first
+        from . import _marshal
     except ImportError:
         return
-    try:
-        from . import _marshal
-    except ImportError as e:
-        raise ImportError(f"_marshal.so cannot be loaded ({e}): build it with `python -m paper_2605_06055_amd.build`") from e
+    if getattr(_marshal, "built_for", None) != _interpreter(torch):
+        return
     at = [ctypes.cast(getattr(lib, f), ctypes.c_void_p).value
           for f in ("moe_plan", "moe_plan_static", "moe_dispatch", "moe_dispatch_quant", "moe_combine")]
     _marshal.use(*at, MoeShape, _PlanStruct, MoePlan, _raise)
     _native = _marshal
+
+
+def _interpreter(torch) -> str:
+    return f"torch {torch.__version__}, {sys.implementation.cache_tag}"
 
 
 def _raise(code: int, where: str) -> None:

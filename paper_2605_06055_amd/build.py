@@ -46,10 +46,12 @@ def build_marshal(out: str = os.path.join(PKG, "_marshal.so")) -> str:
     calls were 10 to 20 % slower."""
     import sysconfig
     import torch
+    from .binding import _interpreter
     at = os.path.dirname(torch.__file__)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-DNDEBUG", "-Wall", "-I", os.path.join(ROOT, "include"),
            "-isystem", os.path.join(at, "include"), "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DMOE_BUILT_FOR="{_interpreter(torch)}"',
            "-o", out, os.path.join(CSRC, "marshal.cpp"), "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
            "-Wl,-rpath," + os.path.join(at, "lib")]
     res = subprocess.run(cmd, capture_output=True, text=True)

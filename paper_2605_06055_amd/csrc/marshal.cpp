@@ -289,5 +289,8 @@ PyMODINIT_FUNC PyInit__marshal() {
   bound_type.tp_dealloc = bound_free;
   bound_type.tp_methods = bound_methods;
   if (PyType_Ready(&bound_type) < 0) return nullptr;
-  return PyModule_Create(&module);
+  PyObject *m = PyModule_Create(&module);
+  // the torch and the Python whose objects are read here: the binding leaves the module aside where it finds others
+  if (m && PyModule_AddStringConstant(m, "built_for", MOE_BUILT_FOR) < 0) Py_CLEAR(m);
+  return m;
 }

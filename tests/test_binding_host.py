@@ -1,5 +1,5 @@
-"""The calls that MoeLayer binds, for every form of argument.  A stand-in library that only records its arguments takes the place of the HIP
-one."""
+"""The binding where its native half is missing or was built for another torch, and the calls that MoeLayer binds, for every form of
+argument.  A stand-in library that only records its arguments takes the place of the HIP one."""
 import os
 import subprocess
 import sys
@@ -21,6 +21,18 @@ def library():
 x, ids, w = torch.zeros(5, 16), torch.zeros(5, 2, dtype=torch.int32), torch.zeros(5, 2)
 def layer(schedule=1, **more):
     return MoeLayer(5, 16, 2, 4, 2, dtype=moe.MOE_DTYPE_F32, schedule=schedule, device="cpu", **more)
+def every_call(expected_native):
+    lib, seen, answer = library()
+    assert (B._native is not None) == expected_native
+    for schedule in (1, 2):
+        l = layer(schedule)
+        l.dispatch(x, ids, stream=55)
+        assert seen[42] == x.data_ptr() and seen[44] == l.window.data_ptr() and seen[46] == 55
+        l.combine(w, stream=55)
+        assert seen[42] == l.expert_out.data_ptr() and seen[44] == l.y.data_ptr()
+        moe.moe_plan(l.shape, ids, l.plan, 55)
+        assert seen[42] == ids.data_ptr() and seen[46] == 55
+        bound(seen, answer, l, schedule, *l.bind(x, ids, w, stream=55))
 def bound(seen, answer, l, schedule, dispatch, combine, stream=55):
     seen[50] = 0
     dispatch()
@@ -66,3 +78,17 @@ for schedule in (1, 2):
     bound(seen, answer, l, schedule, *l.bind(x, ids, w, stream=55))
     assert list(seen)[40:42] == [1, 1]
 """)
+
+
+def test_without_the_native_half(run):
+    """The library alone is enough: every call then goes by way of ctypes."""
+    run("sys.modules['paper_2605_06055_amd._marshal'] = None\nevery_call(False)\n")
+
+
+def test_native_half_of_another_torch(run):
+    """It reads torch's objects by their layout, so one built for another version is left aside."""
+    run("torch.__version__ = '1.2.3'\nevery_call(False)\n")
+
+
+def test_native_half_of_this_torch(run):
+    run("every_call(True)\n")
