@@ -260,11 +260,11 @@ def moe_combine(shape: MoeShape, expert_out, topk_w, plan, y, stream=None) -> No
         raise MoeError(code, "moe_combine")
 
 
-def _bind(shape, plan, prefill, x, topk_idx, topk_w, window, expert_out, y, stream):
+def _bind(shape, plan, prefill, x, topk_idx, topk_w, window, expert_out, y, stream, buffers):
     """A layer's two calls on fixed addresses, (dispatch, combine): natively, or by way of ctypes for what the native marshalling
-    does not read (it then returns None)."""
+    does not read (it then returns None).  Each of the two keeps `buffers`, the owners of the memory."""
     lib = load_library()
-    calls = _native.bind(shape, plan, prefill, x, topk_idx, topk_w, window, expert_out, y, stream) if _native else None
+    calls = _native.bind(shape, plan, prefill, x, topk_idx, topk_w, window, expert_out, y, stream, buffers) if _native else None
     if calls is not None:
         return calls.dispatch, calls.combine
     vp = ctypes.c_void_p
@@ -279,4 +279,5 @@ def _bind(shape, plan, prefill, x, topk_idx, topk_w, window, expert_out, y, stre
     def combine():
         _check(lib.moe_combine(shape, expert_out, topk_w, plan, y, stream), "moe_combine")
 
+    dispatch.buffers = combine.buffers = buffers
     return dispatch, combine

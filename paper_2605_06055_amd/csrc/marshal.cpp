@@ -179,10 +179,10 @@ PyObject *combine(PyObject *, PyObject *const *o, Py_ssize_t n) {
   return without_gil([&] { return lib.combine(a.shape, a.in[0], (const float *)a.in[1], a.plan, a.out[0], a.stream); });
 }
 
-// A layer's calls on fixed buffers.  The structures are kept alive and read at every call.
+// A layer's calls on fixed buffers.  The structures are read at every call; they and `buffers`, which owns the memory, are kept alive.
 struct Bound {
   PyObject_HEAD
-  PyObject *shape, *plan;
+  PyObject *shape, *plan, *buffers;
   const moe_shape *sh;
   moe_plan_t *pl;
   void *x, *ids, *weights, *window, *expert_out, *y, *stream;
@@ -192,6 +192,7 @@ void bound_free(PyObject *o) {
   Bound *b = (Bound *)o;
   Py_XDECREF(b->shape);
   Py_XDECREF(b->plan);
+  Py_XDECREF(b->buffers);
   Py_TYPE(o)->tp_free(o);
 }
 PyObject *failed(int code, const char *where) { return PyObject_CallFunction(raise_error, "is", code, where); }
@@ -221,9 +222,9 @@ PyMethodDef bound_methods[] = {{"dispatch", bound_dispatch, METH_NOARGS, "plan (
                                {nullptr, nullptr, 0, nullptr}};
 PyTypeObject bound_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
-// bind(shape, plan struct, prefill, x, ids, weights, window, expert_out, y, stream): an object with dispatch() and combine()
+// bind(shape, plan struct, prefill, x, ids, weights, window, expert_out, y, stream, buffers): an object with dispatch() and combine()
 PyObject *bind(PyObject *, PyObject *const *o, Py_ssize_t n) {
-  if (n != 10 || !lib.plan) Py_RETURN_NONE;
+  if (n != 11 || !lib.plan) Py_RETURN_NONE;
   void *sh, *pl, *at[7];
   TRY(structure(o[0], shape_type, sizeof(moe_shape), &sh))
   TRY(structure(o[1], struct_type, sizeof(moe_plan_t), &pl))
@@ -234,7 +235,8 @@ PyObject *bind(PyObject *, PyObject *const *o, Py_ssize_t n) {
   if (!b) return nullptr;
   Py_INCREF(o[0]);
   Py_INCREF(o[1]);
-  b->shape = o[0], b->plan = o[1], b->sh = (const moe_shape *)sh, b->pl = (moe_plan_t *)pl, b->prefill = prefill;
+  Py_INCREF(o[10]);
+  b->shape = o[0], b->plan = o[1], b->buffers = o[10], b->sh = (const moe_shape *)sh, b->pl = (moe_plan_t *)pl, b->prefill = prefill;
   b->x = at[0], b->ids = at[1], b->weights = at[2], b->window = at[3], b->expert_out = at[4], b->y = at[5], b->stream = at[6];
   return (PyObject *)b;
 }

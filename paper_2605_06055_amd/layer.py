@@ -61,8 +61,8 @@ class MoeLayer:
     def bind(self, x, topk_idx, topk_w, stream=None):
         """Pre-marshalled calls for a serving loop that re-runs the layer on the same buffers: returns
         (dispatch, combine) callables whose arguments were read once.  The stream is the one
-        current at bind time unless given."""
+        current at bind time unless given.  Each of the two keeps the buffers alive, without the layer too."""
         st = B._stream(stream) or 0
-        self._bound_keepalive = (x, topk_idx, topk_w)
-        return B._bind(self.shape, self._plan_struct, self.schedule == B.MOE_SCHEDULE_PREFILL,
-                       *(B._ptr(t) for t in (x, topk_idx, topk_w, self.window, self.expert_out, self.y)), st)
+        tensors = (x, topk_idx, topk_w, self.window, self.expert_out, self.y)
+        return B._bind(self.shape, self._plan_struct, self.schedule == B.MOE_SCHEDULE_PREFILL, *(B._ptr(t) for t in tensors), st,
+                       (tensors, tuple(vars(self.plan).values())))

@@ -1,5 +1,5 @@
 """The binding where its native half is missing or was built for another torch, and the calls that MoeLayer binds, for every form of
-argument.  A stand-in library that only records its arguments takes the place of the HIP one."""
+argument and for as long as a caller holds them.  A stand-in library that only records its arguments takes the place of the HIP one."""
 import os
 import subprocess
 import sys
@@ -21,6 +21,8 @@ def library():
 x, ids, w = torch.zeros(5, 16), torch.zeros(5, 2, dtype=torch.int32), torch.zeros(5, 2)
 def layer(schedule=1, **more):
     return MoeLayer(5, 16, 2, 4, 2, dtype=moe.MOE_DTYPE_F32, schedule=schedule, device="cpu", **more)
+def all_alive(refs):
+    return all(r() is not None for r in refs)
 def every_call(expected_native):
     lib, seen, answer = library()
     assert (B._native is not None) == expected_native
@@ -92,3 +94,31 @@ def test_native_half_of_another_torch(run):
 
 def test_native_half_of_this_torch(run):
     run("every_call(True)\n")
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_bound_calls_keep_their_buffers(run, native):
+    """Each of the two calls alone keeps everything that the launches read and write, whatever the caller drops and however often the
+    layer is bound again; nothing is kept once they are gone."""
+    run(("" if native else "sys.modules['paper_2605_06055_amd._marshal'] = None\n") + """
+lib, seen, answer = library()
+for which in (0, 1):
+    refs, at, held = [], [], []
+    l = layer(source_count=torch.zeros(2, 4, dtype=torch.int32), window_rows=10)
+    for n in range(2):
+        mine = torch.full((5, 16), float(n)), torch.zeros(5, 2, dtype=torch.int32), torch.ones(5, 2)
+        held.append(l.bind(*mine, stream=55)[which])
+        all = [*mine, l.window, l.expert_out, l.y, *(t for t in vars(l.plan).values() if t is not None)]
+        refs.append([weakref.ref(t) for t in all])
+        at.append(mine[0].data_ptr() if which == 0 else mine[2].data_ptr())
+        del mine, all
+    del l
+    gc.collect()
+    for n in range(2):
+        assert all_alive(refs[n])
+        held[n]()
+        assert seen[42 if which == 0 else 43] == at[n]
+    held.clear()
+    gc.collect()
+    assert not any(r() is not None for r in refs[0] + refs[1])
+""")
