@@ -50,9 +50,14 @@ class MoeLayer:
         caches while it runs (moe_plan_t.prefetch)."""
         if self.schedule == B.MOE_SCHEDULE_PREFILL:
             if self.prefetch_x:
-                self._plan_struct.prefetch = B._ptr(x)
-                self._plan_struct.prefetch_bytes = x.numel() * x.element_size()
-            B.moe_plan(self.shape, topk_idx, self._plan_struct, stream)
+                plan = self._plan_struct
+                plan.prefetch, plan.prefetch_bytes = B._ptr(x), x.numel() * x.element_size()
+                try:
+                    B.moe_plan(self.shape, topk_idx, plan, stream)
+                finally:                      # the structure outlives x
+                    plan.prefetch, plan.prefetch_bytes = None, 0
+            else:
+                B.moe_plan(self.shape, topk_idx, self._plan_struct, stream)
         B.moe_dispatch(self.shape, x, topk_idx, self._plan_struct, self.window, stream)
 
     def combine(self, topk_w, stream=None):

@@ -122,3 +122,27 @@ for which in (0, 1):
     gc.collect()
     assert not any(r() is not None for r in refs[0] + refs[1])
 """)
+
+
+def test_prefetch_is_named_for_one_call_only(run):
+    """The address of x goes to the plan call and does not stay behind for later calls, whose x may be another."""
+    run("""
+lib, seen, answer = library()
+at_plan = []
+l = layer()
+real = B.moe_plan
+B.moe_plan = lambda *a: (real(*a), at_plan.append((seen[8 + 13], seen[8 + 14])))[0]
+l.prefetch_x = True
+for code in (0, -3):
+    answer.value = code
+    try:
+        l.dispatch(x, ids, stream=55)
+    except moe.MoeError as e:
+        at_plan.append((seen[8 + 13], seen[8 + 14]))
+    answer.value = 0
+    assert at_plan.pop() == (x.data_ptr(), 5 * 16 * 4) and not at_plan
+    assert l._plan_struct.prefetch is None and l._plan_struct.prefetch_bytes == 0
+l.prefetch_x = False
+l.dispatch(x, ids, stream=55)
+assert at_plan.pop() == (0, 0)
+""")
