@@ -130,9 +130,8 @@ __global__ __launch_bounds__(BLOCK) void combine_rows_kernel(const u32x4 *__rest
 // 268 / 260.5, group-limited 32768 845 / 837.
 // K: the routing degree; G: its rows that are in flight together.  Degrees of 10 and 5 take this form too, the former 5 rows at a time:
 // us per combine, combine_rows_kernel / this with 2, 5, 8, 10 rows in flight: k = 10: H = 3456, T = 25255 341 / 381, 290, 304, 298; H = 2048,
-// T = 12000 92 / 113, 87, -, -.  us per layer: k = 10: H = 7168, T = 8000 414 / 389; H = 1032, T = 24000 253 / 236; k = 5: H = 7168, T = 8000 230 / 226;
-// H = 5120, T = 16000 358 / 351; not where more than an eighth of the padded columns is idle (H = 1600, T = 24000 163 / 168; H = 2176,
-// T = 6000 60.4 / 63.1).  k = 8 with 4 rows in flight: H = 4096, T = 16000 388 / 384, but Zipf H = 7168, T = 16384 710 / 721 and H = 640,
+// T = 12000 92 / 113, 87, -, -.  us per layer: k = 10: H = 7168, T = 8000 414 / 389; k = 5: H = 7168, T = 8000 230 / 226;
+// H = 5120, T = 16000 358 / 351; not where many of the padded columns are idle (see launch_combine).  k = 8 with 4 rows in flight: H = 4096, T = 16000 388 / 384, but Zipf H = 7168, T = 16384 710 / 721 and H = 640,
 // T = 28000 118 / 132; k = 6 with 3: 6 % slower.
 // Same arithmetic as combine_rows_kernel
 // (ascending j, one fma per placed branch, one rounding).  Units (token, column) are numbered token-major over
@@ -395,7 +394,11 @@ hipError_t launch_combine(const Dims &d, const void *expert_out, const float *W,
   // columns past the last whole wave of several tokens packed into one wave: H = 4104, k = 6 33.3 / 34.3 a combine, H = 640, k = 8 51 / 56.)
   const int cols_pad = (d.H16 + 63) / 64 * 64, waves = cols_pad / kWave;
   const bool threes = waves % 2 == 1 && waves % 3 == 0;
-  const bool held = d.k == 10 || d.k == 8 || d.k == 6 || (d.k == 5 && !threes && cols_pad * 7 <= d.H16 * 8);
+  // Degrees of 10 and 5 hold back only where few padded columns are idle (at most a third of the row, a seventh): us per combine, rows /
+  // held, k = 10, X of 100 MB: H = 520 217 / 264, 640 199 / 218, 704 198 / 205, 768 200 / 194, 1032 217 / 217, 1152 199 / 193, 1664 213 / 187; k = 5:
+  // H = 448 101.6 / 104.5, 480 108.6 / 102.3, 768 104.8 / 114.2, 896 105.5 / 103.6, 1792 110.1 / 100.8.
+  const bool held = d.k == 8 || d.k == 6 || (d.k == 10 && cols_pad * 3 <= d.H16 * 4) ||
+                    (d.k == 5 && !threes && cols_pad * 7 <= d.H16 * 8 && d.H16 >= 60);
   const long long units = (long long)d.T * cols_pad;
   if (!small && held && units < 0x7fffffffLL)
     return d.dtype == MOE_DTYPE_BF16

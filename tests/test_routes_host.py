@@ -1,0 +1,89 @@
+"""Which kernel a call takes where both of two forms would be right and only one is fast, seen without a GPU: a stand-in for the
+runtime's launch call notes the kernel's name and the workgroup.  The rules and their measurements stand beside the code."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+FAKE = r"""
+#define _GNU_SOURCE
+#include <dlfcn.h>
+#include <stddef.h>
+#include <stdint.h>
+#include <string.h>
+typedef struct { uint32_t x, y, z; } dim3;
+int fake_launches, fake_block;
+char fake_names[4096];
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipDeviceGetAttribute(int *v, int attr, int dev) { (void)attr; (void)dev; *v = 256; return 0; }
+int hipFuncSetAttribute(const void *kernel, int attr, int value) { (void)kernel; (void)attr; (void)value; return 0; }
+int hipLaunchKernel(const void *kernel, dim3 grid, dim3 block, void **args, size_t lds, void *stream) {
+  (void)grid; (void)args; (void)lds; (void)stream;
+  Dl_info at;
+  const char *name = dladdr(kernel, &at) && at.dli_sname ? at.dli_sname : "?";
+  if (strlen(fake_names) + strlen(name) + 2 < sizeof(fake_names)) strcat(strcat(fake_names, name), " ");
+  fake_block = (int)block.x;
+  ++fake_launches;
+  return 0;
+}
+"""
+
+PRELUDE = """
+import ctypes, sys
+sys.path.insert(0, {root!r})
+fake = ctypes.CDLL({so!r}, mode=ctypes.RTLD_GLOBAL)
+import paper_2605_06055_amd as moe
+from paper_2605_06055_amd.binding import _PlanStruct
+moe.load_library()
+X, K, W, WINDOW = 1 << 40, 1 << 36, 1 << 37, 1 << 44        # never dereferenced
+PLAN = _PlanStruct(expert_count=0x1000, rank_count=0x2000, expert_offset=0x3000, region_base=0x4000, send_idx=0x5000,
+                   row_map=0x6000, status=0x7000, workspace=0x8000, workspace_bytes=1 << 40)
+names = (ctypes.c_char * 4096).in_dll(fake, "fake_names")
+def shape(**kw):
+    return moe.MoeShape(**{{**dict(E=64, R=1, dtype=moe.MOE_DTYPE_BF16, schedule=moe.MOE_SCHEDULE_PREFILL), **kw}})
+def launched(call, *a):
+    ctypes.memset(names, 0, 4096)
+    call(*a, 0)
+    return names.value.decode().split(), ctypes.c_int.in_dll(fake, "fake_block").value
+def combine(H16, k, T=60000):
+    return launched(moe.moe_combine, shape(T=T, H=8 * H16, k=k), X, W, PLAN, WINDOW)[0][0]
+def plan(N, k, E):
+    return len(launched(moe.moe_plan, shape(T=N // k, H=8, k=k, E=E), K, PLAN)[0])
+def decode(N, k, E=64, H16=512, quant=False):
+    s = shape(T=N // k, H=8 * H16, k=k, E=E, schedule=moe.MOE_SCHEDULE_DECODE)
+    n, block = launched(moe.moe_dispatch_quant, s, X, K, PLAN, WINDOW, W) if quant else launched(moe.moe_dispatch, s, X, K, PLAN, WINDOW)
+    assert len(n) == 1
+    return ("histogram" if "decode_hist" in n[0] else "ballots"), block
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("fake_hip")
+    src, so = folder / "fake_hip.c", str(folder / "libfake_hip.so")
+    src.write_text(FAKE)
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-o", so, str(src), "-ldl"])
+
+    def child(body):
+        res = subprocess.run([sys.executable, "-c", PRELUDE.format(root=ROOT, so=so) + body], capture_output=True,
+                             text=True, timeout=300)
+        assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-3000:]
+    return child
+
+
+def test_combine_of_padded_rows(run):
+    """Degrees of 10 and 5 do not hold results back where too many of the padded columns are idle."""
+    run("""
+held = lambda *a: "combine_deferred" in combine(*a)
+for H16 in (65, 66, 72, 80, 88, 92, 95):
+    assert not held(H16, 10) and not held(H16, 5), H16
+for H16 in (96, 112, 128, 144, 160, 513, 896):
+    assert held(H16, 10), H16
+for H16 in (48, 52, 56, 129, 160):
+    assert not held(H16, 5), H16
+for H16 in (60, 64, 112, 128, 224, 449, 640, 641, 896):
+    assert held(H16, 5), H16
+""")
