@@ -313,6 +313,9 @@ bool plan_uses_workspace(int64_t N) { return N > (int64_t)MOE_PLAN_FUSED_MAX_TIL
 // a popular expert may have a large part of all branches: Zipf, 18 000 of degree 1, E = 16 7.5 / 8.6, of degree 3 7.0 / 7.2.
 static bool plan_in_one_launch(const Dims &d, int tiles) {
   if (!plan_uses_workspace(d.N)) return true;
+  // Few experts: the atomics of all workgroups meet in few words.  us per plan, two launches / one: E = 8: 16 000 branches 7.45 / 6.35,
+  // 20 000 7.45 / 7.3, 24 576 7.5 / 8.0, 28 600 7.45 / 8.9; E = 4: 13 000 7.35 / 7.0, 20 000 7.4 / 9.2; E = 12: 24 576 7.6 / 7.5, 28 600 7.6 / 8.1.
+  if (d.N > 2 * kPlanMinTile * d.E) return false;
   return d.k >= 4 && d.N <= 28 * kPlanMinTile && (d.order_tiles == 0 || d.order_tiles >= tiles);
 }
 

@@ -87,3 +87,13 @@ for H16 in (48, 52, 56, 129, 160):
 for H16 in (60, 64, 112, 128, 224, 449, 640, 641, 896):
     assert held(H16, 5), H16
 """)
+
+
+def test_plan_of_few_experts(run):
+    """A single launch counts all ids in every workgroup: not beyond 2048 branches an expert."""
+    run("""
+for k in (4, 8):
+    for N, E, launches in ((12288, 1, 1), (12296, 1, 2), (12296, 4, 2), (16384, 8, 1), (16392, 8, 2), (24576, 8, 2), (24576, 12, 1),
+                           (24584, 12, 2), (28672, 14, 1), (28672, 256, 1), (28680, 256, 2)):
+        assert plan(N, k, E) == launches, (N, k, E)
+""")
