@@ -691,18 +691,39 @@ hipError_t launch_dispatch(const Dims &d, const void *x, const PlanView &p, void
 }
 
 // Which kernel a decode batch takes: compares and ballots while the counting is small (fewer barriers), the histogram beyond.
-// us per dispatch, ballots / histogram, in replayed graphs on cold buffers:
-//   k = 8: H = 7168: T = 160 5.6 / 6.0, 192 6.9 / 6.6, 512 14.8 / 13.7; H = 5120 and 6144 (chunks of 5 and 6 waves): T = 256 6.4 / 6.5
-//          and 7.2 / 7.3, 320 7.7 / 7.6 and 8.7 / 8.3, 448 11.0 / 9.7 and 12.1 / 11.0; H = 2048: T = 192 5.0 / 4.2, 512 9.8 / 6.5;
-//   k = 5, 4, 3, 2, 1: H = 4096, T = 256 5.2 / 4.8, 4.7 / 4.5, 4.4 / 4.3, 3.9 / 4.0, 3.7 / 3.7; T = 1024 16.8 / 13.9, 14.6 / 9.7,
-//          12.3 / 8.0, 10.2 / 6.1, 7.7 / 5.3; H = 1024, k = 1, T = 5000 51.5 / 8.0;
-//   quantised: k = 8: H = 7168, T = 64 3.7 / 4.2, 128 4.9 / 4.8, 512 12.6 / 9.3; k = 1 to 5, H = 4096, T = 64 4.05 to 4.4 / 3.75 to 4.2.
+// us per dispatch, ballots / histogram, in replayed graphs on cold buffers, by the number of branches (E = 256, or 64 for degrees beyond 8):
+//   k = 8: H = 2048: 1408 4.7 / 4.3, 5000 12.4 / 7.6; H = 4096: 1152 4.75 / 4.6, 1408 4.95 / 4.9, 5000 15.2 / 10.7; H = 5120: 1408 5.2 / 5.4, 1536 5.7 / 5.6,
+//     3500 10.8 / 9.7; H = 7168: 1408 6.0 / 6.5, 1536 6.6 / 6.7, 1700 7.2 / 7.2, 2304 9.4 / 8.8; H = 10 240: 1408 7.9 / 8.0, 1700 10.6 / 9.1; H = 14 336: 1536
+//     10.4 / 11.0, 1700 12.9 / 12.7.  More experts, H = 7168: E = 512: 1900 7.7 / 7.9, 2304 9.4 / 9.0; E = 1024: 2304 9.4 / 9.3, 3000 11.1 / 11.2
+//   k = 6: H = 4096: 1404 5.9 / 5.0; H = 7168: 2304 9.4 / 9.9, 3500 13.0 / 13.0, 4092 15.7 / 14.3; H = 14 336: 1700 12.1 / 12.5, 3500 22.4 / 24.0, 4092 25.9 / 25.0
+//   k = 10, H = 7168: 1400 7.2 / 6.6; k = 16: H = 2048: 1152 5.2 / 4.5; H = 7168: 1536 6.1 / 6.6, 1700 8.0 / 7.1
+//   k = 5: H = 2048 (five slots for four waves): 600 4.2 / 4.3, 1020 4.35 / 4.6, 1400 5.5 / 4.9; E = 512: 1280 4.85 / 5.0, 1410 5.5 / 5.3; H = 4096: 600
+//     4.45 / 4.35, 2300 7.45 / 6.45; H = 7168, E = 1024: 640 5.1 / 5.7, 1280 6.6 / 6.8, 1700 8.4 / 8.1
+//   k = 4, 3, 2, 1, H = 4096: 600 4.45 / 4.35, 4.45 / 4.35, 4.85 / 4.45, 5.65 / 4.7; 5000 20 / 11.5, 23 / 15, 31 / 12.4, 54 / 15.4; k = 4, H = 7168, E = 1024: 1024
+//     5.6 / 6.1, 1700 8.3 / 8.1
+//   quantised: k = 8: H = 2048: 1152 4.45 / 4.6, 1280 4.5 / 4.55, 1536 4.8 / 4.6; H = 7168: 640 4.6 / 4.5, 1152 5.85 / 5.55, E = 1024: 1280 5.9 / 6.3, 1536 6.6 / 6.4;
+//     k = 6, H = 2048: 1152 4.5 / 4.55, 1278 4.8 / 4.6; k = 10, H = 2048: 640 4.35 / 4.5, 1020 4.9 / 4.6; k = 5, H = 2048: 320 4.3 / 4.45, 640 4.7 / 4.6, E = 512: 640
+//     4.8 / 5.2, 1025 5.65 / 5.3; k = 4, H = 4096: 128 4.4 / 4.15, 4096 14.7 / 7.8; k = 2, H = 2048, E = 512: 128 4.05 / 4.25, 320 4.4 / 4.4, 640 5.1 / 4.65
+// (Rows of 1024 to 1280 vectors: where the workgroups of 5 waves fill the compute units unevenly the histogram loses: k = 8, 2600 branches 13.2 / 14.8.)
 // With several source ranks always the histogram, to which the other ranks' rows are added.
 static bool decode_by_hist(const Dims &d, const PlanView &p, bool quant) {
   if (p.source_count) return true;
-  if (d.k < 6) return quant || d.N > 600;
-  if (quant) return d.N > 1024;
-  return d.N > (d.H16 > 512 && d.H16 <= 832 ? 2304 : 1408);
+  const bool wide = d.H16 > 1024;
+  const int more = std::max(0, d.E - 256);            // experts past 256: the counts take longer to clear, scan and sum
+  if (quant) {
+    if (d.k == 5 && d.H16 <= 256) return d.N > 600 + more;
+    if (d.k < 6) return wide || more == 0 || d.N > 256;
+    if (d.k > 8 || !(d.H16 <= 256 || (d.E > 512 && !wide))) return d.N > 1024;
+    return d.N > (d.k == 6 ? 1152 : 1280);
+  }
+  if (d.k == 5 && d.H16 <= 256) return d.N > 1152 + more;
+  if (d.k < 6) return d.N > 600 + (d.E > 512 && d.k >= 3 && (d.k == 5 || !wide) ? more : 0);
+  // rows of which the ballots' workgroups of 1024 vectors leave a large part idle
+  const bool narrow = d.H16 <= 512 || (wide && d.H16 <= 1280);
+  if (d.k > 8) return d.N > (narrow || d.k < 12 ? 1408 : 1536);
+  if (narrow) return d.N > 1408;
+  if (d.k == 6 && d.H16 > 832) return d.N > 3584;
+  return d.N > 1536 + 2 * more;
 }
 
 template <int V, int TT, int G, bool QUANT>

@@ -97,3 +97,22 @@ for k in (4, 8):
                            (24584, 12, 2), (28672, 14, 1), (28672, 256, 1), (28680, 256, 2)):
         assert plan(N, k, E) == launches, (N, k, E)
 """)
+
+
+def test_decode_kernel(run):
+    """Compares and ballots up to a number of branches, the histogram beyond; one line of a rule each."""
+    run("""
+for k, E, H16, quant, last in ((8, 256, 512, 0, 1408), (8, 512, 512, 0, 1408), (8, 256, 640, 0, 1536), (8, 256, 896, 0, 1536), (7, 512, 896, 0, 2044),
+                               (8, 512, 896, 0, 2048), (8, 1024, 896, 0, 3072), (8, 256, 1280, 0, 1408), (8, 256, 1792, 0, 1536),
+                               (6, 256, 832, 0, 1536), (6, 256, 896, 0, 3582), (6, 64, 1792, 0, 3582), (6, 256, 1280, 0, 1404),
+                               (10, 64, 896, 0, 1400), (16, 64, 896, 0, 1536), (16, 64, 256, 0, 1408),
+                               (5, 256, 256, 0, 1150), (5, 512, 256, 0, 1405), (5, 256, 264, 0, 600), (5, 512, 896, 0, 600), (5, 1024, 896, 0, 1365),
+                               (4, 512, 512, 0, 600), (4, 1024, 512, 0, 1368), (4, 1024, 1032, 0, 600), (2, 1024, 512, 0, 600), (1, 256, 512, 0, 600),
+                               (8, 256, 256, 1, 1280), (6, 256, 256, 1, 1152), (8, 256, 512, 1, 1024), (8, 1024, 512, 1, 1280), (8, 1024, 1032, 1, 1024),
+                               (10, 64, 256, 1, 1020), (5, 256, 256, 1, 600), (5, 512, 256, 1, 855), (5, 256, 264, 1, 0), (5, 512, 264, 1, 255),
+                               (4, 256, 256, 1, 0), (4, 512, 256, 1, 256), (2, 512, 1032, 1, 0)):
+    for N in ([last] if last else []) + [k]:
+        if N <= last:
+            assert decode(N, k, E, H16, quant)[0] == "ballots", (k, E, H16, quant, N)
+    assert decode(last + k, k, E, H16, quant)[0] == "histogram", (k, E, H16, quant, last)
+""")
