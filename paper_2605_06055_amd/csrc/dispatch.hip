@@ -15,13 +15,6 @@
 
 namespace moe_rbf {
 
-#ifndef MOE_DECODE_BLOCK
-#define MOE_DECODE_BLOCK 512
-#endif
-#ifndef MOE_DECODE_VEC
-#define MOE_DECODE_VEC 1
-#endif
-
 constexpr int kSlices = 8;   // column slices per row = XCDs per device
 constexpr int kLine = 8;     // 16-byte vectors of a 128-byte cache line
 constexpr int kWarmTokens = 8;
@@ -180,7 +173,7 @@ __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__rest
 //
 // Row of branch (t,j) with expert e:  region/expert base + #{ids i : lo <= K_i < e} + #{i < t*k+j : K_i = e}
 // (lo = 0 and base = 0 for tight windows; lo = first expert of e's rank and base = rank*stride otherwise).
-// Both terms are plain counts over the <= 8192 routing ids of the batch, so a payload workgroup gets
+// Both terms are plain counts over the routing ids of the batch (at most 3584 here, see decode_by_hist), so a payload workgroup gets
 // them with compares on the ids it holds in registers, wave ballots (the counts land in scalar
 // registers) and one LDS exchange between its waves: no histogram, no scan, one barrier.  The two
 // counts of a slot travel packed in one word (low 16 bits: ids below e; high 16 bits: equal ids in
@@ -792,20 +785,19 @@ hipError_t launch_decode_dispatch(const Dims &d, const void *x, const int32_t *K
                         : launch_decode_hist<2, false>(d, x, K, p, window, nullptr, s);
   // With a routing degree of at least 6 the slots of a token are split over 4 workgroups of 8 waves (2 slots
   // each), or over 2 (4 slots each) once the batch is so large that the counting, which every workgroup of a
-  // token repeats over all ids, outweighs the better spread of the stores.  Measured, k = 8, us per dispatch
-  // (one workgroup per token and chunk / two groups / four groups):
+  // token repeats over all ids, outweighs the better spread of the stores (degree 6, and batches of many experts).
+  // Measured, k = 8, us per dispatch (one workgroup per token and chunk / two groups / four groups):
   //   H = 7168: T = 16: 3.9 / 3.5 / 3.5, T = 64: 4.2 / 4.0 / 4.1, T = 128: 5.4 / 4.9 / 4.8, T = 144: 6.0 / 5.5 / 5.2,
-  //             T = 256: 8.8 / 8.0 / 7.7, T = 512: 16.3 / 14.6 / 14.5;
-  //   H = 4096: T = 128: 4.7 / 4.2 / 4.2, T = 256: 6.3 / 5.7 / 6.2, T = 512: 11.0 / 11.2 / 12.4.
+  //             T = 256: 8.8 / 8.0 / 7.7;  H = 4096: T = 128: 4.7 / 4.2 / 4.2, T = 256: 6.3 / 5.7 / 6.2.
   if (d.k >= 6) {
     if (d.N <= 1536) return launch_decode_dispatch_shape<512, 2, 2, 4>(d, x, K, p, window, s);
     return launch_decode_dispatch_shape<512, 2, 4, 2>(d, x, K, p, window, s);
   }
   // Few slots per token: one workgroup per token and chunk.  Every workgroup of a token repeats the
-  // counting, so from about 900 branches on two vectors per lane (half as many chunks) win.
-  if (d.H16 > MOE_DECODE_BLOCK && d.N >= 896)
-    return launch_decode_dispatch_shape<MOE_DECODE_BLOCK, 2, 8, 1>(d, x, K, p, window, s);
-  return launch_decode_dispatch_shape<MOE_DECODE_BLOCK, MOE_DECODE_VEC, 8, 1>(d, x, K, p, window, s);
+  // counting, so from about 900 branches on (which come here with more than 512 experts) two vectors per lane, half as many
+  // chunks, win.
+  if (d.H16 > 512 && d.N >= 896) return launch_decode_dispatch_shape<512, 2, 8, 1>(d, x, K, p, window, s);
+  return launch_decode_dispatch_shape<512, 1, 8, 1>(d, x, K, p, window, s);
 }
 
 // Whole-row workgroup shapes (threads, vectors per thread) covering H16 <= 4096, for the quantised kernels.
@@ -844,18 +836,15 @@ static hipError_t launch_decode_quant_shape(const Dims &d, const void *x, const 
                 window_scale, d, p, 1, per_group);
 }
 
-// Slot groups as in launch_decode_dispatch.  Measured, k = 8, us per quantised dispatch, one workgroup of
-// 1024 threads per token / this rule: H = 7168: T = 32: 5.1 / 3.8, T = 128: 6.0 / 5.1, T = 256: 7.4 / 6.9;
-// H = 4096, T = 128: 5.3 / 4.5; H = 2048, T = 128: 5.1 / 4.2.
+// Slot groups as in launch_decode_dispatch; no batch of more than 1280 branches comes here, and of smaller degrees only rows of up to 1024
+// vectors (see decode_by_hist).  Measured, k = 8, us per quantised dispatch, one workgroup of 1024 threads per token / this rule: H = 7168:
+// T = 32: 5.1 / 3.8, T = 128: 6.0 / 5.1; H = 4096, T = 128: 5.3 / 4.5; H = 2048, T = 128: 5.1 / 4.2.
 template <int B, int V>
 static hipError_t launch_decode_quant_bv(const Dims &d, const void *x, const int32_t *K, const PlanView &p,
                                          void *window_q, float *window_scale, hipStream_t s) {
-  if (d.k >= 6) {
-    if (d.N <= 1536)
-      return launch_decode_quant_shape<B, V, 2, 4>(d, x, K, p, window_q, window_scale, s);
-    return launch_decode_quant_shape<B, V, 4, 2>(d, x, K, p, window_q, window_scale, s);
-  }
-  return launch_decode_quant_shape<B, V, 8, 1>(d, x, K, p, window_q, window_scale, s);
+  if constexpr (B < 1024)
+    if (d.k < 6) return launch_decode_quant_shape<B, V, 8, 1>(d, x, K, p, window_q, window_scale, s);
+  return launch_decode_quant_shape<B, V, 2, 4>(d, x, K, p, window_q, window_scale, s);
 }
 
 hipError_t launch_decode_dispatch_quant(const Dims &d, const void *x, const int32_t *K, const PlanView &p,

@@ -28,7 +28,6 @@ constexpr int kPlanWaves = kPlanBlock / kWave;
 constexpr int kPlanMinTile = kPlanBlock;          // one branch per thread
 constexpr int kPlanMaxTiles = 512;
 constexpr int kCopies = 4;                        // of each count of a single-launch plan
-typedef int i32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int sum4(const int *p) {
   const i32x4 v = *(const i32x4 *)p;
   return (v[0] + v[1]) + (v[2] + v[3]);
@@ -106,7 +105,7 @@ __global__ __launch_bounds__(kPlanBlock) void plan_rank_kernel(const int32_t *__
   int *pre = st_excl + E + 1;          // [E]    branches of the source ranks below this one (several sources only)
   int *post = pre + E;                 // [E]    ... above this one
   int *misc = post + E;                // [2]    scratch
-  int *wcur = misc + 2;                // [waves][E+1] segment histograms, then running s per wave segment.  The odd row length
+  int *wcur = misc + 2;                // [waves][E|1] segment histograms, then running s per wave segment.  The odd row length
   const int wrow = E | 1;              // spreads an expert's 16 counts over the LDS banks
   __shared__ unsigned long long others_rows;   // rows of the other source ranks, 64-bit
   const int tid = threadIdx.x, wave = uniform(tid / kWave), lane = tid % kWave;

@@ -266,7 +266,8 @@ __device__ __forceinline__ i32x4 load_ids(const int32_t *__restrict__ K, int q, 
 
 // One workgroup builds the whole histogram from the routing ids themselves (counts only: LDS integer
 // atomics) and writes the tables.  Used where no per-tile histograms exist: the fused decode dispatch and
-// the single-launch plan.  LDS: 4E + 3 ints.  Must be called by every thread of the workgroup.
+// the single-launch plan.  LDS: 4E + 3 ints.  Must be called by every thread of the workgroup; with several source ranks one of at least
+// 512 threads (SourceSums), as the plan and the histogram kernel of the decode dispatch have.
 // The launch waits for this workgroup, so the next trip's ids are requested ahead of this one's counting.
 __device__ __forceinline__ void tables_from_ids_block(const int32_t *__restrict__ K, const Dims &d, const PlanView &p,
                                                     int *lds) {
