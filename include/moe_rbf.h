@@ -60,8 +60,8 @@ enum moe_status {
   MOE_ERR_ALIGN = -3,      /* H*elem_bytes not a multiple of 16, or a device pointer not 16-byte aligned */
   MOE_ERR_OVERFLOW = -4,   /* T*k or the window row count does not fit in int32, or a launch grid would not:
                               8*T*k and T*ceil(H*elem_bytes/1024) must also stay below 2^31 */
-  MOE_ERR_WORKSPACE = -5,  /* plan->workspace missing or smaller than moe_workspace_bytes (only when moe_plan
-                              uses it: batches of more than MOE_PLAN_SINGLE_LAUNCH_MAX_BRANCHES branches) */
+  MOE_ERR_WORKSPACE = -5,  /* plan->workspace missing or smaller than moe_workspace_bytes (only where moe_plan
+                              asks for it: batches of more than MOE_PLAN_SINGLE_LAUNCH_MAX_BRANCHES branches) */
   MOE_ERR_LAUNCH = -6,     /* the HIP runtime refused a kernel launch */
   MOE_ERR_OVERLAP = -7     /* x overlaps the window, or y overlaps expert_out (byte ranges known on the host) */
 };
@@ -69,7 +69,9 @@ enum moe_status {
 #define MOE_MAX_EXPERTS 1024
 #define MOE_AUTO_DECODE_MAX_BRANCHES 5120
 #define MOE_DECODE_MAX_BRANCHES 8192
-#define MOE_PLAN_SINGLE_LAUNCH_MAX_BRANCHES 12288 /* up to here moe_plan is one launch and ignores plan->workspace */
+#define MOE_PLAN_SINGLE_LAUNCH_MAX_BRANCHES 12288 /* up to here moe_plan is one launch and ignores plan->workspace; beyond, it asks
+                                                     for the workspace, also for those batches of up to 28672 branches that it
+                                                     plans in one launch without touching it */
 #ifndef MOE_PREFETCH_MAX_BYTES
 #define MOE_PREFETCH_MAX_BYTES (224u << 20)       /* what moe_plan reads of plan->prefetch at most (the Infinity Cache holds 256 MB) */
 #endif
@@ -130,11 +132,12 @@ typedef struct moe_plan_t {
                                     The result of moe_dispatch is the same with or without it.  Content and use are
                                     decided by the shape alone; a DECODE dispatch leaves a valid list too.
                                     moe_dispatch_quant does not read it: a caller that only dispatches quantised rows
-                                    passes NULL and saves the plan 0.4 to 3 us (5 000 to 130 000 branches). */
+                                    passes NULL and saves the plan 0.4 to 1 us (5 000 to 130 000 branches; 1.8 us where
+                                    it is then planned in one launch instead of two). */
   const void *prefetch;    /* optional (NULL: none), read by moe_plan / moe_plan_static only: device memory that the
                                     call should pull into the cache hierarchy while it plans, normally the x of the
                                     moe_dispatch that follows.  The plan kernels are latency-bound and leave the
-                                    memory system idle; spare workgroups of the second plan launch read this range
+                                    memory system idle; spare workgroups of the plan's last launch read this range
                                     (nothing is written, no result depends on it).  A dispatch whose token rows are
                                     not cached runs 15-35 % slower (they are fetched in small pieces while the chip
                                     is saturated with writes), so a caller that cannot tell whether x is still

@@ -726,7 +726,9 @@ static hipError_t launch_decode_hist_shape(const Dims &d, const void *x, const i
   // chunks of nearly the same length, and as many waves as a chunk needs, but enough to count the ids
   const int chunks = (d.H16 + kMost * V - 1) / (kMost * V);
   const int width = ((d.H16 + chunks - 1) / chunks + kLine - 1) / kLine * kLine;
-  // (7 waves: 8.  H = 7168, T = 512 14.3 / 13.6 us; but 5 and 6 waves stay: H = 5120, T = 400 9.2 / 10.9)
+  // (7 waves: 8, us per dispatch, 7 / 8 waves, k = 8: H = 3584: 2600 branches 6.7 / 6.3, 4096 9.0 / 8.4; H = 6400, 4096 13.1 / 12.6; H = 7168: 2048 8.1 / 7.8, 4096
+  // 14.4 / 13.8; H = 14 336, 4096 25.5 / 24.5; k = 2, H = 7168, 4096 17.4 / 16.0; equal elsewhere.  5 and 6 waves stay: k = 8: H = 5120, 3200 9.1 / 10.4, H = 6144,
+  // 3200 10.5 / 11.7, H = 10 240, 1600 8.8 / 10.0; but 8 would do better in rows of one vector a lane: H = 2560, 2600 6.0 / 5.3, H = 3072, 4096 8.2 / 7.6)
   int threads = std::max(p.source_count ? 512 : 256, ((width + V - 1) / V + kWave - 1) / kWave * kWave);
   if (threads == 7 * kWave) threads = 8 * kWave;
   const int per_group = (d.k + G - 1) / G;

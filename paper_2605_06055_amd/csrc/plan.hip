@@ -34,8 +34,10 @@ __device__ __forceinline__ int sum4(const int *p) {
 }
 
 // Every pass-2 workgroup sums the histograms of all tiles, so many tiles cost more than long ones from about
-// 200 000 branches on.  Measured, us per plan with tiles of 1024 / 2048 / 4096 branches: 32 768 branches
-// 9.5 / 10.7 / 13.3, 131 072: 11.9 / 12.1 / 13.6, 262 144: 15.1 / 11.0 / 12.5.
+// 200 000 branches on (from fewer with many experts, from more with few).  Measured, us per plan without the order list with tiles of
+// 1024 / 2048 / 4096 branches: E = 256: 32 768 branches 9.0 / 10.0 / 12.5, 131 072 11.5 / 11.0 / 12.9, 196 608 12.5 / 11.7 / 13.4, 262 144 19.9 / 12.9 /
+// 13.7, 400 000 28.5 / 14.1 / 14.5, 524 288 42 / 21.2 / 15.9; E = 64: 131 072 8.4 / 9.2 / 11.3, 196 608 8.9 / 9.8 / 11.8, 262 144 12.8 / 9.7 / 11.6;
+// E = 1024: 65 536 15.6 / 15.1 / 16.5, 131 072 20.4 / 17.8 / 18.0, 262 144 47 / 22.3 / 20.3.
 int plan_tile_size(int64_t N) {
   int64_t tile = N >= 196608 ? 2 * kPlanMinTile : kPlanMinTile;
   while ((N + tile - 1) / tile > kPlanMaxTiles) tile *= 2;
@@ -307,7 +309,7 @@ hipError_t launch_plan_empty(const Dims &d, const PlanView &p, hipStream_t s) {
 bool plan_uses_workspace(int64_t N) { return N > (int64_t)MOE_PLAN_FUSED_MAX_TILES * kPlanMinTile; }
 
 // Batches planned with one launch: all that need no workspace, and further ones whose order list is one stretch (such a plan sorts
-// the whole batch).  us per plan, two launches / one: k = 8: 17 920 branches, E = 256 9.0 / 7.6, Zipf 8.4 / 7.3; k = 6: 18 006, E = 96
+// the whole batch) and whose experts are not too few.  us per plan, two launches / one: k = 8: 17 920 branches, E = 256 9.0 / 7.6, Zipf 8.4 / 7.3; k = 6: 18 006, E = 96
 // 8.1 / 7.1, 24 576, E = 256 8.7 / 7.6, E = 64 7.3 / 6.9; 28 672, E = 96 7.85 / 7.85, E = 256 8.85 / 8.3; 32 768 9.2 / 9.0; degrees below 4, where
 // a popular expert may have a large part of all branches: Zipf, 18 000 of degree 1, E = 16 7.5 / 8.6, of degree 3 7.0 / 7.2.
 static bool plan_in_one_launch(const Dims &d, int tiles) {
@@ -334,6 +336,9 @@ static bool plan_in_one_launch(const Dims &d, int tiles) {
 //   for rows of 12 KB or more while X holds at most 96 MiB and the window at most 770 MiB,
 //   for narrower rows with windows of up to 1100 MiB,
 // and for larger X with bulk reads (order_streams_x).
+// (All layers here were measured with the plan as it was before its tile histograms were packed, on both sides.  The list cost that plan 1.3 us
+// at 32 768 branches and 2.8 at 131 072; it costs the present one 0.4 to 0.65 up to 65 536, 1.0 at 131 072, 1.4 at 262 144, so both sides are 1 to 4 us
+// shorter now and the list's by 0.7 to 2 us more.)
 // Rows of 2 to 4 KB, us per layer with the list / in token order: H = 2048: T = 8192 105.4 / 108.0, 16384 197.0 / 204.3,
 // 32768 388.6 / 407.6; H = 1024: T = 16384 110.0 / 113.4, 65536 405.7 / 426.0.  With slices cut at cache lines and units
 // packed side by side the same holds for most widths from 1.5 KB on (sum of the kernels' us): H = 2560, T = 11468
