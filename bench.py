@@ -545,8 +545,7 @@ def main():
                                         "identical routing is reused (dispatch reads the stored row map): a cached "
                                         "mode for repeated routing, not the figure for fresh routing",
                          "us_per_layer_eager": round(de["us_per_layer"], 2),
-                         "eager_launch": "kernel by kernel from Python with pre-marshalled ctypes arguments "
-                                         "(MoeLayer.bind); marshalling per call would cost ~7 us per launch",
+                         "eager_launch": "kernel by kernel from Python, calls bound once (MoeLayer.bind)",
                          "cache": "cold: 20 disjoint buffer sets (660 MB) rotated so no step finds its lines in "
                                   "the 256 MB Infinity Cache",
                          "kernels": rounded(d["kernels"])}
