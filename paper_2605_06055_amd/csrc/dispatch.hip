@@ -17,7 +17,6 @@ namespace moe_rbf {
 
 constexpr int kSlices = 8;   // column slices per row = XCDs per device
 constexpr int kLine = 8;     // 16-byte vectors of a 128-byte cache line
-constexpr int kWarmTokens = 8;
 
 // Both prefill kernels split a destination row into 8 column slices, one per XCD, cut at cache lines of the
 // DESTINATION: a line that two XCDs write halves of leaves two L2s as partial writes, and that costs far more than
@@ -68,6 +67,24 @@ __device__ __forceinline__ size_t row_offset(int row, int H16) {
   return (size_t)((unsigned long long)(unsigned)row * (unsigned)H16);
 }
 
+// Column of vector l of slice c, for slices that are all equal: pieces of `piece` vectors (2^shift, or the whole slice with
+// shift = 31) in turn over the slices.
+// With pieces of the largest power of two that divides the slice an XCD writes the same few address bits in every row (a row
+// being a whole number of 8 pieces), so a DRAM page is written by one XCD.  Slices of another length are not in step with the pages:
+// each is written by several XCDs, which do not run in step either.  Plain fills in order, 2 GB, an XCD owning every 8th block: 256
+// bytes 6.1 TB/s, 512 7.0, 1024 7.35, 2048 6.7, 4096 7.2, but 768 5.4, 1536 5.0, 1792 5.3, 3584 5.3, whatever the occupancy.
+// us per dispatch along the list, slices in one block / in pieces, k = 8: X of 58 MB: H = 12288 (1 KB) 77.3 / 73.8, 6144 (512 bytes) 80.5 /
+// 75.1, 14336 79.2 / 75.6, 10240 79.1 / 76.7; 256 bytes: 7168 82.3 / 79.7, 3072 81.7 / 77.3, 5120 80.6 / 79.5, 9216 79.8 / 77.4; 128 bytes: 2560
+// 82.4 / 86.0, 4608 80.4 / 85.2, 7680 82.2 / 86.6 (but 3584 84.6 / 80.8).  With bulk reads, X of 100, 150, 235 MB: 12288 142 / 133, 235 / 208, 386 /
+// 344; 6144 151 / 139, 252 / 234, 417 / 374; 14336 160 / 142, 251 / 232, 357 / 347; 7168 161 / 156, 254 / 255, 384 / 379; 5120 153 / 144, 253 /
+// 254, 401 / 402; 3072 150.5 / 153.7, 255 / 262, 388 / 395 (so rows under 8 KB keep one block there).
+// Larger pieces than divide the row, owned by address all the same, are needed by 2 to 8 XCDs for each token: H = 7168 82 / 104, 119, 125
+// (with stretches shortened to what L2 then holds 87, 97, 112).  Other kinds of stores, which fills like (ordinary, sc1, sc0 sc1 6.2 to
+// 7.3 TB/s along the list's runs, nt 5.0), push X out of L2: 148 us.
+__device__ __forceinline__ int slice_col(int c, int l, int piece, int shift) {
+  return (int)__umul24(l >> shift, piece * kSlices) + (int)__umul24(c, piece) + (l & (int)((1u << shift) - 1u));
+}
+
 // Prefill dispatch, one unit per (branch, column slice).  LIST: along the plan's order list, unit p copies a slice of
 // X[token] to window[row] for the p-th (token, row) pair.  The pairs are sorted by row inside stretches of tokens whose X
 // slices fit the L2 of an XCD, so consecutive workgroups of an XCD write consecutive rows of one expert block and re-read
@@ -82,7 +99,12 @@ __device__ __forceinline__ size_t row_offset(int row, int H16) {
 // stretches, and the first warm_blocks workgroups of each read the stretch's X, every XCD the slices that its units are
 // about to copy.  The list asks for a token's row at k scattered moments while the chip is saturated with writes; what is
 // not cached then comes in 1 KB pieces, and the write stream waits behind them.  Read in bulk, 24 MB at a time and just
-// before it is used, X costs little more than its bytes.  Nothing waits for the reads: they are a hint.
+// before it is used, X costs little more than its bytes.  Nothing waits for the reads: they are a hint.  A unit reads one token:
+// the readers then fill all wave slots of the chip, and the copies behind them start when X is there.  With 8 tokens a unit they held
+// 12 slots of 32, and the copies in the others asked for X in random order in the meantime; the gap in the stores at each stretch was
+// 6.4 us for 24 MB.  us per dispatch, X not cached, 8 tokens / 1 (4, 2: in between): group-limited T = 32768, H = 4096 449 / 426;
+// T = 24000 288 / 278; H = 6144, T = 12160 263 / 252; H = 2560, T = 45888 427 / 406; H = 7168: T = 16384 395 / 384, k = 4, T = 10463 148 /
+// 141; H = 4104, T = 14000 220 / 208; H = 7400, T = 9000 223 / 214.
 // us per layer, token order / list / list with bulk reads, X not cached when the layer starts: H = 7168: T = 8192 485 / 420 /
 // 383, 13000 760 / 699 / 602, Zipf 16384 933 / 812 / 725; H = 8192, T = 12000 768 / 656 / 609; H = 4096: T = 24000 633 / 683 /
 // 605, 11000 294 (list) / 268; H = 3072, k = 10, T = 32768 1087 / 908 / 799; H = 4096, k = 3, T = 16000 263 / 212 / 188; X
@@ -102,7 +124,7 @@ __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__rest
                                                              const int32_t *__restrict__ entries,
                                                              u32x4 *__restrict__ window, int k, int H16, int misalign,
                                                              int N, int lanes, unsigned magic, int U, int T,
-                                                             int warm_blocks, int stretch) {
+                                                             int warm_blocks, int stretch, int piece, int shift) {
   typedef int i32x2 __attribute__((ext_vector_type(2)));
   const int unit = ALONE ? 0 : (int)__umulhi(threadIdx.x, magic);          // threadIdx.x / lanes
   const int lane = (int)threadIdx.x - (int)__umul24(unit, lanes);
@@ -110,21 +132,15 @@ __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__rest
   if (WARM) {
     stretch_start = (int)blockIdx.y * stretch;
     if (block < warm_blocks) {                                 // warm_blocks is a multiple of 8: XCD = block % 8
-      const int first = stretch_start / k + ((block / kSlices) * U + unit) * kWarmTokens;
-      const int last = min(min(first + kWarmTokens, (stretch_start + stretch + k - 1) / k), T);
-      const int n = (H16 + kLine - 1) / kLine;
-      u32x4 w[kWarmTokens];
-#pragma unroll
-      for (int i = 0; i < kWarmTokens; ++i) {
-        const int c = (block + (ROTATE ? first + i : 0)) % kSlices;
-        const int cn = (int)__umul24(c, n);
-        const int x = (cn >> 3) * kLine + lane, stop = min(((cn + n) >> 3) * kLine, H16);
-        w[i] = first + i < last && x < stop ? X[row_offset(first + i, H16) + (unsigned)x] : u32x4{0u, 0u, 0u, 0u};
+      const int t = stretch_start / k + (block / kSlices) * U + unit;
+      const int last = min((stretch_start + stretch + k - 1) / k, T);
+      const int c = (block + (ROTATE ? t : 0)) % kSlices;
+      const int n = (H16 + kLine - 1) / kLine, cn = (int)__umul24(c, n);
+      const int x = ROTATE ? (cn >> 3) * kLine + lane : slice_col(c, lane, piece, shift);
+      if (t < last && (ROTATE ? x < min(((cn + n) >> 3) * kLine, H16) : lane < H16 / kSlices)) {
+        const unsigned used = X[row_offset(t, H16) + (unsigned)x][0];
+        asm volatile("" ::"v"(used));    // the load is kept although nothing uses its value
       }
-      unsigned used = 0;
-#pragma unroll
-      for (int i = 0; i < kWarmTokens; ++i) used |= w[i][0];
-      asm volatile("" ::"v"(used));      // the loads are kept although nothing uses their values
       return;
     }
     block -= warm_blocks;
@@ -149,13 +165,18 @@ __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__rest
   }
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
-    const int a = ALIGNED ? 0 : (misalign + (int)((unsigned)row[q] * (unsigned)H16)) & (kLine - 1);
     const int c = (blockIdx.x + (ROTATE ? t[q] : 0)) % kSlices;
-    const int n = (a + H16 + kLine - 1) / kLine;
-    const int cn = (int)__umul24(c, n);
-    col[q] = (cn >> 3) * kLine - a + lane;                     // below 0: the line's part in front of the row
-    end[q] = min(((cn + n) >> 3) * kLine - a, H16);
-    if (!ALIGNED && col[q] < 0) col[q] += lanes;               // (past the slice, unless it is longer than a workgroup)
+    if (ROTATE) {
+      const int a = ALIGNED ? 0 : (misalign + (int)((unsigned)row[q] * (unsigned)H16)) & (kLine - 1);
+      const int n = (a + H16 + kLine - 1) / kLine;
+      const int cn = (int)__umul24(c, n);
+      col[q] = (cn >> 3) * kLine - a + lane;                   // below 0: the line's part in front of the row
+      end[q] = min(((cn + n) >> 3) * kLine - a, H16);
+      if (!ALIGNED && col[q] < 0) col[q] += lanes;             // (past the slice, unless it is longer than a workgroup)
+    } else {
+      col[q] = slice_col(c, lane, piece, shift);
+      end[q] = lane < H16 / kSlices ? H16 : 0;
+    }
     if ((t[q] | row[q]) < 0) end[q] = 0;                       // nothing to do
     if (col[q] < end[q]) v[q] = X[row_offset(t[q], H16) + (unsigned)col[q]];
   }
@@ -163,9 +184,15 @@ __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__rest
   for (int q = 0; q < Q; ++q) {
     if (col[q] >= end[q]) continue;
     store_stream(window + (row_offset(row[q], H16) + (unsigned)col[q]), v[q]);
-    if (Q == 1)                                                // slices longer than a workgroup
+    if (Q == 1 && ROTATE) {                                    // slices longer than a workgroup
       for (int x = col[q] + lanes; x < end[q]; x += lanes)
         store_stream(window + (row_offset(row[q], H16) + (unsigned)x), X[row_offset(t[q], H16) + (unsigned)x]);
+    } else if (Q == 1) {
+      for (int l = lane + lanes; l < H16 / kSlices; l += lanes) {
+        const unsigned x = (unsigned)slice_col((int)blockIdx.x % kSlices, l, piece, shift);
+        store_stream(window + (row_offset(row[q], H16) + x), X[row_offset(t[q], H16) + x]);
+      }
+    }
   }
 }
 
@@ -579,18 +606,22 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
   if (warm) {
     stretch = d.order_tiles * plan_tile_size(d.N);
     const int tokens = stretch / d.k + 2;                      // a stretch may begin and end inside a token
-    warm_blocks = (tokens + U * kWarmTokens - 1) / (U * kWarmTokens) * kSlices;
+    warm_blocks = (tokens + U - 1) / U * kSlices;
     warm_grid = warm_blocks + ((int64_t)stretch + U * Q - 1) / (U * Q) * kSlices;
     warm = (uint64_t)warm_grid * (uint64_t)(U * lanes) <= kMostThreads;        // (not so from a few thousand branches a token on)
   }
   const bool alone = list && aligned && !warm && lanes > 96 && lanes <= 112;
   if (alone) U = 1, lanes = 128;
+  // equal slices as pieces, from 256 bytes on (24-bit products); narrow rows that are read in bulk from 512 bytes on (see slice_col)
+  int piece = d.H16 / kSlices, shift = 31;
+  if (!rotate && d.H16 < 1 << 24 && (piece & -piece) >= (warm && d.H16 < 512 ? 32 : 16))
+    piece &= -piece, shift = __builtin_ctz((unsigned)piece);
   const int per = U * Q;
   auto go = [&](auto kernel) {
     auto part = [&](dim3 grid, int start) {
       return launch(kernel, grid, dim3((unsigned)(U * lanes)), 0, s, (const u32x4 *)x,
                     (const int32_t *)(list ? p.order : p.row_map), (u32x4 *)window, d.k, d.H16, misalign, d.N, lanes, magic,
-                    U, d.T, warm_blocks, start);
+                    U, d.T, warm_blocks, start, piece, shift);
     };
     if (warm) return part(dim3((unsigned)warm_grid, (unsigned)((d.N + stretch - 1) / stretch)), stretch);
     // one launch, or as many as the limit on its threads asks for (windows of more than about 2 GiB at 16 bytes a row, 57 GiB

@@ -63,11 +63,22 @@ def test_dispatch_writes_every_vector_once(moe, H16, shift):
                                           (9000, 4864, 5, 7000),     # unequal slices, dropped branches, ragged last stretch
                                           (29000, 1600, 3, 0),       # two branches per unit, rows of 25 lines
                                           (28500, 1544, 4, 14500),   # two branches per unit, ragged rows, dropped branches
-                                          (29000, 1536, 2, 0)])      # degree 2, equal slices
+                                          (29000, 1536, 2, 0),       # degree 2, equal slices
+                                          (14001, 3072, 5, 0),       # three pieces of 256 bytes: one block
+                                          (8501, 5120, 3, 0),        # five pieces of 256 bytes
+                                          (7002, 6144, 3, 3340),     # three of 512, dropped branches
+                                          (1300, 49152, 10, 0)])     # three of 4 KB, slices longer than a workgroup
 def test_dispatch_with_bulk_reads_of_x(moe, T, H, k, stride):
     """X of more than 80 MiB: the list's stretches are read in bulk ahead of their copies."""
     assert T * H * 2 > 80 << 20
     dispatch_large(moe, T, H, k, stride, True)
+
+
+@pytest.mark.parametrize("H16", [384, 640, 768, 896, 1152, 1536, 1792, 3072, 6144, 7168])
+@pytest.mark.parametrize("shift", [0, 8])                      # a window that starts at another line
+def test_slices_in_pieces(moe, H16, shift):
+    """Equal slices that are no power of two are written in pieces of 256 bytes to 4 KB; H16 >= 6144: longer than a workgroup."""
+    test_dispatch_writes_every_vector_once(moe, H16, shift)
 
 
 @pytest.mark.parametrize("T,H,k,stride,given,used", [(2700, 16392, 3, 0, True, True),      # a single-launch plan: one stretch, no bulk reads
