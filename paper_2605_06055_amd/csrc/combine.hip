@@ -19,6 +19,7 @@
 namespace moe_rbf {
 
 constexpr int kGather = 8;  // rows fetched together
+constexpr int kRowMost = 640;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -78,6 +79,7 @@ struct Acc<MOE_DTYPE_F32> {
   }
 };
 
+// BLOCK: threads of a workgroup; kRowMost: as many as the launch says, up to that (whole rows, see launch_combine).
 // KFIX > 0: the routing degree is the compile-time constant KFIX (straight-line code, no bounds tests, all rows at once; us per
 // combine, rows taken 8 at a time / this: T = 300, H = 4096: k = 5 4.4 / 4.25, k = 10 6.9 / 6.3);
 // KFIX == 0: any k, rows taken kGather at a time.
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(BLOCK) void combine_rows_kernel(const u32x4 *__rest
   const int k = KFIX > 0 ? KFIX : k_arg;
   const int t = blockIdx.x / chunks;
   const int c = blockIdx.x - t * chunks;
-  const int col = c * BLOCK + threadIdx.x;
+  const int col = c * (BLOCK == kRowMost ? (int)blockDim.x : BLOCK) + threadIdx.x;
   if (col >= H16) return;
   // both arrays are 16-byte aligned (checked at the boundary): lets the scalar loads be wide
   const int32_t *rows = (const int32_t *)__builtin_assume_aligned(row_map, 16) + (size_t)t * k;
@@ -354,13 +356,27 @@ static hipError_t launch_combine_deferred(const Dims &d, const void *expert_out,
   }
 }
 
+// Waves of a workgroup that takes a whole row, or an equal part of one of more than 10 waves (of 3 waves or more, where that leaves none
+// idle).
+static int row_waves(int waves) {
+  const int most = kRowMost / kWave;
+  for (int w = most; w >= 3; --w)
+    if (waves % w == 0) return w;
+  const int parts = (waves + most - 1) / most;
+  return (waves + parts - 1) / parts;
+}
+
+// B: threads of a workgroup, or kRowMost: row_waves
 template <int DT, int B>
 static hipError_t launch_combine_dt(const Dims &d, const void *expert_out, const float *W, const PlanView &p, void *y,
                                     hipStream_t s) {
-  const int chunks = (d.H16 + B - 1) / B;
+  const int block = B == kRowMost ? row_waves((d.H16 + kWave - 1) / kWave) * kWave : B;
+  const int chunks = (d.H16 + block - 1) / block;
   const dim3 grid((unsigned)d.T * (unsigned)chunks);
+  if (B == kRowMost && (uint64_t)grid.x * (unsigned)block > kMostThreads)
+    return launch_combine_dt<DT, 128>(d, expert_out, W, p, y, s);
   auto go = [&](auto kernel) {
-    return launch(kernel, grid, dim3(B), 0, s, (const u32x4 *)expert_out, W, (const int32_t *)p.row_map, (u32x4 *)y,
+    return launch(kernel, grid, dim3((unsigned)block), 0, s, (const u32x4 *)expert_out, W, (const int32_t *)p.row_map, (u32x4 *)y,
                   d.k, d.H16, chunks);
   };
   switch (d.k) {
@@ -397,7 +413,15 @@ hipError_t launch_combine(const Dims &d, const void *expert_out, const float *W,
   // Degrees of 10 and 5 hold back only where few padded columns are idle (at most a third of the row, a seventh): us per combine, rows /
   // held, k = 10, X of 100 MB: H = 520 217 / 264, 640 199 / 218, 704 198 / 205, 768 200 / 194, 1032 217 / 217, 1152 199 / 193, 1664 213 / 187; k = 5:
   // H = 448 101.6 / 104.5, 480 108.6 / 102.3, 768 104.8 / 114.2, 896 105.5 / 103.6, 1792 110.1 / 100.8.
-  const bool held = d.k == 8 || d.k == 6 || (d.k == 10 && cols_pad * 3 <= d.H16 * 4) ||
+  // Idle columns cost degrees of 8 and 6 as well: us per combine, held / rows of whole workgroups (below): k = 8: T = 40000: H = 576 80 / 71,
+  // 640 84 / 80, T = 60000, H = 520 126 / 107, but 648 45.8 / 46.7, 1032 104 / 106, 2056 80.6 / 81.0, 4104 72.4 / 75.0; k = 6: H = 576 74 / 57,
+  // 640 76 / 64, 1152 72 / 67, 1280 66 / 64, 2176 66.7 / 64.4, 2304 68.7 / 68.1 (896 65.3 / 65.8), and rows that are no multiple of a line: 520 115 /
+  // 84, 1032 91 / 83, 2056 166 / 153, 4104 170 / 158 (2664 60.1 / 60.5, 5000 64.7 / 65.4; fp32 2056 94.3 / 92.3, 3076 95.6 / 97.6).
+  const bool ragged = d.H16 % 8 != 0 || ((uintptr_t)expert_out >> 4) % 8 != 0;
+  const bool idle = (cols_pad - d.H16) * 20 >= cols_pad * 3;
+  const bool held = (d.k == 8 && cols_pad * 5 < d.H16 * 8) ||
+                    (d.k == 6 && !idle && !(ragged && (cols_pad - d.H16) * 10 >= cols_pad)) ||
+                    (d.k == 10 && cols_pad * 3 <= d.H16 * 4) ||
                     (d.k == 5 && !threes && cols_pad * 7 <= d.H16 * 8 && d.H16 >= 60);
   const long long units = (long long)d.T * cols_pad;
   if (!small && held && units < 0x7fffffffLL)
@@ -406,6 +430,14 @@ hipError_t launch_combine(const Dims &d, const void *expert_out, const float *W,
                : launch_combine_deferred<MOE_DTYPE_F32>(d, expert_out, W, p, y, cols_pad, (int)units, s);
   auto rows = [&](auto dtype) {
     constexpr int DT = decltype(dtype)::value;
+    // Rows that are no multiple of a line: a wave's 1 KB shares its first and last line with its neighbours, which a workgroup of the
+    // whole row finds in the compute unit's cache; workgroups of one wave went to different XCDs, which fetched them again.  Rows with idle columns:
+    // fewer workgroups.  Not in the smallest launches, where every wave should start as early as possible.  us per combine, one wave (T * H16 <= 1.5 M) or two
+    // or three / the row: H = 4104: k = 8: T = 128 8.1 / 8.2, 256 7.9 / 7.5, 512 11.3 / 10.5, 1500 24.9 / 23.3, 2600 39.9 / 36.7; k = 6, T = 3001 35.9 / 32.4; k = 4,
+    // T = 9000 67.4 / 64.9; H = 1032: T = 5000 23.6 / 21.1; k = 2, T = 9000 16.4 / 15.2; H = 656, T = 5000 16.8 / 14.9; H = 520, k = 4, T = 20000 29.0 / 23.4;
+    // H = 2056: T = 3000 25.6 / 23.5; k = 5, T = 30000 143 / 132; H = 7400 (15 waves: 5), T = 1600 43.0 / 40.9; H = 768: T = 4371 15.1 / 14.2, 12000 34.0 / 31.6.
+    // Rows of whole lines and waves: no gain (H = 2048, T = 5000, k = 6 27.7 / 28.4).
+    if ((ragged || idle) && (int64_t)d.T * d.H16 >= 100000) return launch_combine_dt<DT, kRowMost>(d, expert_out, W, p, y, s);
     if (small) return launch_combine_dt<DT, 64>(d, expert_out, W, p, y, s);
     return threes ? launch_combine_dt<DT, 192>(d, expert_out, W, p, y, s) : launch_combine_dt<DT, 128>(d, expert_out, W, p, y, s);
   };

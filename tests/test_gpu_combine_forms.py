@@ -1,5 +1,5 @@
 """Combine at the degrees and widths that choose its form: 5 and 10 rows with results held back (at the numbers of results per thread
-where they move), rows of 3 and 9 waves in workgroups of 3, one row past and short of them, small launches."""
+where they move), rows of 3 and 9 waves in workgroups of 3, one row past and short of them, small launches, workgroups of whole rows."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -33,10 +33,17 @@ def cases():
     for k in (3, 5, 10, 11):
         for H16 in (1, 64, 129, 513):
             yield k, "f32", H16, 77
+    # workgroups of a whole row or an equal part of it: ragged rows, idle columns, at the size from which they are used
+    for k, dtype in ((1, "bf16"), (6, "bf16"), (8, "f32"), (10, "bf16"), (11, "bf16")):
+        for H16 in (1, 65, 80, 96, 333, 641, 705, 833, 897, 1089, 1857):
+            yield k, dtype, H16, -(-100000 // H16)
+            yield k, dtype, H16, -(-100000 // H16) - 1
+    for k, H16 in ((8, 72), (6, 144), (6, 513)):               # streaming launches that do not hold their results back
+        yield k, "bf16", H16, STREAMS // H16 + 1
 
 
 @pytest.mark.parametrize("k,dtype,H16,T", list(cases()))
-def test_combine(moe, k, dtype, H16, T):
+def test_combine(moe, k, dtype, H16, T, shift=0):
     bf16 = dtype == "bf16"
     H = H16 * (8 if bf16 else 4)
     print(f"[forms] T={T} H={H} k={k} {dtype}", flush=True)
@@ -44,7 +51,8 @@ def test_combine(moe, k, dtype, H16, T):
     gen.manual_seed(T + k)
     storage = torch.bfloat16 if bf16 else torch.float32
     # small integers: every product and partial sum is exact in fp32, so only the last rounding is left
-    out = torch.randint(-8, 9, (T * k, H), generator=gen, device="cuda", dtype=torch.int8).to(storage)
+    out = torch.empty(T * k * H + shift * (H // H16), dtype=storage, device="cuda")[shift * (H // H16):].view(T * k, H)
+    out.copy_(torch.randint(-8, 9, (T * k, H), generator=gen, device="cuda", dtype=torch.int8))
     w = torch.randint(-4, 5, (T, k), generator=gen, device="cuda").float()
     rows = torch.randperm(T * k, generator=gen, device="cuda").to(torch.int32).view(T, k)
     rows[torch.rand((T, k), generator=gen, device="cuda") < 0.05] = -1
@@ -60,3 +68,9 @@ def test_combine(moe, k, dtype, H16, T):
         want += torch.where(at[:, None] >= 0, w[:, j:j + 1] * out[at.clamp_min(0)].float(), 0.0)
     assert torch.equal(y[:T], want.to(storage))
     assert bool((y[T] == 77.0).all())
+
+
+@pytest.mark.parametrize("k,H16,T", [(8, 896, 128), (6, 512, 400), (8, 512, 3200), (3, 576, 3000)])
+def test_combine_of_rows_past_a_line(moe, k, H16, T):
+    """expert_out that starts 16 bytes past a cache line: rows of whole lines that all start inside one."""
+    test_combine(moe, k, "bf16", H16, T, shift=1)

@@ -89,6 +89,31 @@ for H16 in (60, 64, 112, 128, 224, 449, 640, 641, 896):
 """)
 
 
+def test_combine_workgroups(run):
+    """Whole rows, or equal parts of 3 to 10 waves, where rows are no multiple of a line or leave columns idle; one wave in the smallest
+    launches.  Degrees of 8 and 6 hold their results back unless too many columns are idle."""
+    run("""
+def block(H16, k, T, shift=0):
+    n, b = launched(moe.moe_combine, shape(T=T, H=8 * H16, k=k), X + 16 * shift, W, PLAN, WINDOW)
+    return n[0].split("combine_")[1].split("_kernel")[0], b
+for H16, waves in ((65, 2), (129, 3), (513, 9), (625, 10), (641, 6), (705, 6), (801, 7), (897, 5), (1089, 9), (1857, 10)):
+    T = -(-100000 // H16)
+    assert block(H16, 8, T) == ("rows", 64 * waves), H16
+    assert block(H16, 8, T - 1) == ("rows", 64), H16
+assert block(96, 8, 2000) == ("rows", 128) and block(160, 8, 2000) == ("rows", 192)
+assert block(112, 8, 2000) == ("rows", 64) and block(512, 8, 2000) == ("rows", 64) and block(512, 8, 2000, 1) == ("rows", 512)
+assert block(512, 4, 60000) == ("rows", 128) and block(513, 4, 60000) == ("rows", 576)
+for H16 in (65, 72, 80):
+    assert block(H16, 8, 60000) == ("rows", 128)
+for H16 in (81, 96, 129, 513):
+    assert block(H16, 8, 60000)[0] == "deferred", H16
+for H16 in (72, 144, 160, 272, 513, 257):
+    assert block(H16, 6, 60000)[0] == "rows", H16
+for H16 in (64, 112, 288, 512, 625, 896):
+    assert block(H16, 6, 60000)[0] == "deferred", H16
+""")
+
+
 def test_plan_of_few_experts(run):
     """A single launch counts all ids in every workgroup: not beyond 2048 branches an expert."""
     run("""
