@@ -119,6 +119,8 @@ __device__ __forceinline__ int slice_col(int c, int l, int piece, int shift) {
 // 66.5 / 65.3, 120.9 / 124.4, 174.7 / 172.8 (with X not cached 210 / 197).  Shorter and longer slices do not: H = 5632 33.0 / 33.6,
 // 55.2 / 56.7, 98.0 / 101.0, 137.6 / 141.1; H = 7424 (120 vectors) 40.1 / 39.2, 69.3 / 68.1, 126.9 / 127.7, 181.1 / 184.9; H = 7680
 // 40.3 / 39.9, 70.2 / 70.7, 129.0 / 134.4, 184.5 / 188.5; H = 8192 42.0 / 42.0, 73.8 / 75.2, 136.0 / 138.3, 189.7 / 190.5.
+// (All of that with slices in one block; in pieces H = 7168: T = 700 37.3 / 36.5, 1400 65.2 / 63.7, 2800 122.1 / 123.6, 4096 175.2 / 176.8, k = 4 102.3 /
+// 100.9, k = 10 206.7 / 202.8.)
 template <int Q, bool LIST, bool ROTATE, bool ALIGNED, bool WARM, bool ALONE = false>
 __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__restrict__ X,
                                                              const int32_t *__restrict__ entries,
@@ -165,16 +167,16 @@ __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__rest
   }
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
-    const int c = (blockIdx.x + (ROTATE ? t[q] : 0)) % kSlices;
     if (ROTATE) {
       const int a = ALIGNED ? 0 : (misalign + (int)((unsigned)row[q] * (unsigned)H16)) & (kLine - 1);
+      const int c = (blockIdx.x + t[q]) % kSlices;
       const int n = (a + H16 + kLine - 1) / kLine;
       const int cn = (int)__umul24(c, n);
       col[q] = (cn >> 3) * kLine - a + lane;                   // below 0: the line's part in front of the row
       end[q] = min(((cn + n) >> 3) * kLine - a, H16);
       if (!ALIGNED && col[q] < 0) col[q] += lanes;             // (past the slice, unless it is longer than a workgroup)
     } else {
-      col[q] = slice_col(c, lane, piece, shift);
+      col[q] = slice_col((int)blockIdx.x % kSlices, lane, piece, shift);
       end[q] = lane < H16 / kSlices ? H16 : 0;
     }
     if ((t[q] | row[q]) < 0) end[q] = 0;                       // nothing to do
