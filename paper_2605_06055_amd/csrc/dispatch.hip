@@ -74,10 +74,13 @@ __device__ __forceinline__ size_t row_offset(int row, int H16) {
 // each is written by several XCDs, which do not run in step either.  Plain fills in order, 2 GB, an XCD owning every 8th block: 256
 // bytes 6.1 TB/s, 512 7.0, 1024 7.35, 2048 6.7, 4096 7.2, but 768 5.4, 1536 5.0, 1792 5.3, 3584 5.3, whatever the occupancy.
 // us per dispatch along the list, slices in one block / in pieces, k = 8: X of 58 MB: H = 12288 (1 KB) 77.3 / 73.8, 6144 (512 bytes) 80.5 /
-// 75.1, 14336 79.2 / 75.6, 10240 79.1 / 76.7; 256 bytes: 7168 82.3 / 79.7, 3072 81.7 / 77.3, 5120 80.6 / 79.5, 9216 79.8 / 77.4; 128 bytes: 2560
+// 75.1, 14336 79.2 / 75.6, 10240 79.1 / 76.7; 256 bytes: 3072 81.7 / 77.3, 5120 80.6 / 79.5, 9216 79.8 / 77.4; 128 bytes: 2560
 // 82.4 / 86.0, 4608 80.4 / 85.2, 7680 82.2 / 86.6 (but 3584 84.6 / 80.8).  With bulk reads, X of 100, 150, 235 MB: 12288 142 / 133, 235 / 208, 386 /
 // 344; 6144 151 / 139, 252 / 234, 417 / 374; 14336 160 / 142, 251 / 232, 357 / 347; 7168 161 / 156, 254 / 255, 384 / 379; 5120 153 / 144, 253 /
 // 254, 401 / 402; 3072 150.5 / 153.7, 255 / 262, 388 / 395 (so rows under 8 KB keep one block there).
+// X that is not cached (58 MB, 8 copies in turn), us per layer: 6144 206.1 / 205.9, 3072 209.9 / 208.4, 5120 215.1 / 213.5, 12288 197.6 / 194.4, 9216 209.9 /
+// 208.1; but units that are alone in a workgroup (H = 7168, see ALONE below) read such an X better in one block: 197.9 / 204.1 (k = 4 123.8 / 128.5),
+// and a cached one better in pieces: 174.5 / 171.8.  They keep the block.
 // Larger pieces than divide the row, owned by address all the same, are needed by 2 to 8 XCDs for each token: H = 7168 82 / 104, 119, 125
 // (with stretches shortened to what L2 then holds 87, 97, 112).  Other kinds of stores, which fills like (ordinary, sc1, sc0 sc1 6.2 to
 // 7.3 TB/s along the list's runs, nt 5.0), push X out of L2: 148 us.
@@ -119,8 +122,6 @@ __device__ __forceinline__ int slice_col(int c, int l, int piece, int shift) {
 // 66.5 / 65.3, 120.9 / 124.4, 174.7 / 172.8 (with X not cached 210 / 197).  Shorter and longer slices do not: H = 5632 33.0 / 33.6,
 // 55.2 / 56.7, 98.0 / 101.0, 137.6 / 141.1; H = 7424 (120 vectors) 40.1 / 39.2, 69.3 / 68.1, 126.9 / 127.7, 181.1 / 184.9; H = 7680
 // 40.3 / 39.9, 70.2 / 70.7, 129.0 / 134.4, 184.5 / 188.5; H = 8192 42.0 / 42.0, 73.8 / 75.2, 136.0 / 138.3, 189.7 / 190.5.
-// (All of that with slices in one block; in pieces H = 7168: T = 700 37.3 / 36.5, 1400 65.2 / 63.7, 2800 122.1 / 123.6, 4096 175.2 / 176.8, k = 4 102.3 /
-// 100.9, k = 10 206.7 / 202.8.)
 template <int Q, bool LIST, bool ROTATE, bool ALIGNED, bool WARM, bool ALONE = false>
 __global__ __launch_bounds__(640) void dispatch_units_kernel(const u32x4 *__restrict__ X,
                                                              const int32_t *__restrict__ entries,
@@ -614,9 +615,10 @@ static hipError_t launch_dispatch_units(const Dims &d, const void *x, const Plan
   }
   const bool alone = list && aligned && !warm && lanes > 96 && lanes <= 112;
   if (alone) U = 1, lanes = 128;
-  // equal slices as pieces, from 256 bytes on (24-bit products); narrow rows that are read in bulk from 512 bytes on (see slice_col)
+  // equal slices as pieces, from 256 bytes on (24-bit products); narrow rows that are read in bulk from 512 bytes on, units that are alone
+  // in a workgroup in one block (see slice_col)
   int piece = d.H16 / kSlices, shift = 31;
-  if (!rotate && d.H16 < 1 << 24 && (piece & -piece) >= (warm && d.H16 < 512 ? 32 : 16))
+  if (!rotate && !alone && d.H16 < 1 << 24 && (piece & -piece) >= (warm && d.H16 < 512 ? 32 : 16))
     piece &= -piece, shift = __builtin_ctz((unsigned)piece);
   const int per = U * Q;
   auto go = [&](auto kernel) {
