@@ -2,7 +2,7 @@
 // order (paper, Section 5.2 "Prefill Combine", Section 5.3 "Decode Combine"; second loop of
 // Algorithms 1 and 2):  Y[t,:] = sum_j W[t,j] * Yexp[row_map[t,j], :].
 //
-// Work unit = (token, 16-byte output column); workgroups of one or two waves, or, for large launches, a
+// Work unit = (token, 16-byte output column); workgroups of one to three waves or of a whole row, or, for large launches, a
 // persistent grid whose threads hold their results back until a round's loads are done.  A thread fetches its column from up to 8 window rows
 // at once (8 independent 16-byte loads in flight per lane), folds them into fp32 accumulators in
 // ascending j with one fused multiply-add per branch, rounds once and stores 16 bytes.  Every window
