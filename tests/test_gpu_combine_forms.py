@@ -33,11 +33,11 @@ def cases():
     for k in (3, 5, 10, 11):
         for H16 in (1, 64, 129, 513):
             yield k, "f32", H16, 77
-    # workgroups of a whole row or an equal part of it: ragged rows, idle columns, at the size from which they are used
-    for k, dtype in ((1, "bf16"), (6, "bf16"), (8, "f32"), (10, "bf16"), (11, "bf16")):
-        for H16 in (1, 65, 80, 96, 333, 641, 705, 833, 897, 1089, 1857):
-            yield k, dtype, H16, -(-100000 // H16)
-            yield k, dtype, H16, -(-100000 // H16) - 1
+    # workgroups of a whole row or an equal part of it: ragged rows, idle columns; each width at two degrees, each degree at several widths
+    forms = ((1, "bf16"), (6, "bf16"), (8, "f32"), (10, "bf16"), (11, "bf16"))
+    for n, H16 in enumerate((1, 65, 80, 96, 333, 641, 705, 833, 897, 1089, 1857)):
+        for k, dtype in (forms[n % 5], forms[(n + 2) % 5]):
+            yield k, dtype, H16, -(-100000 // H16) if H16 <= 256 or k == 1 else max(640, -(-2400000 // (k * H16)))
     for k, H16 in ((8, 72), (6, 144), (6, 513)):               # streaming launches that do not hold their results back
         yield k, "bf16", H16, STREAMS // H16 + 1
 
@@ -70,7 +70,7 @@ def test_combine(moe, k, dtype, H16, T, shift=0):
     assert bool((y[T] == 77.0).all())
 
 
-@pytest.mark.parametrize("k,H16,T", [(8, 896, 128), (6, 512, 400), (8, 512, 3200), (3, 576, 3000)])
+@pytest.mark.parametrize("k,H16,T", [(8, 896, 128), (6, 512, 400), (8, 512, 700), (8, 512, 3200), (3, 576, 3000)])
 def test_combine_of_rows_past_a_line(moe, k, H16, T):
     """expert_out that starts 16 bytes past a cache line: rows of whole lines that all start inside one."""
     test_combine(moe, k, "bf16", H16, T, shift=1)

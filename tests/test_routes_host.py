@@ -89,20 +89,34 @@ for H16 in (60, 64, 112, 128, 224, 449, 640, 641, 896):
 """)
 
 
-def test_combine_workgroups(run):
-    """Whole rows, or equal parts of 3 to 10 waves, where rows are no multiple of a line or leave columns idle; one wave in the smallest
-    launches.  Degrees of 8 and 6 hold their results back unless too many columns are idle."""
-    run("""
+BLOCK = """
 def block(H16, k, T, shift=0):
     n, b = launched(moe.moe_combine, shape(T=T, H=8 * H16, k=k), X + 16 * shift, W, PLAN, WINDOW)
     return n[0].split("combine_")[1].split("_kernel")[0], b
-for H16, waves in ((65, 2), (129, 3), (513, 9), (625, 10), (641, 6), (705, 6), (801, 7), (897, 5), (1089, 9), (1857, 10)):
+"""
+
+
+def test_combine_workgroups(run):
+    """Whole rows, or equal parts of 3 to 10 waves, where rows are no multiple of a line or leave columns idle; one wave in the smallest
+    launches.  Degrees of 8 and 6 hold their results back unless too many columns are idle."""
+    run(BLOCK + """
+for H16, waves in ((65, 2), (129, 3), (193, 4), (72, 2), (96, 2)):                  # up to 4 waves, whole lines up to 2
     T = -(-100000 // H16)
     assert block(H16, 8, T) == ("rows", 64 * waves), H16
     assert block(H16, 8, T - 1) == ("rows", 64), H16
-assert block(96, 8, 2000) == ("rows", 128) and block(160, 8, 2000) == ("rows", 192)
+# wider rows: 2.4 M vectors of window and 2.5 workgroups a compute unit
+for H16, waves, k in ((257, 5, 8), (333, 6, 4), (513, 9, 6), (641, 6, 2), (705, 6, 10), (801, 7, 8), (897, 5, 6), (1089, 9, 8), (1350, 8, 4), (1857, 10, 8)):
+    T = max(-(-2400000 // (k * H16)), -(-640 // -(-H16 // (64 * waves))))
+    assert block(H16, k, T) == ("rows", 64 * waves), H16
+    assert block(H16, k, T - 1) == ("rows", 64), H16
+assert block(625, 10, 640) == ("rows", 640) and block(625, 10, 639) == ("rows", 64)
+for H16, k, T, waves in ((513, 1, 195, 9), (513, 1, 5000, 9), (513, 2, 584, 9), (264, 2, 1136, 5), (264, 1, 2272, 5), (144, 1, 4166, 3), (208, 1, 7000, 4),
+                         (208, 4, 2885, 4), (208, 8, 1443, 4)):                     # little work; 4 waves of whole lines
+    assert block(H16, k, T) == ("rows", 64 * waves), (H16, k, T)
+for H16, k, T in ((513, 8, 262), (513, 2, 585), (1350, 8, 96), (264, 2, 1137), (264, 1, 2273), (264, 8, 5000), (144, 8, 5000), (144, 1, 4167), (208, 8, 1442)):
+    assert block(H16, k, T) == ("rows", 64), (H16, k, T)
 assert block(112, 8, 2000) == ("rows", 64) and block(512, 8, 2000) == ("rows", 64) and block(512, 8, 2000, 1) == ("rows", 512)
-assert block(512, 4, 60000) == ("rows", 128) and block(513, 4, 60000) == ("rows", 576)
+assert block(512, 4, 60000) == ("rows", 128) and block(513, 4, 60000) == ("rows", 576) and block(272, 4, 60000) == ("rows", 128)
 for H16 in (65, 72, 80):
     assert block(H16, 8, 60000) == ("rows", 128)
 for H16 in (81, 96, 129, 513):
@@ -111,6 +125,14 @@ for H16 in (72, 144, 160, 272, 513, 257):
     assert block(H16, 6, 60000)[0] == "rows", H16
 for H16 in (64, 112, 288, 512, 625, 896):
     assert block(H16, 6, 60000)[0] == "deferred", H16
+""")
+
+
+def test_combine_of_more_threads_than_a_launch_takes(run):
+    """Rows of 22 waves as 3 times 8: beyond 2^32 threads they take workgroups of two waves, which leave none idle."""
+    run(BLOCK + """
+assert block(1350, 1, (1 << 32) // 1536) == ("rows", 512)
+assert block(1350, 1, (1 << 32) // 1536 + 1) == ("rows", 128)
 """)
 
 
