@@ -437,17 +437,24 @@ hipError_t launch_combine(const Dims &d, const void *expert_out, const float *W,
   // columns past the last whole wave of several tokens packed into one wave: H = 4104, k = 6 33.3 / 34.3 a combine, H = 640, k = 8 51 / 56.)
   const int cols_pad = (d.H16 + 63) / 64 * 64, waves = cols_pad / kWave;
   const bool threes = waves % 2 == 1 && waves % 3 == 0;
-  // Degrees of 10 and 5 hold back only where few padded columns are idle (at most a third of the row, a seventh): us per combine, rows /
-  // held, k = 10, X of 100 MB: H = 520 217 / 264, 640 199 / 218, 704 198 / 205, 768 200 / 194, 1032 217 / 217, 1152 199 / 193, 1664 213 / 187; k = 5:
-  // H = 448 101.6 / 104.5, 480 108.6 / 102.3, 768 104.8 / 114.2, 896 105.5 / 103.6, 1792 110.1 / 100.8.
-  // Idle columns cost degrees of 8 and 6 as well: us per combine, held / rows of whole workgroups (below): k = 8: T = 40000: H = 576 80 / 71,
-  // 640 84 / 80, T = 60000, H = 520 126 / 107, but 648 45.8 / 46.7, 1032 104 / 106, 2056 80.6 / 81.0, 4104 72.4 / 75.0; k = 6: H = 576 74 / 57,
-  // 640 76 / 64, 1152 72 / 67, 1280 66 / 64, 2176 66.7 / 64.4, 2304 68.7 / 68.1 (896 65.3 / 65.8), and rows that are no multiple of a line: 520 115 /
-  // 84, 1032 91 / 83, 2056 166 / 153, 4104 170 / 158 (2664 60.1 / 60.5, 5000 64.7 / 65.4; fp32 2056 94.3 / 92.3, 3076 95.6 / 97.6).
+  // Results are held back only where few padded columns are idle, judged inside layers: alone in a loop the held form reads better than it is,
+  // since the rest of the layer is slower behind it.  us per layer, held / rows of whole workgroups (see whole_rows):
+  //   k = 10 (a third of the row idle at most): H = 704, T = 29545 174.5 / 166.2, 1032, T = 20155 200.3 / 194.2, but 800, T = 55000 371.0 / 376.3, 1280, T = 16250
+  //     157.6 / 160.5, 2056, T = 10116 171.5 / 174.9, 4104, T = 5068 168.6 / 173.4, 5128, T = 4056 161.3 / 177.0;
+  //   k = 5 (a seventh): H = 1664, T = 12500 95.3 / 91.4, 2056, T = 10116 103.5 / 98.6, 4104, T = 5068 101.7 / 97.5 (this line was drawn for rows of 1 to 3 waves a
+  //     workgroup; ragged rows would still gain: H = 1800, T = 11555 103.9 / 100.1, 5000, T = 4160 97.8 / 95.6, but 5128, T = 4056 97.3 / 98.9);
+  //   k = 8 (three eighths): H = 320, T = 80000 170.0 / 167.8, 352 189.5 / 195.8; 520, T = 60000 270.9 / 259.7, 576, T = 40000 158.2 / 149.9, 640 162.1 / 159.8, 672 171.7 /
+  //     172.5, 1032, T = 20000 159.1 / 160.4;
+  //   k = 6 (a fifth, of one wave a quarter): H = 384, T = 60000 119.2 / 116.6, but 400, T = 52000 136.7 / 140.1, 432, T = 48148 133.7 / 138.4; 520, T = 60000 223.5 / 198.2,
+  //     576, T = 40000 134.3 / 119.3, 768, T = 60000 235.0 / 227.9, 1152, T = 18055 107.9 / 105.8, 1216, T = 17105 105.7 / 105.0, but 832, T = 25000 105.2 / 106.5, 1280, T = 16250
+  //     104.4 / 105.3, 2176: T = 9558 103.1 / 105.0, T = 20000 208.5 / 212.6; rows of 2 waves and more that are no multiple of a line from a tenth on:
+  //     2056, T = 30000 343.3 / 332.8, 4104: T = 5068 113.0 / 112.5, T = 18600 403.6 / 396.2, 2664: T = 7807 112.3 / 112.8, T = 15600 220.6 / 216.7 (of one wave, which share
+  //     no line inside the row: 456, T = 45614 140.2 / 144.3).
   const bool ragged = d.H16 % 8 != 0 || ((uintptr_t)expert_out >> 4) % 8 != 0;
-  const bool idle = (cols_pad - d.H16) * 20 >= cols_pad * 3;
+  const int pad = cols_pad - d.H16;
+  const bool idle = pad * 20 >= cols_pad * 3;
   const bool held = (d.k == 8 && cols_pad * 5 < d.H16 * 8) ||
-                    (d.k == 6 && !idle && !(ragged && (cols_pad - d.H16) * 10 >= cols_pad)) ||
+                    (d.k == 6 && pad * (waves == 1 ? 4 : 5) < cols_pad && !(ragged && waves > 1 && pad * 10 >= cols_pad)) ||
                     (d.k == 10 && cols_pad * 3 <= d.H16 * 4) ||
                     (d.k == 5 && !threes && cols_pad * 7 <= d.H16 * 8 && d.H16 >= 60);
   const long long units = (long long)d.T * cols_pad;

@@ -121,9 +121,9 @@ for H16 in (65, 72, 80):
     assert block(H16, 8, 60000) == ("rows", 128)
 for H16 in (81, 96, 129, 513):
     assert block(H16, 8, 60000)[0] == "deferred", H16
-for H16 in (72, 144, 160, 272, 513, 257):
+for H16 in (40, 48, 72, 100, 144, 152, 200, 257, 513):
     assert block(H16, 6, 60000)[0] == "rows", H16
-for H16 in (64, 112, 288, 512, 625, 896):
+for H16 in (50, 54, 57, 64, 104, 112, 160, 208, 272, 288, 512, 525, 625, 896):         # a fifth idle, of one wave a quarter, ragged a tenth
     assert block(H16, 6, 60000)[0] == "deferred", H16
 """)
 
