@@ -1,5 +1,5 @@
 """Which kernel a call takes where both of two forms would be right and only one is fast, seen without a GPU: a stand-in for the
-runtime's launch call notes the kernel's name and the workgroup.  The rules and their measurements stand beside the code."""
+runtime's launch call notes the kernel's name and the workgroup, and how the prefill dispatch cuts its slices.  The rules and their measurements stand beside the code."""
 import os
 import subprocess
 import sys
@@ -15,16 +15,21 @@ FAKE = r"""
 #include <stdint.h>
 #include <string.h>
 typedef struct { uint32_t x, y, z; } dim3;
-int fake_launches, fake_block;
+int fake_launches, fake_block, fake_cut[3];
 char fake_names[4096];
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipDeviceGetAttribute(int *v, int attr, int dev) { (void)attr; (void)dev; *v = 256; return 0; }
 int hipFuncSetAttribute(const void *kernel, int attr, int value) { (void)kernel; (void)attr; (void)value; return 0; }
 int hipLaunchKernel(const void *kernel, dim3 grid, dim3 block, void **args, size_t lds, void *stream) {
-  (void)grid; (void)args; (void)lds; (void)stream;
+  (void)grid; (void)lds; (void)stream;
   Dl_info at;
   const char *name = dladdr(kernel, &at) && at.dli_sname ? at.dli_sname : "?";
   if (strlen(fake_names) + strlen(name) + 2 < sizeof(fake_names)) strcat(strcat(fake_names, name), " ");
+  if (strstr(name, "dispatch_units_kernel")) {       /* its last arguments: warm_blocks, stretch, piece, shift */
+    fake_cut[0] = *(const int *)args[11] > 0;
+    fake_cut[1] = *(const int *)args[13];
+    fake_cut[2] = *(const int *)args[14];
+  }
   fake_block = (int)block.x;
   ++fake_launches;
   return 0;
@@ -133,6 +138,29 @@ def test_combine_of_more_threads_than_a_launch_takes(run):
     run(BLOCK + """
 assert block(1350, 1, (1 << 32) // 1536) == ("rows", 512)
 assert block(1350, 1, (1 << 32) // 1536 + 1) == ("rows", 128)
+""")
+
+
+def test_dispatch_pieces(run):
+    """Equal slices are written in pieces of the largest power of two that divides them, from 256 bytes on; with bulk reads narrow rows only from
+    512; not by units that are alone in a workgroup, and never where the slices differ."""
+    run("""
+LISTED = _PlanStruct.from_buffer_copy(PLAN)
+LISTED.dispatch_order = 0x9000
+cut = (ctypes.c_int * 3).in_dll(fake, "fake_cut")
+def pieces(H16, mib, k=8, shift=0):
+    T = (mib << 20) // (16 * H16)
+    n, _ = launched(moe.moe_dispatch, shape(T=T, H=8 * H16, k=k), X, K, LISTED, WINDOW + 16 * shift)
+    assert "dispatch_units" in n[0], (H16, mib)
+    return tuple(cut)
+BLOCK = 31                     # the whole slice as one piece
+for H16, piece, bulk in ((256, 32, 32), (384, 16, 0), (448, 0, 0), (512, 64, 64), (640, 16, 16), (768, 32, 32), (832, 0, 0), (896, 0, 16), (960, 0, 0),
+                         (1152, 16, 16), (1536, 64, 64), (1792, 32, 32), (2048, 256, 256)):
+    for mib, warm, want in ((50, 0, piece), (120, 1, bulk)):
+        assert pieces(H16, mib) == (warm, want or H16 // 8, want.bit_length() - 1 if want else BLOCK), (H16, mib)
+for H16 in (513, 520, 1000, 2000):
+    assert pieces(H16, 50)[2] == pieces(H16, 120)[2] == BLOCK, H16
+assert pieces(1536, 50, shift=1)[2] == BLOCK
 """)
 
 
