@@ -133,12 +133,12 @@ __global__ __launch_bounds__(BLOCK) void combine_rows_kernel(const u32x4 *__rest
 // K: the routing degree; G: its rows that are in flight together.  Degrees of 10 and 5 take this form too, the former 5 rows at a time:
 // us per combine, combine_rows_kernel / this with 2, 5, 8, 10 rows in flight: k = 10: H = 3456, T = 25255 341 / 381, 290, 304, 298; H = 2048,
 // T = 12000 92 / 113, 87, -, -.  us per layer: k = 10: H = 7168, T = 8000 414 / 389; k = 5: H = 7168, T = 8000 230 / 226;
-// H = 5120, T = 16000 358 / 351; not where many of the padded columns are idle (see launch_combine).  k = 8 with 4 rows in flight: H = 4096, T = 16000 388 / 384, but Zipf H = 7168, T = 16384 710 / 721 and H = 640,
-// T = 28000 118 / 132; k = 6 with 3: 6 % slower.
+// H = 5120, T = 16000 358 / 351; not where many of the padded columns are idle (see launch_combine).  k = 8 with 4 rows in flight: H = 4096, T = 16000 388 / 384, but Zipf H = 7168, T = 16384 710 / 721;
+// k = 6 with 3: 6 % slower.
 // Same arithmetic as combine_rows_kernel
 // (ascending j, one fma per placed branch, one rounding).  Units (token, column) are numbered token-major over
 // columns padded to a multiple of 64, so that a wave stays inside one token: without the padding (H = 4104: 115
-// against 95 us per combine, H = 640 79 / 68) the row numbers are no longer scalar and every unit waits for them.
+// against 95 us per combine) the row numbers are no longer scalar and every unit waits for them.
 constexpr int kDeferBlock = 512;
 constexpr int kDeferRegs = 36;     // results per thread held in registers ...
 constexpr int kDeferLds = 20;      // ... and in LDS (all 160 KB)
@@ -231,8 +231,8 @@ __global__ __launch_bounds__(kDeferBlock) void combine_deferred_kernel(const u32
 }
 
 // The form for at most 28 units a thread (one launch, no LDS): the loop that the compiler unrolls by itself, with the tests as
-// lane masks.  us per layer, the form above / this one: k = 6: H = 7168, T = 3000 105.9 / 102.3, T = 4096 139.1 / 134.6; H = 4104, T = 5500
-// 124.2 / 120.9; k = 8: H = 7168: T = 2400 107.1 / 106.4, 3584 155.1 / 154.3, 4096 175.8 / 175.8; H = 1024, T = 28000 178.9 /
+// lane masks.  us per layer, the form above / this one: k = 6: H = 7168, T = 3000 105.9 / 102.3, T = 4096 139.1 / 134.6;
+// k = 8: H = 7168: T = 2400 107.1 / 106.4, 3584 155.1 / 154.3, 4096 175.8 / 175.8; H = 1024, T = 28000 178.9 /
 // 178.1; H = 4104, T = 6300 176.0 / 174.2; fp32: H = 2056, T = 5000 138.8 / 138.2.  Not for more units: with 36 results the
 // compiler keeps part of them in scratch memory (H = 7168: T = 4096 211, T = 4600 244 against 193).  The unit's code is written
 // out and the loop over `base`, which runs once, stays: as a call of combine_unit the compiler schedules it otherwise, which costs
@@ -432,9 +432,9 @@ hipError_t launch_combine(const Dims &d, const void *expert_out, const float *W,
   // 104.1 / 103.4, H = 2176, T = 24000 96 / 86 (a combine), k = 3: H = 7168, T = 8000 83 / 74 (smaller degrees, and degrees without a
   // compile-time form, whose results array the compiler would spill, stay).
   // The others: rows of an odd number of waves that is a multiple of 3 take workgroups of 3 waves, so that no workgroup is half
-  // idle.  us per layer, 2 waves / 3: T = 20000: H = 1152: k = 1 50.8 / 48.2, k = 3 73.2 / 68.4, k = 5 104.9 / 98.5; H = 1536, k = 4 109.3 / 105.9;
-  // H = 4104, k = 2 205.7 / 202.4, k = 5 405.7 / 400.3.  (Of one wave: H = 4104, k = 5 417; of 5 or 7 where the row has as many: no gain.  The
-  // columns past the last whole wave of several tokens packed into one wave: H = 4104, k = 6 33.3 / 34.3 a combine, H = 640, k = 8 51 / 56.)
+  // idle.  us per layer, 2 waves / 3: T = 20000: H = 1152: k = 1 50.8 / 48.2, k = 3 73.2 / 68.4, k = 5 104.9 / 98.5; H = 1536, k = 4 109.3 / 105.9.
+  // (Of 5 or 7 where a row of whole lines has as many: no gain.  The columns past the last whole wave of several tokens packed into one wave:
+  // H = 4104, k = 6 33.3 / 34.3 a combine.)
   const int cols_pad = (d.H16 + 63) / 64 * 64, waves = cols_pad / kWave;
   const bool threes = waves % 2 == 1 && waves % 3 == 0;
   // Results are held back only where few padded columns are idle, judged inside layers: alone in a loop the held form reads better than it is,

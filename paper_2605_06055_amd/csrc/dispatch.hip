@@ -73,14 +73,16 @@ __device__ __forceinline__ size_t row_offset(int row, int H16) {
 // being a whole number of 8 pieces), so a DRAM page is written by one XCD.  Slices of another length are not in step with the pages:
 // each is written by several XCDs, which do not run in step either.  Plain fills in order, 2 GB, an XCD owning every 8th block: 256
 // bytes 6.1 TB/s, 512 7.0, 1024 7.35, 2048 6.7, 4096 7.2, but 768 5.4, 1536 5.0, 1792 5.3, 3584 5.3, whatever the occupancy.
+// An XCD then also fetches X less often: H = 6144, T = 12160 in bulk 1.57 times in one block and 1.06 in pieces, Zipf H = 7168, T = 16384 1.19 / 1.05.
 // us per dispatch along the list, slices in one block / in pieces, k = 8: X of 58 MB: H = 12288 (1 KB) 77.3 / 73.8, 6144 (512 bytes) 80.5 /
 // 75.1, 14336 79.2 / 75.6, 10240 79.1 / 76.7; 256 bytes: 3072 81.7 / 77.3, 5120 80.6 / 79.5, 9216 79.8 / 77.4; 128 bytes: 2560
 // 82.4 / 86.0, 4608 80.4 / 85.2, 7680 82.2 / 86.6 (but 3584 84.6 / 80.8).  With bulk reads, X of 100, 150, 235 MB: 12288 142 / 133, 235 / 208, 386 /
 // 344; 6144 151 / 139, 252 / 234, 417 / 374; 14336 160 / 142, 251 / 232, 357 / 347; 7168 161 / 156, 254 / 255, 384 / 379; 5120 153 / 144, 253 /
-// 254, 401 / 402; 3072 150.5 / 153.7, 255 / 262, 388 / 395 (so rows under 8 KB keep one block there).
-// X that is not cached (58 MB, 8 copies in turn), us per layer: 6144 206.1 / 205.9, 3072 209.9 / 208.4, 5120 215.1 / 213.5, 12288 197.6 / 194.4, 9216 209.9 /
+// 254, 401 / 402; 3072 150.5 / 153.7, 255 / 262, 388 / 395 (of the rows under 8 KB with 256-byte pieces these are the only ones; they keep one block there).
+// X that is not cached (58 MB, 8 copies in turn), us per layer: 6144 206.1 / 205.9, 3072 209.9 / 208.4 (T = 9898 213.4 / 218.2, cached 178.0 / 178.6), 5120 215.1 / 213.5, 12288 197.6 / 194.4, 9216 209.9 /
 // 208.1; but units that are alone in a workgroup (H = 7168, see ALONE below) read such an X better in one block: 197.9 / 204.1 (k = 4 123.8 / 128.5),
-// and a cached one better in pieces: 174.5 / 171.8.  They keep the block.
+// and a cached one better in pieces: 174.5 / 171.8.  They keep the block.  (That is this one width: 104 vectors have no pieces of 256 bytes.  With the block
+// as a compile-time case the kernel needs 6 VGPRs instead of 14: cached 174.8 against 176.2 with it, not cached 199.0 / 198.1; not kept.)
 // Larger pieces than divide the row, owned by address all the same, are needed by 2 to 8 XCDs for each token: H = 7168 82 / 104, 119, 125
 // (with stretches shortened to what L2 then holds 87, 97, 112).  Other kinds of stores, which fills like (ordinary, sc1, sc0 sc1 6.2 to
 // 7.3 TB/s along the list's runs, nt 5.0), push X out of L2: 148 us.
@@ -107,12 +109,18 @@ __device__ __forceinline__ int slice_col(int c, int l, int piece, int shift) {
 // 12 slots of 32, and the copies in the others asked for X in random order in the meantime; the gap in the stores at each stretch was
 // 6.4 us for 24 MB.  us per dispatch, X not cached, 8 tokens / 1 (4, 2: in between): group-limited T = 32768, H = 4096 449 / 426;
 // T = 24000 288 / 278; H = 6144, T = 12160 263 / 252; H = 2560, T = 45888 427 / 406; H = 7168: T = 16384 395 / 384, k = 4, T = 10463 148 /
-// 141; H = 4104, T = 14000 220 / 208; H = 7400, T = 9000 223 / 214.
+// 141; H = 4104, T = 14000 220 / 208; H = 7400, T = 9000 223 / 214.  (X is fetched as often with 8 tokens as with one, only later.  Of slices of more than
+// 512 vectors, rows over 64 KB, the readers read the first 512.)  What it costs where X is cached: us per layer, 8 / 1: H = 7168: T = 8192 355.3 / 357.9, k = 4,
+// T = 10463 260.5 / 263.9; H = 4096: T = 12000 275.4 / 278.8, k = 3, T = 24000 261.0 / 264.4; H = 7680, T = 5515 252.6 / 254.3; H = 6144, T = 8128, Zipf 279.1 / 283.6.  Where
+// the plan has prefetched X it depends: H = 6144, T = 8128, Zipf 289.7 / 293.5; H = 4096, T = 12000 286.4 / 288.8; H = 7168, T = 16384, Zipf 695.8 / 698.9; but H = 2560, T = 34000
+// 567.8 / 561.5; H = 12288, T = 6080 445.3 / 434.1; H = 7168, k = 4, T = 10463 296.7 / 285.3; so the readers do not ask whether it has.
 // us per layer, token order / list / list with bulk reads, X not cached when the layer starts: H = 7168: T = 8192 485 / 420 /
 // 383, 13000 760 / 699 / 602, Zipf 16384 933 / 812 / 725; H = 8192, T = 12000 768 / 656 / 609; H = 4096: T = 24000 633 / 683 /
 // 605, 11000 294 (list) / 268; H = 3072, k = 10, T = 32768 1087 / 908 / 799; H = 4096, k = 3, T = 16000 263 / 212 / 188; X
 // fully cached: H = 7168: T = 8192 356 / 357 / 371, 16384 709 / 718 / 741; H = 4096, T = 20000 505 / 466 / 479.  So a cached X
-// loses 1 to 4 % (k = 4, T = 10000, H = 7168 233 / 246: 6 %), and one that is not wins 8 to 25 %.  The latter decides: X of this size
+// loses 1 to 4 % (k = 4, T = 10000, H = 7168 233 / 246: 6 %), and one that is not wins 8 to 25 %.  (These are with 8 tokens a reader and slices in one block.  Now,
+// token order / list with bulk reads: cached H = 7168: T = 6144 266 / 267, 8192 372 / 372, 16384 692 / 719, k = 4, T = 8192 193 / 212; H = 6144, T = 8192 311 / 291; H = 4096, T = 16384
+// 421 / 405; not cached 363 / 267, 488 / 381, 949 / 750, 249 / 219, 340 / 298, 435 / 408.)  The latter decides: X of this size
 // stays cached only while little else runs, and not even always when the kernel in front of the layer has just written
 // it (H = 7168, T = 16384, token order / list with bulk reads: 928 / 757).
 // ALONE: one unit per workgroup of 128 threads, its entry in scalar registers.  Slices of 104 and 112 vectors nearly fill two

@@ -338,7 +338,11 @@ static bool plan_in_one_launch(const Dims &d, int tiles) {
 // and for larger X with bulk reads (order_streams_x).
 // (All layers here were measured with the plan as it was before its tile histograms were packed, on both sides.  The list cost that plan 1.3 us
 // at 32 768 branches and 2.8 at 131 072; it costs the present one 0.4 to 0.65 up to 65 536, 1.0 at 131 072, 1.4 at 262 144, so both sides are 1 to 4 us
-// shorter now and the list's by 0.7 to 2 us more.)
+// shorter now and the list's by 0.7 to 2 us more.  And with slices in one block.  Now, list / token order, E = 256 or 64, X cached; not cached: H = 7168: k = 8: T = 1536 68.0 / 75.6;
+// 69.4 / 73.4, 3072 136.7 / 136.2; 136.3 / 136.0, 4096 180.6 / 187.2; 199 / 249, 5800 246 / 251; 277 / 345; k = 6, T = 4096 137.6 / 137.9; 159 / 187; k = 4, T = 4096 103.9 / 98.9; 122 / 129; k = 2,
+// T = 4096 67.9 / 63.9; 73.9 / 71.9 (a loss); H = 6144: T = 4096 149.9 / 166.3; 174 / 182; H = 4096: T = 8192 193 / 207; 227 / 226, k = 2, T = 10000 86.6 / 85.6; 102 / 97 (a loss); H = 5120, k = 4,
+// T = 5000 91.9 / 87.8; 116 / 104 (a loss); H = 3072, T = 8192 147 / 158; 176 / 169; H = 2560, T = 12288 187 / 199; 231 / 207; H = 1024, T = 32768 193 / 210; 243 / 220.  The lines below have not been drawn
+// again: degrees of 2 and 4 would be better off without the list at more widths than those named.)
 // Rows of 2 to 4 KB, us per layer with the list / in token order: H = 2048: T = 8192 105.4 / 108.0, 16384 197.0 / 204.3,
 // 32768 388.6 / 407.6; H = 1024: T = 16384 110.0 / 113.4, 65536 405.7 / 426.0.  With slices cut at cache lines and units
 // packed side by side the same holds for most widths from 1.5 KB on (sum of the kernels' us): H = 2560, T = 11468
