@@ -396,27 +396,28 @@ static hipError_t launch_combine_dt(const Dims &d, const void *expert_out, const
 // shares its first and last line with its neighbours, which a workgroup of the whole row finds in the compute unit's cache.  Rows with idle
 // columns: fewer workgroups.  Against it: the launch lasts as long as the compute unit with the most rows, and 262 rows on 256 units are
 // uneven where 262 times 9 one-wave workgroups are not.  So rows of 5 waves and more take it from 2.4 M window vectors and 2.5 workgroups a
-// compute unit on, or where a row is little work.  (Counts in between that happen to be even would gain 3 %: H = 2664, k = 8, T = 700 21.0 / 20.4.)
+// compute unit on, from 1.7 M where the last workgroups nearly fill the units, or where a row is little work.
 // us per layer, one wave (T * H16 <= 1.5 M) or two / the row; the second pair, if any, with expert_out rotating through 600 MB instead of
 // the same in each layer:
 //   not taken: H = 4104, k = 8: T = 262 12.3 / 13.1, 12.2 / 12.9, 372 15.3 / 15.6, 15.4 / 15.4; H = 5000: k = 8, T = 304 15.1 / 16.0, 15.1 / 15.8, k = 4,
 //     T = 655 17.3 / 17.8, 17.5 / 17.2, k = 2, T = 960 15.7 / 16.0, 15.4 / 15.6; H = 8200, k = 10, T = 142 14.5 / 15.7; H = 10800, k = 8, T = 96 11.2 / 12.1;
-//   taken: H = 4104: k = 8, T = 797 31.1 / 30.8, 1170 42.4 / 40.9, k = 6, T = 3001 73.8 / 70.5, k = 4, T = 1717 35.6 / 34.0; H = 10800, k = 8, T = 1156 85.8 / 83.5;
+//   taken: H = 2664, k = 8, T = 700 (2.7 a unit) 21.1 / 20.4; H = 4104: k = 8, T = 455 (1.8) 18.1 / 17.6, T = 797 31.1 / 30.8, 1170 42.4 / 40.9, k = 6, T = 3001 73.8 / 70.5, k = 4, T = 1717 35.6 / 34.0; H = 10800, k = 8, T = 1156 85.8 / 83.5;
 //     little work: k = 2: H = 4104, T = 543 10.9 / 10.5, H = 5000, T = 172 8.7 / 8.5; k = 1, H = 4104, T = 543 13.1 / 12.3;
 //     up to 4 waves: H = 1032, k = 8, T = 2159 27.2 / 26.3; H = 1544, k = 8, T = 3109 45.3 / 43.1; H = 520, k = 8, T = 13549 71.8 / 65.2;
 //   rows of whole lines with idle columns: taken: H = 576, k = 8, T = 2636 20.5 / 19.2; H = 1664, k = 4, T = 9122 61.9 / 60.7; k = 1: H = 1152, T = 1318
 //     8.9 / 8.4, H = 2112, T = 719 8.7 / 8.1; not (3 or 5 waves): H = 1152: k = 8, T = 898 14.2 / 14.5, k = 2, T = 4167 19.8 / 20.1; H = 2112: k = 2, T = 2273
 //     15.8 / 16.5, k = 1, T = 3800 17.1 / 17.5.
-// Known loss: rows of 11 waves as 2 times 6 with expert_out written just in front of combine (H = 5128, k = 8, T = 700 54.5 / 55.4 with that copy; else 32.2 / 32.0).
+// Known losses, up to 2.5 %: 1 shape in 80, most of them rows of 11 waves as 2 times 6 with expert_out written just in front of combine (H = 5128, k = 8, T = 700 54.5 / 55.4 with that copy; else 32.2 / 32.0).
 // Rows of whole lines and waves: no gain (H = 2048, T = 5000, k = 6 27.7 / 28.4 a combine).
 static bool whole_rows(const Dims &d, int waves, bool ragged, bool idle) {
   const int64_t vecs = (int64_t)d.T * d.H16, window = vecs * d.k;
-  if (vecs < 100000) return false;
-  const int w = row_waves(waves), groups = (waves + w - 1) / w;
-  const bool little = d.k <= 2 && window < 600000;
-  const bool streams = window >= 2400000 && (int64_t)d.T * groups >= 640;
-  if (ragged) return waves <= 4 || d.k == 1 || little || streams;
-  return idle && (waves <= 2 || little || (waves == 4 && (d.k == 1 || streams)));
+  if (!(ragged || idle) || vecs < 100000) return false;
+  if (waves <= 2 || (d.k <= 2 && window < 600000) || (ragged && waves <= 4) || (d.k == 1 && (ragged || waves == 4))) return true;
+  if (!ragged && waves != 4) return false;
+  const int w = row_waves(waves);
+  const int64_t cus = device_cus(), groups = (int64_t)d.T * ((waves + w - 1) / w), even = (groups + cus - 1) / cus * cus;   // workgroups, and as many to each unit
+  return (window >= 2400000 && groups * 2 >= cus * 5) ||
+         (d.k > 2 && window >= 1700000 && groups * 4 >= cus * 7 && groups * 20 >= even * 17);
 }
 
 hipError_t launch_combine(const Dims &d, const void *expert_out, const float *W, const PlanView &p, void *y,

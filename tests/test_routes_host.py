@@ -111,14 +111,21 @@ for H16, waves in ((65, 2), (129, 3), (193, 4), (72, 2), (96, 2)):              
     assert block(H16, 8, T - 1) == ("rows", 64), H16
 # wider rows: 2.4 M vectors of window and 2.5 workgroups a compute unit
 for H16, waves, k in ((257, 5, 8), (333, 6, 4), (513, 9, 6), (641, 6, 2), (705, 6, 10), (801, 7, 8), (897, 5, 6), (1089, 9, 8), (1350, 8, 4), (1857, 10, 8)):
-    T = max(-(-2400000 // (k * H16)), -(-640 // -(-H16 // (64 * waves))))
+    groups = -(-H16 // (64 * waves))
+    def even(T):                                                                    # 1.7 M, 1.75 a unit and the units 85 % full
+        n = T * groups
+        return k > 2 and T * k * H16 >= 1700000 and n >= 448 and n / (-(-n // 256) * 256) >= 0.85
+    T = max(-(-2400000 // (k * H16)), -(-640 // groups))
     assert block(H16, k, T) == ("rows", 64 * waves), H16
-    assert block(H16, k, T - 1) == ("rows", 64), H16
-assert block(625, 10, 640) == ("rows", 640) and block(625, 10, 639) == ("rows", 64)
+    for t in (T - 1, T * 9 // 10, T * 8 // 10, T * 3 // 4, T * 2 // 3):
+        assert block(H16, k, t) == ("rows", 64 * waves if even(t) else 64), (H16, t)
+for H16, k, T, row in ((625, 10, 640, 1), (625, 10, 639, 0), (625, 10, 512, 1), (625, 10, 513, 0), (625, 10, 448, 1), (625, 10, 447, 0), (333, 8, 700, 1),
+                       (333, 8, 652, 0), (333, 8, 638, 0), (257, 8, 827, 0), (257, 8, 871, 1), (257, 2, 3307, 0), (513, 2, 2300, 0)):
+    assert block(H16, k, T) == ("rows", (64 * -(-H16 // 64) if row else 64)), (H16, k, T)
 for H16, k, T, waves in ((513, 1, 195, 9), (513, 1, 5000, 9), (513, 2, 584, 9), (264, 2, 1136, 5), (264, 1, 2272, 5), (144, 1, 4166, 3), (208, 1, 7000, 4),
                          (208, 4, 2885, 4), (208, 8, 1443, 4)):                     # little work; 4 waves of whole lines
     assert block(H16, k, T) == ("rows", 64 * waves), (H16, k, T)
-for H16, k, T in ((513, 8, 262), (513, 2, 585), (1350, 8, 96), (264, 2, 1137), (264, 1, 2273), (264, 8, 5000), (144, 8, 5000), (144, 1, 4167), (208, 8, 1442)):
+for H16, k, T in ((513, 8, 262), (513, 2, 585), (1350, 8, 96), (264, 2, 1137), (264, 1, 2273), (264, 8, 5000), (144, 8, 5000), (144, 1, 4167), (208, 8, 1050)):
     assert block(H16, k, T) == ("rows", 64), (H16, k, T)
 assert block(112, 8, 2000) == ("rows", 64) and block(512, 8, 2000) == ("rows", 64) and block(512, 8, 2000, 1) == ("rows", 512)
 assert block(512, 4, 60000) == ("rows", 128) and block(513, 4, 60000) == ("rows", 576) and block(272, 4, 60000) == ("rows", 128)
